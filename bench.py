@@ -36,7 +36,7 @@ METRIC = "psi_r evals/s and SCV objective+grad evals/s, batched+adjoint vs plain
 PEAK_FP64_VECTOR = 78.6e12          # MI355X FP64 vector FLOP/s (256 CU x 4 SIMD x 16 lanes x 2 x 2.4 GHz)
 EXP_FLOPS = 20                      # flops charged per exp (the device exp is ~13 FMA + 4 other FP64 ops)
 ROW_KERNEL_SOURCES = ["rows_impl.h", "dev_kernels.h", "dev_common.h", "finish.h", "rows_dispatch.h", "rows_d2.hip",
-                      "rows.hip", "params.h"]
+                      "rows.hip", "params.h", "cols.h", "cols.hip"]
 
 
 def parse():
@@ -89,6 +89,13 @@ def flops_per_run(N, d=2):
     RL, SEG = moment_walk_layout(N)
     return (RL * (2 * 8 + 1) + (3 + 25 * q) + 4 * d * (SEG - 1) / SEG
             + 2 * (2 * d * d + 2 * d + 4 + 2 * EXP_FLOPS) / SEG)
+
+
+def col_walk_flops_per_lag():
+    """FP64 flops of the column walk (variants 5, 6) at one lag, two Gaussians:
+    the run coefficient (1) and three Horner steps (2 each), and per run of 8
+    lags the fold of its three sums (16) and the step to the next run (8)."""
+    return 2 * (1 + 3 * 2 + (16 + 8) / 8)
 
 
 def algorithmic_flops_per_candidate(M, N, d=2, variant=0, rows=None):
@@ -329,7 +336,8 @@ def main():
     RL = moment_walk_layout(N)[0]
     all_runs = (B + 1) * M * (N // RL)
     walked_runs = kf.scv_walk_runs([ds], vechL) if variant >= 5 else all_runs
-    flops = (walked_runs * flops_per_run(N, d) if variant >= 3
+    flops = (walked_runs * RL * col_walk_flops_per_lag() if variant >= 5
+             else walked_runs * flops_per_run(N, d) if variant >= 3
              else algorithmic_flops_per_candidate(M, N, d, variant) * B)
     achieved = flops / (scv_ms * 1e-3)
     spec_flops = algorithmic_flops_per_candidate(M, N, d, spec_variant) * B
@@ -344,8 +352,9 @@ def main():
             ent = rec.get("launches", {}).get(f"{variant},{grid_blocks}")
             if ent:
                 traffic = ent["hbm_bytes_per_launch"]
-    kname = (f"k_lag_mom<2,{N},ScvFun<2,1>,256,{RL},{'true' if variant in (4, 6) else 'false'},"
-             f"{'true' if variant >= 5 else 'false'}> variant {variant}"
+    kname = (f"k_cols_scv<2,1,false> variant {variant}" if variant >= 5 else
+             f"k_lag_mom<2,{N},ScvFun<2,1>,256,{RL},{'true' if variant == 4 else 'false'}>"
+             f" variant {variant}"
              if variant >= 3 else f"k_rows<2,{N},ScvFun<2,1>> variant {variant}")
     kname += " (grid: one block per work item)" if grid_blocks < 0 else " (grid: resident blocks)"
     roofline = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP64_VECTOR / 1e12,
@@ -595,10 +604,12 @@ def main_case5(a):
     if variant >= 3:
         rows = M * (2 * M - 1) ** (d - 2)
         if variant >= 5:   # the compacted walk: the runs it visits, counted on the device
-            flops = kf.scv_walk_runs(dss, vech, per_ds=per) * flops_per_run(P_last, d)
+            flops = (kf.scv_walk_runs(dss, vech, per_ds=per) * moment_walk_layout(P_last)[0]
+                     * col_walk_flops_per_lag())
         else:
             flops = B * algorithmic_flops_per_candidate(M, P_last, d=d, variant=variant, rows=rows)
-        roofline = {"bound": "alu", "kernel": f"k_lag_mom<{d},{P_last},ScvFun<{d},1>> variant {variant}",
+        roofline = {"bound": "alu", "kernel": (f"k_cols_scv<{d},1,false> variant {variant}" if variant >= 5
+                               else f"k_lag_mom<{d},{P_last},ScvFun<{d},1>> variant {variant}"),
                     "launch_ms": lag_ms, "flops_per_launch": flops, "achieved": flops / (lag_ms * 1e-3) / 1e12,
                     "peak": 78.6, "unit": "TFLOP/s", "frac": flops / (lag_ms * 1e-3) / 1e12 / 78.6}
     # one large dataset: binning alone vs full preparation -> count-transform time

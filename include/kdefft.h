@@ -91,8 +91,8 @@ typedef struct kdefft_grid {
  *   alag    float64 [P_0, ..., P_{d-1}]     prod P times the autocorrelation of the
  *                                           counts, A_l = sum_i c_i c_{i+l}, lag l at
  *                                           index l mod P (inverse transform of |C|^2);
- *                                           exact zeros where the last-axis lag has
- *                                           |l_{d-1}| > M_{d-1} - 1 (zero exactly)
+ *                                           exact zeros where some |l_k| > M_k - 1
+ *                                           (zero exactly)
  *   scal    float64 [4]                     scal[0] = n^-2 sum sum phi_{2G} (binned), the
  *                                           constant SCV term, written by every batched
  *                                           SCV objective call on the dataset (0 after
@@ -406,14 +406,14 @@ int kdefft_scv_plain(const kdefft_dataset* ds_host, const double* H_host, double
  * (identical sums, no per-candidate transform); for the SCV families, runs of
  * lags that start below 1e-290 and rise are evaluated lag by lag (3) or
  * walked with values scaled by e^600 (4); the psi and eta families treat 3 and
- * 4 alike and have no spectral variants for eta.  Variants 5 and 6 are 3 and 4
- * with the work compacted: each row's lags whose Gaussians all stay below
- * 1e-30 of their peak are bounded analytically and skipped, and only the
- * remaining runs are dealt to the threads (the dropped terms are far below
- * float64 rounding of the result; the psi and eta families treat 5 and 6 as
- * 3); variant 5 with one block per work item (the untuned default of the SCV
- * families) deals each candidate's rows round-robin over its items and also
- * builds the candidates' parameter blocks inside the launch.
+ * 4 alike and have no spectral variants for eta.  Variants 5 and 6 (one
+ * kernel for both) walk the lag array in columns along axis d-2, 16
+ * neighbouring lags of the last axis together, with every Gaussian whitened by
+ * its Cholesky factor: only the lags whose widest Gaussian reaches 1e-30 of its
+ * peak are walked (found in closed form per column; the dropped terms are far
+ * below float64 rounding of the result), and the launch builds the candidates'
+ * parameters itself.  Variant 5 with one block per work item is the untuned
+ * default of the SCV families; the psi and eta families treat 5 and 6 as 3.
  * The untuned default of the other families is variant 3, grid 0.
  * variant = -1 drops the pinned (or tuned) choice of that key, so the untuned
  * default applies again.  Used by kdefft_autotune and by tests that cover

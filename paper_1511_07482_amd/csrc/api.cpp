@@ -431,8 +431,7 @@ struct BatchScratch {
     double* prm;
     double* partial;
     int32_t* counters;   // completion counters, one per candidate
-    int32_t* wc;         // live segment counts per candidate (balanced plan)
-    int32_t* item_off;   // first item of each candidate (balanced plan)
+    int32_t* wc;         // live run counts per candidate (kdefft_scv_walk_runs)
 };
 
 // Completion of a psi launch: fused into the row kernel for the lag-domain
@@ -468,7 +467,6 @@ BatchScratch carve_batch(Arena& a, const kdefft_grid& g, int kind, int r, int64_
     b.partial = a.take<double>(ncand * need);
     b.counters = a.take<int32_t>(ncand);
     b.wc = a.take<int32_t>(ncand);
-    b.item_off = a.take<int32_t>(ncand + 1);
     return b;
 }
 
@@ -1197,14 +1195,6 @@ static int psi_batch_common(const kdefft_dataset* ds, int n_ds, const double* G_
 // Q_r use the scalar eta_r families.  The dispatch order passed to the row
 // kernels is 2 for the SCV families and r for the eta families (which pick the
 // kernel compiled for r's order class).
-// The balanced plan of the compacted moment walk (variants 5, 6): for
-// candidates with a few thousand rows each and at most MAX_PLAN candidates, on
-// the resident grid (its items are numbered on the device).
-static bool balanced_ok(const RowGeom& geo, int kind, const RowLaunch& rl, int64_t nc) {
-    const bool mom = kind == FUN_SCV_OBJ || kind == FUN_SCV_OBJGRAD || kind == FUN_SCV_GRAD;
-    return mom && rl.variant >= 5 && rl.grid_blocks == 0 && nc <= 1024 && geo.nrows <= 4096;
-}
-
 static int crit_kind(int crit, int r, bool want_grad, bool adjoint) {
     if (crit == KDEFFT_CRIT_QR) return FUN_ETA1;
     if (r > 0) return FUN_ETA2;
@@ -1255,17 +1245,12 @@ static int crit_common(const kdefft_dataset* ds, int n_ds, const int64_t* off, c
     const int npseudo = (crit == KDEFFT_CRIT_SCV && kind != FUN_SCV_GRAD) ? n_ds : 0;
     const int64_t nc = B + npseudo;
     RowGeom geo = make_geom(g, kind, kr, nc, rl.variant);
-    if (balanced_ok(geo, kind, rl, nc)) {
-        geo.nplan = (int)nc;
-        geo.wc = b.wc;
-        geo.item_off = b.item_off;
-    }
     // the criteria complete in their own kernel: fused into the row kernel the
     // assembly lengthens the dominant launch by about what the separate
     // launch costs in a replayed graph
     if (walk_runs) {
         // the live runs of every candidate (the compacted walk's work), summed
-        HIPCHK(launch_scv_setup(vechL, a, B, npseudo, b.prm, status, geo, b.wc, s, true), "criterion setup");
+        HIPCHK(launch_scv_setup(vechL, a, B, npseudo, b.prm, status, geo, b.wc, s), "criterion setup");
         std::vector<int32_t> wc((size_t)nc);
         HIPCHK(hipMemcpyAsync(wc.data(), b.wc, wc.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s), "readback");
         HIPCHK(hipStreamSynchronize(s), "sync");
@@ -1274,12 +1259,9 @@ static int crit_common(const kdefft_dataset* ds, int n_ds, const int64_t* off, c
         *walk_runs = t;
         return KDEFFT_OK;
     }
-    // the compacted lag walk (variant 5) with one block per work item computes
-    // its parameter blocks itself (the balanced plan needs the set-up kernel's
-    // counts; a resident grid takes several items per block)
+    // the column walk (variants 5, 6) computes its parameters in its own launch
     const bool mom = kind == FUN_SCV_OBJ || kind == FUN_SCV_OBJGRAD || kind == FUN_SCV_GRAD;
-    if (mom && rl.variant == 5 && rl.grid_blocks == -1 && geo.nplan == 0) {
-        geo.setup.on = 1;
+    if (mom && rl.variant >= 5) {
         geo.setup.npseudo = npseudo;
         geo.setup.ncand = B;
         geo.setup.vechL = vechL;
@@ -1287,8 +1269,7 @@ static int crit_common(const kdefft_dataset* ds, int n_ds, const int64_t* off, c
         geo.setup.prm_out = b.prm;
         geo.setup.a = a;
     } else {
-        HIPCHK(launch_scv_setup(vechL, a, B, npseudo, b.prm, status, geo, geo.nplan > 0 ? b.wc : nullptr, s),
-               "criterion setup");
+        HIPCHK(launch_scv_setup(vechL, a, B, npseudo, b.prm, status, geo, nullptr, s), "criterion setup");
     }
     HIPCHK(timed_rows(kind, g.d, kr, geo, b.prm, nc, b.partial, rl, s), "criterion rows");
     HIPCHK(launch_scv_final(kind, b.partial, geo, b.prm, B, npseudo, grad_out, obj, grad, s), "criterion final");

@@ -1,0 +1,707 @@
+// Column walk: the lag-domain sums sum_l k(l) A(l) of the batched criteria,
+// walked along axis D-2 of the lag array with 16 neighbouring lags of the last
+// axis on the 16 lanes of a group (D = 1: one lag per lane, no walk).
+//
+// Coordinates.  With S = L L^T in the axis order (0..D-3, D-1, D-2) and
+// y = L^{-1} x, every Gaussian of the family is c exp(-|y|^2 / 2), D^{(x)2} phi =
+// L^{-T} (y y^T - I) L^{-1} phi, and only the last component y_w changes along
+// the walked axis (by u per lag).  A column (fixed lags of the other axes)
+// therefore costs the moments m_p = sum w y_w^p, w = exp(-|y|^2 / 2) A; the
+// products with the fixed components are added once per column, and L^{-1} is
+// applied once per work item.
+//
+// Along a column, with y the walked component at a run's first row,
+//   exp(-(y + u t)^2 / 2) = e r^t g_t,  e = exp(-y^2 / 2), r = exp(-u y),
+//   g_t = exp(-u^2 t^2 / 2) (the same for every column: computed once per item),
+// so a run of RUN = 8 rows is a polynomial in r with the coefficients a_t g_t:
+// one Horner scheme and its two nested ones give sum w, sum s w and
+// sum s(s+1)/2 w (s = t + 1) in four operations per lag and Gaussian.  The next
+// run starts at e r^8 g_8 and r exp(-8 u^2); a column is walked in segments of
+// SEG rows, each started with exponentials.  The constants that carry a walk
+// on are common to all columns, so their rounding would not average out (with
+// plain doubles 1.5e-14 of the d = 3, 4 results): they are kept as two doubles.
+//
+// Bound: FP64 issue (d = 4), the latency of an item's set-up and reductions
+// (few candidates).  16 lanes x 8 bytes are one cache line, so a wavefront's
+// load touches four lines; a row-wise walk (one lane per row run) touches 64
+// and folds 25 flops per Hessian entry into every run.  Whole SCV
+// objective-and-gradient call, replayed: d = 2, M = 256, 256 candidates 53.1 ->
+// 42.9 us, 4 candidates 23.6 -> 16.8 us; d = 3, M = 64, 64 candidates 150 ->
+// 65 us; d = 4, M = 32, four datasets of 64 candidates 3618 -> 979 us (row walk
+// -> column walk).
+//
+// Live set: a lag is walked when its first Gaussian is at or above the cut of
+// its peak (LOG_REL_CUT).  The first Gaussian is the widest of its family
+// (2H + 2G against H + 2G, 2H against H), so it bounds the others; the walk
+// enumerates the box around its ellipsoid and each column's interval is found
+// in closed form.  Every start is at most RUN - 1 lags before a column's live
+// interval, so with u^2 < log 2 no value under- or overflows; a kernel narrower
+// than that is evaluated lag by lag.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "dev_common.h"
+#include "dev_kernels.h"
+#include "finish.h"
+#include "internal.h"
+#include "params.h"
+#include "rows_impl.h"
+
+namespace kdefft {
+
+constexpr int COL_RUN = 8;    // rows per run
+// Rows per segment (one start with exponentials each): D = 2 has few columns
+// to deal out, so they are cut shorter.
+__host__ __device__ constexpr int col_seg(int D) { return D == 2 ? 32 : 64; }
+// Segments of an axis with lags up to lw: D = 2 from lag 0 on (half set);
+// D >= 3 around lag 0, segment s of [-n, n] covering the rows from
+// col_seg * s - col_seg / 2.
+__host__ __device__ constexpr int col_side_segs(int D, int lw) {
+    return D == 2 || lw < col_seg(D) / 2 ? 0 : (lw - col_seg(D) / 2) / col_seg(D) + 1;
+}
+__host__ __device__ constexpr int col_segs(int D, int lw) {
+    return D == 2 ? lw / col_seg(D) + 1 : 2 * col_side_segs(D, lw) + 1;
+}
+constexpr int COL_NT = 256;
+static_assert(COL_RUN == 8, "the run's powers and tables are written for 8 rows");
+
+// Axis at position p of the walk order: the walked axis D-2 last, the last
+// axis (the lanes) before it.
+__host__ __device__ constexpr int col_axis(int D, int p) {
+    return D == 1 ? 0 : (p < D - 2 ? p : (p == D - 2 ? D - 1 : D - 2));
+}
+__host__ __device__ constexpr int col_pos(int D, int axis) {
+    for (int p = 0; p < D; ++p)
+        if (col_axis(D, p) == axis) return p;
+    return 0;
+}
+__host__ __device__ constexpr int tri(int i, int j) { return i * (i + 1) / 2 + j; }
+
+// One Gaussian of an item: L^{-1} in walk order, scaled by the grid spacing (ld:
+// y = ld lag, packed lower) and plain (li), normal constant, run tables.
+template <int D>
+struct ColGauss {
+    double ld[D * (D + 1) / 2];
+    double li[D * D];         // (square, zero above the diagonal)
+    double c;
+    double gt[COL_RUN];   // exp(-u^2 t^2 / 2), t < RUN
+    double h[2], g8[2];   // exp(-RUN u^2) and exp(-RUN^2 u^2 / 2), as high and low parts
+};
+
+// An item's parameters, in LDS.
+template <int D, int NGS>
+struct ColItem {
+    ColGauss<D> g[NGS];
+    double sign;
+    const double* A;
+    int lm[4];   // largest |lag| at each position of the walk order
+};
+
+// Factor A (row stride 4, walk order) in place of its inverse: li = L^{-1} packed
+// lower, *det = |A|^{-1/2}; false if A is not positive definite (then the
+// identity, whose results the caller discards).  One reciprocal root per pivot:
+// the set-up is one lane's serial chain at the start of every item.
+template <int D>
+__device__ __forceinline__ bool col_factor(double (&A)[D][D], bool bad, double* li, double* det) {
+    double r[D];
+    bool ok = !bad;
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+        double s = A[j][j];
+#pragma unroll
+        for (int k = 0; k < j; ++k) s = fma(-A[j][k], A[j][k], s);
+        ok = ok && s > 0.0;
+        r[j] = rsqrt(s > 0.0 ? s : 1.0);
+#pragma unroll
+        for (int i = j + 1; i < D; ++i) {
+            double t = A[i][j];
+#pragma unroll
+            for (int k = 0; k < j; ++k) t = fma(-A[i][k], A[j][k], t);
+            A[i][j] = t * r[j];
+        }
+    }
+    *det = 1.0;
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+        li[tri(i, i)] = ok ? r[i] : 1.0;
+        *det *= li[tri(i, i)];
+#pragma unroll
+        for (int j = 0; j < i; ++j) {
+            double s = 0.0;
+#pragma unroll
+            for (int k = j; k < i; ++k) s = fma(-A[i][k], li[tri(k, j)], s);
+            li[tri(i, j)] = ok ? s * r[i] : 0.0;
+        }
+    }
+    return ok;
+}
+
+// 2^(j/32) as high and low parts.
+static __device__ const double2 COL_EXP2[32] = {
+    {1.0, 0.0}, {1.0218971486541166, 5.109225028973444e-17},
+    {1.0442737824274138, 8.551889705537965e-17}, {1.0671404006768237, -7.899853966841582e-17},
+    {1.0905077326652577, -3.046782079812471e-17}, {1.1143867425958924, 1.0410278456845571e-16},
+    {1.1387886347566916, 8.912812676025408e-17}, {1.1637248587775775, 3.8292048369240935e-17},
+    {1.189207115002721, 3.982015231465646e-17}, {1.215247359980469, -7.712630692681488e-17},
+    {1.241857812073484, 4.658027591836937e-17}, {1.2690509571917332, 2.667932131342186e-18},
+    {1.2968395546510096, 2.5382502794888315e-17}, {1.3252366431597413, -2.8587312100388614e-17},
+    {1.3542555469368927, 7.70094837980299e-17}, {1.383909881963832, -6.770511658794786e-17},
+    {1.4142135623730951, -9.667293313452913e-17}, {1.4451808069770467, -3.0237581349939873e-17},
+    {1.4768261459394993, -3.483994556892796e-17}, {1.5091644275934228, -1.016455327754295e-16},
+    {1.5422108254079407, 7.949834809697621e-17}, {1.5759808451078865, -1.0136916471278304e-17},
+    {1.6104903319492543, 2.4707192569797888e-17}, {1.645755478153965, -1.0125679913674773e-16},
+    {1.681792830507429, 8.199010020581497e-17}, {1.718619298122478, -1.851380418263111e-17},
+    {1.7562521603732995, 2.960140695448873e-17}, {1.7947090750031072, 1.8227458427912087e-17},
+    {1.8340080864093424, 3.283107224245627e-17}, {1.8741676341103, -6.122763413004143e-17},
+    {1.9152065613971474, -1.0619946056195963e-16}, {1.9571441241754002, 8.960767791036668e-17}};
+
+// exp(x + xl) for a small correction xl: x = (32 k + j) log 2 / 32 + r,
+// |r| < 0.011, 2^(j/32) from the table (a copy in LDS), the series of exp(r) to
+// r^6.  One rounding of any weight, so the error is that of one rounding and
+// without a bias; a bias of the start's r would be multiplied by the lags
+// walked (the library's exp left 2e-15 of a d = 3 sum, this 3e-16) -- and it
+// takes half the instructions.
+__device__ __forceinline__ double2 col_exp2(double x, double xl, const double2* tab, int* k) {
+    const double n = rint(x * 46.16624130844683);
+    double r = fma(-n, 0.02166084939249829, x);
+    r = fma(-n, 7.247021293269686e-19, r) + xl;
+    const int ni = (int)n;
+    double p = fma(r, 1.0 / 720.0, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p * r, r, r);
+    const double2 t = tab[ni & 31];
+    *k = ni >> 5;
+    return make_double2(t.x, fma(t.x, p, t.y));
+}
+__device__ __forceinline__ double col_exp(double x, double xl, const double2* tab) {
+    int k;
+    const double2 v = col_exp2(x, xl, tab, &k);
+    return ldexp(v.x + v.y, k);
+}
+// exp(-k u^2) as a high and a low part (to about 2^-59): the constants that
+// carry a walk from run to run are the same for every column, so their
+// rounding would not average out.
+__device__ __forceinline__ double2 col_exp_ku2(double k, double u, const double2* tab) {
+#pragma clang fp contract(off)
+    const double uh = u * u, ul = fma(u, u, -uh), a = k * uh;
+    int n;
+    const double2 v = col_exp2(-a, -(fma(k, uh, -a) + k * ul), tab, &n);
+    const double s = v.x + v.y;
+    return make_double2(ldexp(s, n), ldexp(v.y - (s - v.x), n));
+}
+
+// e = exp(-(q + y^2) / 2) and r = exp(-u y), the roundings of the arguments (up
+// to 69) taken along.
+__device__ __forceinline__ void col_start(double q, double u, double y, const double2* tab, double* e, double* r) {
+#pragma clang fp contract(off)
+    const double yy = y * y, s = q + yy, bb = s - q;
+    const double sl = (q - (s - bb)) + (yy - bb) + fma(y, y, -yy);
+    *e = col_exp(-0.5 * s, -0.5 * sl, tab);
+    const double ru = u * y;
+    *r = col_exp(-ru, -fma(u, y, -ru), tab);
+}
+
+// log of the relative cut, doubled: lags with |y|^2 above it are dropped
+constexpr double COL_CUT2 = -2.0 * LOG_REL_CUT;
+
+// Largest lag along an axis where the Gaussian of variance sd2 is above the
+// cut (hardware root and reciprocal, good to 1e-7: rounded up by that).
+__device__ __forceinline__ int col_reach(double sd2, double delta, int lim) {
+    const double v = 11.7540 * 1.00001 * __builtin_amdgcn_sqrt(sd2) * __builtin_amdgcn_rcp(delta);   // sqrt(COL_CUT2)
+    return (int)fmin(fmax(floor(v) + 1.0, 0.0), (double)lim);   // fmax drops a NaN
+}
+
+// Parameters of candidate h of the SCV / LSCV criteria (h >= ncand: the
+// constant term of dataset h - ncand), as scv_params / pseudo_params define
+// them, by the block's first wavefront: its even lanes factor the first
+// Gaussian, its odd ones the second, and each pair of lanes writes another
+// table entry.  For a candidate's first item the slots that the final kernel
+// reads are stored too.
+template <int D>
+__device__ __forceinline__ void col_scv_setup(const ScvSetup& s, int64_t h, bool first, const RowGeom& geo,
+                                              const double2* tab, ColItem<D, 2>* it) {
+    const ScvBatchArgs& a = s.a;
+    const bool pseudo = h >= s.ncand;
+    int j = 0;
+    if (pseudo) {
+        j = (int)(h - s.ncand);
+    } else {
+        int hi = a.n_ds - 1;
+        while (j < hi) {
+            const int mid = (j + hi + 1) >> 1;
+            if (a.off[mid] <= h)
+                j = mid;
+            else
+                hi = mid - 1;
+        }
+    }
+    const int k = threadIdx.x & 1, t = threadIdx.x >> 1;
+    const DsDev& ds = *a.rec[j];
+    constexpr int q = D * (D + 1) / 2;
+    const bool scv = a.crit == KDEFFT_CRIT_SCV;
+    const double gw = scv ? 2.0 : 0.0, hw = k == 0 ? 2.0 : 1.0;
+    double L[D][D], delta[D];
+    bool sing = false;
+    double ldet = 1.0;
+    int o = 0;
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+        delta[c] = ds.delta[c];
+#pragma unroll
+        for (int i = c; i < D; ++i) {
+            const double v = pseudo ? 0.0 : s.vechL[h * q + o];
+            ++o;
+            L[i][c] = v;
+            sing = sing || !isfinite(v) || (i == c && v == 0.0 && !pseudo);
+        }
+        ldet *= fabs(L[c][c]);
+    }
+    // S in walk order
+    double S[D][D];
+#pragma unroll
+    for (int pi = 0; pi < D; ++pi)
+#pragma unroll
+        for (int pj = 0; pj <= pi; ++pj) {
+            const int i = col_axis(D, pi), c = col_axis(D, pj);
+            double v = 0.0;
+#pragma unroll
+            for (int m = 0; m <= (i < c ? i : c); ++m) v = fma(L[i][m], L[c][m], v);
+            S[pi][pj] = hw * v + gw * ds.G[i * 4 + c];
+        }
+    double sd[D];
+#pragma unroll
+    for (int p = 0; p < D; ++p) sd[p] = S[p][p];
+    double li[q], det;
+    const bool ok = col_factor<D>(S, sing, li, &det);
+    sing = __ballot(ok) != ~0ull;
+    const double n = ds.n;
+    const double c0 = two_pi_pow(D) * det;
+    ColGauss<D>* g = &it->g[k];
+    // the narrowest kernels are evaluated lag by lag and read no tables
+    const double u = fmin(li[tri(D - 1, D - 1)] * delta[col_axis(D, D - 1)], 1.0);
+    const double2 v = col_exp_ku2(t < COL_RUN ? 0.5 * (double)(t * t) : (t == COL_RUN ? 8.0 : 32.0), u, tab);
+    if (t < COL_RUN) g->gt[t] = v.x;
+    if (t == COL_RUN || t == COL_RUN + 1) {
+        double* d = t == COL_RUN ? g->h : g->g8;
+        d[0] = v.x;
+        d[1] = v.y;
+    }
+    if (t == 0) {
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                if (c <= i) g->ld[tri(i, c)] = li[tri(i, c)] * delta[col_axis(D, c)];
+                g->li[i * D + c] = c <= i ? li[tri(i, c)] : 0.0;
+            }
+        const bool exact = a.crit == KDEFFT_CRIT_LSCV_EXACT;
+        g->c = k == 1 && pseudo ? 0.0 : (k == 1 && exact ? c0 * (n / (n - 1.0)) : c0);
+        if (k == 0) {
+            it->A = ds.alag;
+#pragma unroll
+            for (int p = 0; p < D; ++p)
+                it->lm[p] = col_reach(ok ? sd[p] : 1.0, delta[col_axis(D, p)], geo.M[col_axis(D, p)] - 1);
+        } else if (first) {
+            // what the final kernel reads
+            double* p = s.prm_out + h * PRM;
+            double c4 = 1.0;   // (4 pi)^{-d/2}
+#pragma unroll
+            for (int m = 0; m < D; ++m) c4 *= 0.28209479177387814347;
+            const double f = scv ? c4 / (n * ldet) : (exact ? 2.0 / (n - 1.0) : 2.0 / n) * c0;
+            p[S_SCALE] = 1.0 / (n * n * a.prodP);
+            p[S_FIRST] = pseudo ? 0.0 : f;
+            p[S_SING] = sing ? 1.0 : 0.0;
+            p[S_PSEUDO] = !pseudo && s.npseudo > 0 ? (double)(s.ncand + j) : -1.0;
+            put_ptr(p + S_FIN_SCAL, ds.scal);
+            if (s.status && !pseudo) s.status[h] = sing ? 1 : 0;
+#pragma unroll
+            for (int i = 0; i < D; ++i)
+#pragma unroll
+                for (int c = 0; c < D; ++c) p[S_L + i * 4 + c] = c <= i ? L[i][c] : 0.0;
+        }
+    }
+}
+
+// Exchanges within each 16 lanes (DPP): lane ^ 1, ^ 2, then the mirrored lane
+// of the 8 and of the 16, so that four steps of an associative operation
+// leave every lane with the result over its 16.
+template <int CTRL>
+__device__ __forceinline__ int dpp16(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false); }
+template <int CTRL>
+__device__ __forceinline__ double dpp16(double v) {
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)dpp16<CTRL>((int)(uint32_t)b), hi = (uint32_t)dpp16<CTRL>((int)(uint32_t)(b >> 32));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+__device__ __forceinline__ double sum16(double v) {
+    v += dpp16<DPP_XOR1>(v);
+    v += dpp16<DPP_XOR2>(v);
+    v += dpp16<DPP_HALF_MIRROR>(v);
+    return v + dpp16<DPP_MIRROR>(v);
+}
+__device__ __forceinline__ int min16(int v) {
+    v = min(v, dpp16<DPP_XOR1>(v));
+    v = min(v, dpp16<DPP_XOR2>(v));
+    v = min(v, dpp16<DPP_HALF_MIRROR>(v));
+    return min(v, dpp16<DPP_MIRROR>(v));
+}
+__device__ __forceinline__ int max16(int v) { return -min16(-v); }
+
+// Quotient of u / d for u < 2^21 by a reciprocal in float (exact: the float
+// error of (u + 1/2) / d stays below 1 / (2 d)).
+__device__ __forceinline__ int fdiv_small(int u, float rd) { return (int)(((float)u + 0.5f) * rd); }
+
+// Units of one candidate: (plane, segment of the walked axis, block of 16
+// lags of the last axis), numbered with the block fastest.
+template <int D>
+struct ColUnits {
+    int nb, nbp;       // lane blocks, of them on the positive side
+    int nseg, nsn;     // segments, of them on the negative side
+    int n1;            // planes along axis 1 (D = 4)
+    int total;
+    float rnb, rnseg, rn1;
+    // n0lags: lags of axis 0 the item takes (D >= 3)
+    __device__ __forceinline__ ColUnits(const int* lm, int N, bool small, int n0lags) {
+        const int lx = lm[D - 2], lw = lm[D - 1];
+        nbp = N <= 16 ? 1 : lx / 16 + 1;
+        nb = nbp + (N <= 16 ? 0 : (lx + 15) / 16);
+        nsn = small ? 0 : col_side_segs(D, lw);
+        nseg = small ? 1 : col_segs(D, lw);
+        n1 = D == 4 ? 2 * lm[1] + 1 : 1;
+        total = nb * nseg * n1 * n0lags;
+        rnb = 1.0f / (float)nb;
+        rnseg = 1.0f / (float)nseg;
+        rn1 = 1.0f / (float)n1;
+    }
+};
+
+// Candidate and part of an item.  D >= 3: consecutive blocks go to the 8 dies
+// in turn, so die x takes the parts x, x + 8, ... and, of each, all candidates
+// one after the other: their blocks read the same planes of the lag array (at
+// most about 2 MB) while those are in the die's L2.  (Candidate by candidate the
+// d = 4 launch of four datasets missed the L2 on 55 of its 70 million line
+// reads, 5.9 TB/s, and took 1200 us instead of 1048.)
+template <int D>
+__device__ __forceinline__ void col_item(const RowGeom& geo, int64_t item, int64_t nitems, int64_t* h, int* ch) {
+    if (D >= 3 && (geo.nchunks & 7) == 0) {
+        const uint32_t ncand = (uint32_t)(nitems / geo.nchunks), i = (uint32_t)(item >> 3), g = i / ncand;
+        *ch = (int)(g * 8 + (uint32_t)(item & 7));
+        *h = i - g * ncand;
+    } else {
+        *h = item / geo.nchunks;
+        *ch = (int)(item - *h * geo.nchunks);
+    }
+}
+
+// Families of the column walk: ScvFun's modes (0 objective, 1 objective and
+// gradient, 2 gradient).
+// SMALL: the walked axis has P < 16 (at most 7 lags): one segment, rows
+// addressed and masked one by one.
+template <int D, int MODE, bool SMALL>
+__global__ __launch_bounds__(COL_NT, D <= 2 ? 4 : 3) void k_cols_scv(RowGeom geo, int64_t nitems, double* __restrict__ partial) {
+    constexpr int NQ = D * (D + 1) / 2;
+    constexpr int NG = ScvFun<D, MODE>::NG;
+    constexpr int NA = MODE == 0 ? 1 : 1 + NQ;   // sums per Gaussian: sum w, sum w y_a y_b
+    constexpr int NV = 2 * NA;
+    constexpr int SEG = col_seg(D);
+    __shared__ ColItem<D, 2> s_it;
+    __shared__ double s_red[COL_NT / 16][NV], s_tot[NV];
+    __shared__ double2 s_exp[32];
+    const int tid = threadIdx.x, l16 = tid & 15;
+    const int N = geo.P[D - 1];
+    const int Pw = D >= 2 ? geo.P[D >= 2 ? D - 2 : 0] : 1;
+
+    if (tid < 32) s_exp[tid] = COL_EXP2[tid];   // (the first wavefront's own, for the set-up)
+    for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
+        int64_t h;
+        int ch;
+        col_item<D>(geo, item, nitems, &h, &ch);
+        if (tid < 64) col_scv_setup<D>(geo.setup, h, ch == 0, geo, s_exp, &s_it);
+        __syncthreads();
+        double uw[2];
+        bool near1 = true;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            uw[k] = wave_uniform(s_it.g[k].ld[tri(D - 1, D - 1)]);
+            near1 = near1 && uw[k] * uw[k] < 0.69314718055994531;
+        }
+        // (a pointer taken from memory: named global so that its loads are not flat ones)
+        using gptr = const __attribute__((address_space(1))) char*;
+        const gptr A = reinterpret_cast<gptr>(
+            static_cast<uintptr_t>(__double_as_longlong(wave_uniform(__longlong_as_double((long long)(uintptr_t)s_it.A)))));
+        int lm[D];
+#pragma unroll
+        for (int p = 0; p < D; ++p) lm[p] = __builtin_amdgcn_readfirstlane(s_it.lm[p]);
+        double acc[2][NA];
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int i = 0; i < NA; ++i) acc[k][i] = 0.0;
+
+        if constexpr (D == 1) {
+            // one lag per lane, the mirror lag counted by weight 2
+            for (int l = ch * COL_NT + tid; l <= lm[0]; l += (int)geo.nchunks * COL_NT) {
+                const double a = (l == 0 ? 1.0 : 2.0) * *reinterpret_cast<const __attribute__((address_space(1))) double*>(A + (size_t)l * 8);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const double y = uw[k] * (double)l;
+                    const double w = exp(-0.5 * y * y) * a;
+                    acc[k][0] += w;
+                    if constexpr (MODE != 0) acc[k][1] += w * (y * y);
+                }
+            }
+        } else {
+            // D >= 3: item ch takes the lags c0, 2 n0 - 1 - c0, 2 n0 + c0, ... of
+            // axis 0 (c0 = ch mod n0) and every nsub-th block step of their
+            // units; D = 2: every nchunks-th block step
+            const int n0 = D >= 3 ? geo.n0 : 1, c0 = D >= 3 ? ch % n0 : 0;
+            const int sub = D >= 3 ? ch / n0 : ch, nsub = (int)geo.nchunks / n0;
+            auto lag0 = [&](int j) { return j & 1 ? (j + 1) * n0 - 1 - c0 : j * n0 + c0; };
+            const int j0 = lm[0] / n0;
+            const ColUnits<D> un(lm, N, SMALL, D >= 3 ? j0 + (lag0(j0) <= lm[0] ? 1 : 0) : 1);
+            const double iu = 1.0 / uw[0];
+            double g[2][COL_RUN], hh[2][2], g8[2][2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+#pragma unroll
+                for (int t = 1; t < COL_RUN; ++t) g[k][t] = wave_uniform(s_it.g[k].gt[t]);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    hh[k][i] = wave_uniform(s_it.g[k].h[i]);
+                    g8[k][i] = wave_uniform(s_it.g[k].g8[i]);
+                }
+            }
+            const uint32_t strideP = (uint32_t)Pw * (uint32_t)N;   // elements of a plane
+            for (int u = sub * 16 + (tid >> 4); u < un.total; u += nsub * 16) {
+                // decode: block fastest, then segment, then plane
+                int r = fdiv_small(u, un.rnb);
+                const int b = u - r * un.nb;
+                int pl = fdiv_small(r, un.rnseg);
+                const int seg = r - pl * un.nseg;
+                int lag[4] = {0, 0, 0, 0};
+                double rw = 2.0;
+                uint32_t col = 0;   // element offset of the column in the half set (below 2^29: prod P <= 2^30)
+                if constexpr (D == 3) {
+                    lag[0] = lag0(pl);
+                    col += (uint32_t)lag[0] * strideP;
+                }
+                if constexpr (D == 4) {
+                    const int i0 = fdiv_small(pl, un.rn1);
+                    const int l1 = pl - i0 * un.n1 - lm[1];
+                    lag[0] = lag0(i0);
+                    lag[1] = l1;
+                    col += ((uint32_t)lag[0] * (uint32_t)geo.P[1] + (uint32_t)(l1 & (geo.P[1] - 1))) * strideP;
+                }
+                if constexpr (D >= 3) rw = lag[0] == 0 ? 1.0 : 2.0;
+                const int idx = (b < un.nbp ? b * 16 : N - 16 * (b - un.nbp + 1)) + l16;
+                const bool inrow = idx < N;
+                lag[D - 2] = idx < N / 2 ? idx : idx - N;
+                col += inrow ? idx : 0;
+                const int wl = lm[D - 1];
+                const int s0 = SMALL ? (D >= 3 ? -wl : 0) : (seg - un.nsn) * SEG - (D == 2 ? 0 : SEG / 2);
+                // whitened fixed components (and, last, the walked one at lag 0)
+                auto whiten = [&](int k, double* y) {
+#pragma unroll
+                    for (int p = 0; p < D; ++p) {
+                        double v = 0.0;
+#pragma unroll
+                        for (int j = 0; j <= (p < D - 1 ? p : D - 2); ++j) v = fma(s_it.g[k].ld[tri(p, j)], (double)lag[j], v);
+                        y[p] = v;
+                    }
+                };
+                double yE[2], q[2];   // yE: the walked component at lag 0
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    double y[D];
+                    whiten(k, y);
+                    q[k] = 0.0;
+#pragma unroll
+                    for (int p = 0; p < D - 1; ++p) q[k] = fma(y[p], y[p], q[k]);
+                    yE[k] = y[D - 1];
+                }
+                // live rows of this column, as runs of the segment
+                int ca = 127, cb = -1;
+                if (inrow && q[0] <= COL_CUT2) {
+                    const double hw = sqrt(COL_CUT2 - q[0]) * iu, ctr = -yE[0] * iu;
+                    const double lo = s0 > -wl ? s0 : -wl;
+                    const double hi = SMALL || s0 + SEG - 1 > wl ? wl : s0 + SEG - 1;
+                    const double fa = fmax(floor(ctr - hw), lo), fb = fmin(ceil(ctr + hw), hi);
+                    if (fa <= fb) {
+                        ca = ((int)fa - s0) / COL_RUN;
+                        cb = ((int)fb - s0) / COL_RUN;
+                    }
+                }
+                const int ga = min16(ca), gb = max16(cb);
+                if (gb < 0) continue;
+                // uniform base, 32-bit byte offset per lane
+                auto at = [&](int l, int t) {
+                    const uint32_t off = (col + (uint32_t)(l & (Pw - 1)) * (uint32_t)N) * 8u;
+                    return *reinterpret_cast<const __attribute__((address_space(1))) double*>(A + (size_t)t * N * 8 + off);
+                };
+                auto fetch = [&](int c, double* av) {
+                    const int l = s0 + COL_RUN * c;
+#pragma unroll
+                    for (int t = 0; t < COL_RUN; ++t) {
+                        if constexpr (SMALL)
+                            av[t] = l + t <= wl ? at(l + t, 0) : 0.0;
+                        else
+                            av[t] = at(l, t);
+                    }
+                    if (D == 2 && l == 0) av[0] *= 0.5;   // row 0 is its own mirror
+                };
+                double m[2][3];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) m[k][0] = m[k][1] = m[k][2] = 0.0;
+                if (near1) {
+                    double e[2], r[2];   // yE: from here the component at the row before the run
+                    const double ls = (double)(s0 + COL_RUN * (cb >= 0 ? ca : 0));
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const double ys = fma(uw[k], ls, yE[k]);
+                        col_start(q[k], uw[k], ys, s_exp, &e[k], &r[k]);
+                        yE[k] = ys - uw[k];
+                    }
+                    auto run = [&](int c, const double* av) {
+                        if (c < ca) return;   // the lane's column starts in a later run
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            double S0 = 0.0, S1 = 0.0, S2 = 0.0;
+#pragma unroll
+                            for (int t = COL_RUN - 1; t >= 0; --t) {
+                                const double p = t == 0 ? av[0] : av[t] * g[k][t];
+                                S0 = t == COL_RUN - 1 ? p : fma(S0, r[k], p);
+                                if constexpr (MODE != 0) {
+                                    S1 = t == COL_RUN - 1 ? p : fma(S1, r[k], S0);
+                                    S2 = t == COL_RUN - 1 ? p : fma(S2, r[k], S1);
+                                }
+                            }
+                            S0 *= e[k];
+                            m[k][0] += S0;
+                            if constexpr (MODE != 0) {
+                                // y = yE + u s, s = t + 1: S1 = sum s w, S2 = sum s(s+1)/2 w
+                                const double us = uw[k] * e[k];
+                                const double b0 = yE[k] * S0, b1 = us * S1;
+                                m[k][1] += b0 + b1;
+                                m[k][2] = fma(yE[k], fma(2.0, b1, b0), m[k][2]);
+                                m[k][2] = fma(uw[k] * us, fma(2.0, S2, -S1), m[k][2]);
+                                yE[k] = fma(uw[k], (double)COL_RUN, yE[k]);
+                            }
+                            const double r2 = r[k] * r[k], r4 = r2 * r2, r8 = r4 * r4;
+                            e[k] *= fma(r8, g8[k][0], r8 * g8[k][1]);
+                            r[k] = fma(r[k], hh[k][0], r[k] * hh[k][1]);   // (the exact product with the high part)
+                        }
+                    };
+                    double a0[COL_RUN], a1[COL_RUN];   // the next run's loads are in flight over the current one
+                    fetch(ga, a0);
+                    for (int c = ga; c <= gb; c += 2) {
+                        fetch(c < gb ? c + 1 : gb, a1);
+                        run(c, a0);
+                        if (c >= gb) break;
+                        fetch(c + 1 < gb ? c + 2 : gb, a0);
+                        run(c + 1, a1);
+                    }
+                } else if (cb >= 0) {
+                    // narrow kernels: lag by lag
+#pragma unroll 1
+                    for (int l = s0 + COL_RUN * ga; l < s0 + COL_RUN * (gb + 1); ++l) {
+                        double a = 0.0;
+                        if (!SMALL || l <= wl) a = at(l, 0);
+                        if (D == 2 && l == 0) a *= 0.5;
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            const double yw = fma(uw[k], (double)l, yE[k]);
+                            const double w = exp(-0.5 * fma(yw, yw, q[k])) * a;
+                            m[k][0] += w;
+                            if constexpr (MODE != 0) {
+                                m[k][1] = fma(w, yw, m[k][1]);
+                                m[k][2] = fma(w * yw, yw, m[k][2]);
+                            }
+                        }
+                    }
+                }
+                // the column's sums: products with the fixed components
+                // (formed again: kept over the walk they would cost registers)
+#pragma unroll
+                for (int p = 0; p < D - 1; ++p) asm volatile("" : "+v"(lag[p]));
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const double m0 = rw * m[k][0];
+                    acc[k][0] += m0;
+                    if constexpr (MODE != 0) {
+                        double y[D];
+                        whiten(k, y);
+                        const double m1 = rw * m[k][1];
+#pragma unroll
+                        for (int i = 0; i < D - 1; ++i) {
+                            const double t0 = y[i] * m0;
+#pragma unroll
+                            for (int j = 0; j <= i; ++j) acc[k][1 + tri(i, j)] = fma(t0, y[j], acc[k][1 + tri(i, j)]);
+                            acc[k][1 + tri(D - 1, i)] = fma(y[i], m1, acc[k][1 + tri(D - 1, i)]);
+                        }
+                        acc[k][1 + tri(D - 1, D - 1)] = fma(rw, m[k][2], acc[k][1 + tri(D - 1, D - 1)]);
+                    }
+                }
+            }
+        }
+        // block sums in a fixed order, then the outputs: c_k times the sums, the
+        // second-order ones transformed back by L^{-1}
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int i = 0; i < NA; ++i) {
+                const double v = sum16(acc[k][i]);
+                if (l16 == 0) s_red[tid >> 4][k * NA + i] = v;
+            }
+        __syncthreads();
+        if (tid < NV) {
+            double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int w = 0; w < COL_NT / 16; ++w) v[w & 3] += s_red[w][tid];
+            s_tot[tid] = (v[0] + v[1]) + (v[2] + v[3]);
+        }
+        __syncthreads();
+        if (tid < NG) {
+            double out;
+            if (MODE != 2 && tid == 0) {
+                out = s_it.g[0].c * s_tot[0] - 2.0 * s_it.g[1].c * s_tot[NA];
+            } else {
+                // output number tid: D_ij, i <= j in axis order, at its walk positions
+                int pi = 0, pj = 0, o = MODE == 2 ? 0 : 1;
+#pragma unroll
+                for (int i = 0; i < D; ++i)
+#pragma unroll
+                    for (int j = i; j < D; ++j, ++o)
+                        if (tid == o) {
+                            pi = col_pos(D, i);
+                            pj = col_pos(D, j);
+                        }
+                double hs[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const double* li = s_it.g[k].li;
+                    double v = 0.0;
+#pragma unroll
+                    for (int a = 0; a < D; ++a) {
+                        double r = 0.0;
+#pragma unroll
+                        for (int b = 0; b < D; ++b) {
+                            const int ab = MODE == 0 ? 0 : 1 + (a >= b ? tri(a, b) : tri(b, a));
+                            r = fma(s_tot[k * NA + ab] - (a == b ? s_tot[k * NA] : 0.0), li[b * D + pj], r);
+                        }
+                        v = fma(li[a * D + pi], r, v);
+                    }
+                    hs[k] = s_it.g[k].c * v;
+                }
+                out = hs[0] - hs[1];
+            }
+            partial[(h * geo.nchunks + ch) * NG + tid] = out;
+        }
+        __syncthreads();
+    }
+}
+
+}  // namespace kdefft

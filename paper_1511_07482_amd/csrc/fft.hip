@@ -137,16 +137,19 @@ struct RowFlip {
     int on;
     int nlead;
     int P[3];
-    int mlast;   // > 0: positions of the last axis with |lag| > mlast - 1 are written as exact zeros
+    int mlast;   // > 0: positions with |lag| > M - 1 along any axis are written as exact zeros (M of the
+    int M[3];    // last axis: mlast, of the leading ones: M); rows of zeros are not read
 };
 
 // Row indices of the passes are below 2^31 (checked on the host), so rows
 // are decoded with 32-bit divisions.
+// -1: a row of zeros.
 __device__ __forceinline__ int64_t flip_row(int64_t row, const RowFlip& f) {
     uint32_t r = (uint32_t)row, out = 0, mul = 1;
     for (int k = f.nlead - 1; k >= 0; --k) {
         const uint32_t p = (uint32_t)f.P[k], i = r % p;
         r /= p;
+        if (f.mlast > 0 && i >= (uint32_t)f.M[k] && i <= p - (uint32_t)f.M[k]) return -1;
         out += (i == 0 ? 0u : p - i) * mul;
         mul *= p;
     }
@@ -278,7 +281,7 @@ __global__ __launch_bounds__(NT) void k_c2r_last(const double2* __restrict__ in,
     constexpr int PS = H + 1;
     __shared__ double2 buf[ROWS * PS];
     __shared__ double2 twl[N];
-    __shared__ int64_t rsrc[ROWS];   // source row of each row (-1: past the end), decoded once per row
+    __shared__ int64_t rsrc[ROWS];   // source row of each row (-1: past the end or zeros), decoded once per row
     TwiddleCopy<N, NT> twc;
     twc.fetch(tw);
     const int64_t r0 = (int64_t)blockIdx.x * ROWS;
@@ -641,7 +644,7 @@ static hipError_t r2c_last(const double* in, double2* out, int64_t rows, int N, 
 #undef CALL
 }
 static hipError_t c2r_last(const double2* in, double* out, int64_t rows, int N, const double2* tw, hipStream_t s,
-                           RowFlip fl = RowFlip{0, 0, {1, 1, 1}, 0}, int fs = FS_AUTO) {
+                           RowFlip fl = RowFlip{0, 0, {1, 1, 1}, 0, {1, 1, 1}}, int fs = FS_AUTO) {
 #define CALL(NN) run_c2r_last<NN>(in, out, rows, tw, s, fl, fs)
     if (N < 4) return hipErrorInvalidValue;
     KDEFFT_SWITCH_N(ilog2i(N), CALL)
@@ -772,10 +775,13 @@ hipError_t fft_autocorr_nd(const double2* wmix, double* alag, const kdefft_grid&
     if (e != hipSuccess) return e;
     // inverting |C|^2 along the leading axes = the forward transform (wmix)
     // read at negated leading indices; then the last-axis inverse.  Lags with
-    // |l| >= M along the last axis are zero in exact arithmetic (the counts
-    // occupy [0, M)) and are stored as exact zeros.
-    RowFlip fl{g.d > 1 ? 1 : 0, g.d - 1, {1, 1, 1}, g.M[g.d - 1]};
-    for (int k = 0; k + 1 < g.d; ++k) fl.P[k] = g.P[k];
+    // |l| >= M along any axis are zero in exact arithmetic (the counts occupy
+    // [0, M)) and are stored as exact zeros.
+    RowFlip fl{g.d > 1 ? 1 : 0, g.d - 1, {1, 1, 1}, g.M[g.d - 1], {1, 1, 1}};
+    for (int k = 0; k + 1 < g.d; ++k) {
+        fl.P[k] = g.P[k];
+        fl.M[k] = g.M[k];
+    }
     return c2r_last(wmix, alag, lead_count(g), g.P[g.d - 1], tw, s, fl, fs);
 }
 

@@ -10,7 +10,7 @@
 
 namespace kdefft {
 
-constexpr int PRM = 96;     // doubles per candidate parameter block
+constexpr int PRM = 72;     // doubles per candidate parameter block
 constexpr int NT_DEF = 256;  // threads per block of the simple kernels
 
 // Parameter block layout (float64 slots) shared by setup, row and finalize kernels.
@@ -21,13 +21,11 @@ constexpr int NT_DEF = 256;  // threads per block of the simple kernels
 //         [46] constant term  [47] singular flag  [48,64) L (scv) / P3 (plain scv)
 //   criteria: [34] first (closed-form) term  [35] r of eta_r  [36] sign (-1)^r
 //         [37] SCV: the candidate index whose objective sum is the dataset's constant phi_{2G} term
-//   lag walk of Gaussian k (k = 0, 1) at [64 + 8k, 72 + 8k): dz[0..3] = delta_last P_k[i][last],
-//         [4] hpl = delta_last^2 P_k[last][last] / 2, [5] sig = exp(-2 hpl), [6] log(1e-290 / c_k)
 enum Slot { S_P1 = 0, S_C = 16, S_P2 = 16, S_C1 = 32, S_C2 = 33, S_FIRST = 34, S_R = 35, S_SIGN = 36, S_PSEUDO = 37,
             S_ALAG = 38,
             S_WMIX = 39, S_DELTA = 40, S_N = 44, S_SCALE = 45, S_CONST = 46, S_SING = 47, S_L = 48,
             // fused completion (FinishArgs): mode, grids, counter and output pointers
-            S_FIN_MODE = 80, S_FIN_NG = 81, S_FIN_CNT = 82, S_FIN_OUT = 83, S_FIN_SCAL = 84 };
+            S_FIN_MODE = 64, S_FIN_NG = 65, S_FIN_CNT = 66, S_FIN_OUT = 67, S_FIN_SCAL = 68 };
 
 // How a psi lag launch completes (written into every candidate's parameter
 // block by the setup kernels): FIN_NONE = a separate final kernel assembles
@@ -85,12 +83,12 @@ struct ParamBlock {
     double v[64];
 };
 
-// Parameter set-up done by the lag kernel itself (the SCV families on the lag
-// launches): each work item's block computes its candidate's parameter block
-// in LDS from vechL and the dataset records, and the block of the candidate's
-// first item also stores it to prm_out (for the final kernel) and its status.
+// What the column walk (cols.h) needs to compute a candidate's parameters in
+// its own launch: each work item's block factors its candidate's matrices from
+// vechL and the dataset records into LDS, and the block of the candidate's
+// first item also stores the slots the final kernel reads to prm_out (and the
+// status).
 struct ScvSetup {
-    int on;
     int npseudo;
     int64_t ncand;
     const double* vechL;
@@ -106,16 +104,10 @@ struct RowGeom {
     int P[4];
     int64_t nrows;     // rows of the half lag set with nonzero kernel values
     int64_t chunk;     // rows per work item
-    int64_t nchunks;   // work items per candidate (balanced plan: an upper bound of items / candidates)
+    int64_t nchunks;   // work items per candidate
+    int n0;            // column walk, d >= 3: groups of axis-0 lags (nchunks is a multiple)
     int Q;             // P[d-1]/2 + 1
-    // Balanced plan of the compacted moment walk (nplan > 0): the nplan
-    // candidates' live segment counts wc (from the set-up kernel) set how many
-    // items each gets; the launch writes the first item of each candidate to
-    // item_off [nplan + 1] for the final kernel.
-    int nplan;
-    const int32_t* wc;
-    int32_t* item_off;
-    ScvSetup setup;    // setup.on: the SCV lag kernel computes its parameter blocks
+    ScvSetup setup;    // the column walk computes its parameters itself (set for variants 5, 6)
 };
 
 // Kinds of kernel families generated on the lag grid.
@@ -228,9 +220,9 @@ int lag_layout(int N, int moments, int* run_len, int* runs_per_seg, int* rows_pe
 // runs); 5, 6: as 3, 4 with only the live runs of each row dealt to the threads
 constexpr int ROW_VARIANTS = 7;
 // ncand real candidates, then npseudo constant-term candidates (SCV: one per
-// dataset); wc (may be NULL): live segment counts for the balanced plan.
+// dataset); wc (may be NULL) receives the candidates' live run counts.
 hipError_t launch_scv_setup(const double* vechL, const ScvBatchArgs& a, int64_t ncand, int npseudo, double* prm,
-                            int32_t* status, const RowGeom& geo, int32_t* wc, hipStream_t s, bool count_runs = false);
+                            int32_t* status, const RowGeom& geo, int32_t* wc, hipStream_t s);
 hipError_t launch_psi_setup(const PsiBatchArgs& a, double* prm, hipStream_t s);
 hipError_t launch_scv_final(int kind, const double* partial, const RowGeom& geo,
                             const double* prm, int64_t ncand, int npseudo, const double* grad_out,
@@ -250,6 +242,14 @@ hipError_t launch_min_final(int64_t B, int q, const double* st, const int32_t* i
                             int32_t* info, hipStream_t s);
 hipError_t launch_pi(const PiArgs& a, const double* psi4, const double* vechL, int64_t ncand, double* obj,
                      double* grad, int32_t* status, hipStream_t s);
+
+// Column walk of the SCV / LSCV families (cols.h); geo.setup describes the batch.
+hipError_t launch_cols_scv(int kind, const RowGeom& geo, int64_t nitems, double* partial, int grid_blocks,
+                           hipStream_t s);
+// Its work items: geo->nchunks and geo->n0.
+void cols_geom(const kdefft_grid& g, int64_t ncand, RowGeom* geo);
+// Resident blocks of its kernels on the current device.
+int cols_slots();
 
 RowGeom make_geom(const kdefft_grid& g, int kind, int r, int64_t ncand, int variant);
 

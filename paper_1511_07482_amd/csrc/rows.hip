@@ -104,20 +104,6 @@ int rows_per_iter(int kind, int d, int r, int N, int variant) {
     }
 }
 
-// Resident blocks of the compacted lag kernels on the current device: their
-// launch bounds ask for 3 blocks of 256 threads per CU at d <= 2, 2 above.
-static int compact_slots(int d) {
-    static int cus[64] = {0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-    if (cus[dev] <= 0) {
-        int c = 0;
-        if (hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || c < 1) c = 256;
-        cus[dev] = c;
-    }
-    return cus[dev] * (d <= 2 ? 3 : 2);
-}
-
 RowGeom make_geom(const kdefft_grid& g, int kind, int r, int64_t ncand, int variant) {
     RowGeom geo{};
     geo.d = g.d;
@@ -135,39 +121,9 @@ RowGeom make_geom(const kdefft_grid& g, int kind, int r, int64_t ncand, int vari
     int ri = rows_per_iter(kind, g.d, r, g.P[g.d - 1], variant);
     if (ri < 1) ri = 1;
     const bool mom = kind == FUN_SCV_OBJ || kind == FUN_SCV_OBJGRAD || kind == FUN_SCV_GRAD;
-    if (variant >= 5 && mom && nrows <= 4096 && ncand <= 1024) {
-        // compacted walk with a balanced plan (items numbered on the device,
-        // at most one per resident block): candidates x nchunks covers the
-        // resident blocks; the launch without a plan takes the same number of
-        // items per candidate, each with every nchunks-th row of its candidate
-        const int64_t slots = (int64_t)compact_slots(g.d);
-        int64_t per = (slots + ncand - 1) / ncand;
-        // more items than resident slots by more than an eighth of them would
-        // start a large second round of blocks: one round of fewer, larger
-        // items instead (a small overflow is absorbed by the blocks that
-        // finish early)
-        if (per > 1 && ncand * per > slots + slots / 8) per = slots / ncand > 1 ? slots / ncand : 1;
-        if (per > nrows) per = nrows;
-        const int64_t chunk = (nrows + per - 1) / per;
-        geo.chunk = chunk;
-        geo.nchunks = (nrows + chunk - 1) / chunk;
-        return geo;
-    }
     if (variant >= 5 && mom) {
-        // compacted walk: the live runs of a whole item are dealt over the
-        // block at once, so items are sized to the resident blocks instead:
-        // the fewest whole rounds of items over the resident slots that keep an
-        // item at most 4096 rows, the items split evenly over the candidates
-        const int64_t slots = (int64_t)compact_slots(g.d);
-        const int64_t maxrows = 4096;
-        int64_t rounds = (nrows * ncand + slots * maxrows - 1) / (slots * maxrows);
-        if (rounds < 1) rounds = 1;
-        int64_t per = slots * rounds / ncand;
-        if (per < 1) per = 1;
-        if (per > nrows) per = nrows;
-        const int64_t chunk = (nrows + per - 1) / per;
-        geo.chunk = chunk;
-        geo.nchunks = (nrows + chunk - 1) / chunk;
+        cols_geom(g, ncand, &geo);
+        geo.chunk = 0;
         return geo;
     }
     // lag kernel: larger items amortise the per-item set-up and block reduction
@@ -191,6 +147,8 @@ hipError_t launch_rows(int kind, int d, int r, const RowGeom& geo, const double*
     }
     const int64_t nitems = ncand * geo.nchunks;
     const int N = geo.P[d - 1];
+    const bool mom = kind == FUN_SCV_OBJ || kind == FUN_SCV_OBJGRAD || kind == FUN_SCV_GRAD;
+    if (mom && rl.variant >= 5) return launch_cols_scv(kind, geo, nitems, partial, rl.grid_blocks, s);
     if (kind == FUN_ETA1 || kind == FUN_ETA2) {
         switch (d) {
             case 1: return launch_rows_eta_d1(kind, r, N, rl.variant, prm, geo, nitems, partial, rl.grid_blocks, s);
@@ -211,14 +169,12 @@ hipError_t launch_rows(int kind, int d, int r, const RowGeom& geo, const double*
 
 // One wavefront per candidate (real ones, then npseudo constant-term
 // candidates): lane 0 writes the parameter block; with wc set, the wavefront
-// then counts the candidate's live segments over all rows of the half lag set
-// (row_live with the moment walk's run length rl and segment length seg) into
-// wc[c] for the balanced plan of the compacted walk (with seg = 1: its live
-// runs, the work the compacted walk does).
+// then counts the candidate's live runs of rl lags over all rows of the half
+// lag set (row_live) into wc[c].
 template <int D>
 __global__ __launch_bounds__(256) void k_scv_setup(const double* __restrict__ vechL, ScvBatchArgs a, int64_t ncand,
                                                    int npseudo, double* __restrict__ prm,
-                                                   int32_t* __restrict__ status, RowGeom geo, int rl, int seg,
+                                                   int32_t* __restrict__ status, RowGeom geo, int rl,
                                                    int32_t* __restrict__ wc) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t c = (int64_t)blockIdx.x * 4 + wave;
@@ -242,7 +198,7 @@ __global__ __launch_bounds__(256) void k_scv_setup(const double* __restrict__ ve
     int units = 0;
     for (int64_t row = lane; row < geo.nrows; row += 64) {
         const LiveRuns lr = row_live<D>(f, row_info<D>(row, geo.nrows, geo, delta, nullptr), M_last, N, rl, delta[D - 1]);
-        units += (lr.pn + seg - 1) / seg + (lr.nn + seg - 1) / seg;
+        units += lr.pn + lr.nn;
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) units += __shfl_xor(units, off, 64);
@@ -250,16 +206,15 @@ __global__ __launch_bounds__(256) void k_scv_setup(const double* __restrict__ ve
 }
 
 hipError_t launch_scv_setup(const double* vechL, const ScvBatchArgs& a, int64_t ncand, int npseudo, double* prm,
-                            int32_t* status, const RowGeom& geo, int32_t* wc, hipStream_t s, bool count_runs) {
+                            int32_t* status, const RowGeom& geo, int32_t* wc, hipStream_t s) {
     const int64_t blocks = (ncand + npseudo + 3) / 4;
     int rl = 1, seg = 1, rows = 1;
     if (wc && !lag_layout(geo.P[geo.d - 1], 1, &rl, &seg, &rows)) return hipErrorInvalidValue;
-    if (count_runs) seg = 1;   // one run per unit: wc counts the live runs
     switch (a.d) {
-        case 1: hipLaunchKernelGGL(k_scv_setup<1>, dim3((unsigned)blocks), dim3(256), 0, s, vechL, a, ncand, npseudo, prm, status, geo, rl, seg, wc); break;
-        case 2: hipLaunchKernelGGL(k_scv_setup<2>, dim3((unsigned)blocks), dim3(256), 0, s, vechL, a, ncand, npseudo, prm, status, geo, rl, seg, wc); break;
-        case 3: hipLaunchKernelGGL(k_scv_setup<3>, dim3((unsigned)blocks), dim3(256), 0, s, vechL, a, ncand, npseudo, prm, status, geo, rl, seg, wc); break;
-        case 4: hipLaunchKernelGGL(k_scv_setup<4>, dim3((unsigned)blocks), dim3(256), 0, s, vechL, a, ncand, npseudo, prm, status, geo, rl, seg, wc); break;
+        case 1: hipLaunchKernelGGL(k_scv_setup<1>, dim3((unsigned)blocks), dim3(256), 0, s, vechL, a, ncand, npseudo, prm, status, geo, rl, wc); break;
+        case 2: hipLaunchKernelGGL(k_scv_setup<2>, dim3((unsigned)blocks), dim3(256), 0, s, vechL, a, ncand, npseudo, prm, status, geo, rl, wc); break;
+        case 3: hipLaunchKernelGGL(k_scv_setup<3>, dim3((unsigned)blocks), dim3(256), 0, s, vechL, a, ncand, npseudo, prm, status, geo, rl, wc); break;
+        case 4: hipLaunchKernelGGL(k_scv_setup<4>, dim3((unsigned)blocks), dim3(256), 0, s, vechL, a, ncand, npseudo, prm, status, geo, rl, wc); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -345,42 +300,37 @@ hipError_t launch_ds_header(const HeaderArgs& h, hipStream_t s) {
 
 // Criterion assembly, one wavefront per candidate (see crit_finish); the
 // npseudo constant-term candidates after the real ones store their term in
-// their dataset's scalar block.  Work items of candidate c: item_off[c] ..
-// item_off[c + 1] (balanced plan) or c * nchunks + [0, nchunks).
+// their dataset's scalar block.  Work items of candidate c: c * nchunks + [0, nchunks).
 template <int D>
-__global__ __launch_bounds__(64) void k_scv_final(int kind, const double* __restrict__ partial, int64_t nchunks,
-                                                  const int32_t* __restrict__ item_off, int ng,
+__global__ __launch_bounds__(64) void k_scv_final(int kind, const double* __restrict__ partial, int64_t nchunks, int ng,
                                                   const double* __restrict__ prm, int64_t ncand, int npseudo,
                                                   const double* __restrict__ grad_out, double* __restrict__ obj,
                                                   double* __restrict__ grad) {
     const int64_t h = blockIdx.x;
     if (h >= ncand + npseudo) return;
-    auto first_of = [&](int64_t c) { return item_off ? (int64_t)item_off[c] : c * nchunks; };
-    auto count_of = [&](int64_t c) { return item_off ? (int64_t)(item_off[c + 1] - item_off[c]) : nchunks; };
     const double* p = prm + h * PRM;
     if (h >= ncand) {
-        const double v = item_sum(partial, first_of(h), count_of(h), ng, 0) * p[S_SCALE];
+        const double v = item_sum(partial, h * nchunks, nchunks, ng, 0) * p[S_SCALE];
         if (threadIdx.x == 0) static_cast<double*>(slot_ptr(p[S_FIN_SCAL]))[0] = v;
         return;
     }
     double cst = 0.0;
     if (p[S_PSEUDO] >= 0.0) {
         const int64_t c = (int64_t)p[S_PSEUDO];
-        cst = item_sum(partial, first_of(c), count_of(c), ng, 0) * prm[c * PRM + S_SCALE];
+        cst = item_sum(partial, c * nchunks, nchunks, ng, 0) * prm[c * PRM + S_SCALE];
     }
-    crit_finish<D>(kind, partial, first_of(h), count_of(h), ng, p, h, cst, grad_out, obj, grad);
+    crit_finish<D>(kind, partial, h * nchunks, nchunks, ng, p, h, cst, grad_out, obj, grad);
 }
 
 hipError_t launch_scv_final(int kind, const double* partial, const RowGeom& geo, const double* prm, int64_t ncand,
                             int npseudo, const double* grad_out, double* obj, double* grad, hipStream_t s) {
     const int ng = ng_of(kind, geo.d, 2);
     const dim3 grid((unsigned)(ncand + npseudo));
-    const int32_t* off = geo.nplan > 0 ? geo.item_off : nullptr;
     switch (geo.d) {
-        case 1: hipLaunchKernelGGL(k_scv_final<1>, grid, dim3(64), 0, s, kind, partial, geo.nchunks, off, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
-        case 2: hipLaunchKernelGGL(k_scv_final<2>, grid, dim3(64), 0, s, kind, partial, geo.nchunks, off, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
-        case 3: hipLaunchKernelGGL(k_scv_final<3>, grid, dim3(64), 0, s, kind, partial, geo.nchunks, off, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
-        case 4: hipLaunchKernelGGL(k_scv_final<4>, grid, dim3(64), 0, s, kind, partial, geo.nchunks, off, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
+        case 1: hipLaunchKernelGGL(k_scv_final<1>, grid, dim3(64), 0, s, kind, partial, geo.nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
+        case 2: hipLaunchKernelGGL(k_scv_final<2>, grid, dim3(64), 0, s, kind, partial, geo.nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
+        case 3: hipLaunchKernelGGL(k_scv_final<3>, grid, dim3(64), 0, s, kind, partial, geo.nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
+        case 4: hipLaunchKernelGGL(k_scv_final<4>, grid, dim3(64), 0, s, kind, partial, geo.nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -543,201 +543,6 @@ __device__ __forceinline__ LiveRuns row_live(const Fun& f, const RowInfo& ri, in
     return lr;
 }
 
-// Segments (of up to SEG runs) of a row's live runs.
-template <int SEG>
-__device__ __forceinline__ int live_units(const LiveRuns& lr) {
-    return (lr.pn + SEG - 1) / SEG + (lr.nn + SEG - 1) / SEG;
-}
-
-// Exclusive block scan of v (all NT threads); *total receives the sum.  Ends
-// with a barrier, so s_wsum can be reused right away.
-template <int NT>
-__device__ __forceinline__ int block_scan_excl(int v, int* s_wsum, int* total) {
-    constexpr int NW = NT / 64;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int x = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(x, off, 64);
-        if (lane >= off) x += y;
-    }
-    if (lane == 63) s_wsum[wave] = x;
-    __syncthreads();
-    int pre = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        pre += w < wave ? s_wsum[w] : 0;
-        tot += s_wsum[w];
-    }
-    __syncthreads();
-    *total = tot;
-    return pre + x - v;
-}
-
-// Unit word of the per-item segment lists: row << 16 | first run << 8 | runs.
-__device__ __forceinline__ uint32_t unit_word(int row, int run, int nruns) {
-    return (uint32_t)row << 16 | (uint32_t)run << 8 | (uint32_t)nruns;
-}
-
-// Append the segments of a row with live runs lr to the list (positive side,
-// then negative side), numbered from first; only those with numbers in
-// [lo, hi) are written, at s_unit[number - lo].
-template <int SEG>
-__device__ __forceinline__ void write_units(uint32_t* s_unit, int row, const LiveRuns& lr, int first, int lo, int hi) {
-    int o = first;
-    for (int a = 0; a < lr.pn; a += SEG, ++o)
-        if (o >= lo && o < hi) s_unit[o - lo] = unit_word(row, lr.pf + a, lr.pn - a < SEG ? lr.pn - a : SEG);
-    for (int a = 0; a < lr.nn; a += SEG, ++o)
-        if (o >= lo && o < hi) s_unit[o - lo] = unit_word(row, lr.nf + a, lr.nn - a < SEG ? lr.nn - a : SEG);
-}
-
-// Largest number of segments one item's list holds in LDS, and of candidates
-// in a balanced plan.
-constexpr int UNIT_CAP = 4096;
-constexpr int MAX_PLAN = 1024;
-
-// Compacted dealing of an item's rows row0, row0 + rstride, ... (count rows):
-// the rows are taken RB at a time; thread t finds row t's live runs
-// (row_live), a block scan numbers their segments, the segments are listed in
-// LDS (rows in order, runs in order within a row, so neighbouring lanes read
-// neighbouring blocks of the autocorrelation), and the threads walk segments
-// t, t + NT, ... of the list with seg_walk(ri, first run, runs).
-template <int D, int N, int RL, int SEG, int NT, class Fun, class Walk>
-__device__ __forceinline__ void live_segments(const Fun& f, const RowGeom& geo, int64_t row0, int64_t rstride,
-                                              int64_t count, const double* delta, Walk&& seg_walk) {
-    constexpr int NRUN = N / RL;                               // runs per row
-    constexpr int UPR = 2 * ((NRUN / 2 + SEG - 1) / SEG);     // segments per row, at most (both sides)
-    constexpr int RB = NT < UNIT_CAP / UPR ? NT : UNIT_CAP / UPR;   // rows per pass
-    static_assert(NRUN <= 256 && NT <= 256 && RB >= 1, "unit word layout");
-    __shared__ uint32_t s_unit[RB * UPR];
-    __shared__ int s_wsum[NT / 64];
-    const int M_last = geo.M[D - 1];
-    for (int64_t jb = 0; jb < count; jb += RB) {
-        const int nb = count - jb < RB ? (int)(count - jb) : RB;
-        LiveRuns lr{0, 0, 0, 0};
-        if ((int)threadIdx.x < nb)
-            lr = row_live<D>(f, row_info<D>(row0 + (jb + threadIdx.x) * rstride, geo.nrows, geo, delta, nullptr),
-                             M_last, N, RL, delta[D - 1]);
-        int total = 0;
-        const int first = block_scan_excl<NT>(live_units<SEG>(lr), s_wsum, &total);
-        if ((int)threadIdx.x < nb) write_units<SEG>(s_unit, (int)threadIdx.x, lr, first, 0, total);
-        __syncthreads();
-        for (int k = threadIdx.x; k < total; k += NT) {
-            const uint32_t u = s_unit[k];
-            seg_walk(row_info<D>(row0 + (jb + (u >> 16)) * rstride, geo.nrows, geo, delta, nullptr),
-                     (int)((u >> 8) & 255u), (int)(u & 255u));
-        }
-        __syncthreads();
-    }
-}
-
-// Balanced dealing: the item is the window [k W / parts, (k + 1) W / parts) of
-// its candidate's list of W live segments over all nrows rows (rows in order).
-// The rows are scanned in passes of NT (a first sweep counts W when the rows
-// span several passes); the window's segments are listed in LDS, UNIT_CAP at a
-// time, and walked as in live_segments.
-template <int D, int N, int RL, int SEG, int NT, class Fun, class Walk>
-__device__ __forceinline__ void live_window(const Fun& f, const RowGeom& geo, int k, int parts,
-                                            const double* delta, Walk&& seg_walk) {
-    static_assert(N / RL <= 256 && NT <= 256, "unit word layout");
-    __shared__ uint32_t s_unit[UNIT_CAP];
-    __shared__ int s_wsum[NT / 64];
-    const int M_last = geo.M[D - 1];
-    const int64_t nrows = geo.nrows;
-    int64_t wtot = -1;
-    if (nrows > NT) {
-        wtot = 0;
-        for (int64_t rb = 0; rb < nrows; rb += NT) {
-            LiveRuns lr{0, 0, 0, 0};
-            if (rb + threadIdx.x < nrows)
-                lr = row_live<D>(f, row_info<D>(rb + threadIdx.x, nrows, geo, delta, nullptr), M_last, N, RL,
-                                 delta[D - 1]);
-            int total = 0;
-            (void)block_scan_excl<NT>(live_units<SEG>(lr), s_wsum, &total);
-            wtot += total;
-        }
-    }
-    int64_t lo = -1, hi = -1;
-    for (int64_t sub = 0;; sub += UNIT_CAP) {
-        int64_t seen = 0, sl = 0, sh = 0;
-        for (int64_t rb = 0; rb < nrows; rb += NT) {
-            LiveRuns lr{0, 0, 0, 0};
-            if (rb + threadIdx.x < nrows)
-                lr = row_live<D>(f, row_info<D>(rb + threadIdx.x, nrows, geo, delta, nullptr), M_last, N, RL,
-                                 delta[D - 1]);
-            int total = 0;
-            const int first = block_scan_excl<NT>(live_units<SEG>(lr), s_wsum, &total);
-            if (wtot < 0) wtot = total;   // all rows in this one pass
-            if (lo < 0) {
-                lo = (int64_t)k * wtot / parts;
-                hi = (int64_t)(k + 1) * wtot / parts;
-            }
-            sl = lo + sub;
-            sh = hi < sl + UNIT_CAP ? hi : sl + UNIT_CAP;
-            if (rb + threadIdx.x < nrows && seen + first < sh)
-                write_units<SEG>(s_unit, (int)(rb + threadIdx.x), lr, (int)(seen + first - sl), 0, (int)(sh - sl));
-            seen += total;
-            if (seen >= sh) break;   // block-uniform
-        }
-        __syncthreads();
-        for (int u = threadIdx.x; u < sh - sl; u += NT) {
-            const uint32_t w = s_unit[u];
-            seg_walk(row_info<D>(w >> 16, nrows, geo, delta, nullptr), (int)((w >> 8) & 255u), (int)(w & 255u));
-        }
-        __syncthreads();
-        if (sh >= hi) break;
-    }
-}
-
-// Items of the balanced plan (every block computes the same plan from the
-// candidates' live segment counts wc): with W the total, the smallest U (from
-// ceil(W / slots), raised by 1/16 steps) for which giving candidate c
-// max(1, ceil(wc / U)) items keeps the total within max(slots, candidates) (the
-// loop ends: once U exceeds every count each candidate has one item);
-// s_off[c] is candidate c's first item, s_off[nplan] the number of items.
-// Block 0 also stores the offsets for the final kernel.
-template <int NT>
-__device__ __forceinline__ int balanced_plan(const RowGeom& geo, int slots, int* s_off, int* s_wsum) {
-    const int nc = geo.nplan;
-    const int target = slots > nc ? slots : nc;
-    int64_t wl = 0;
-    for (int c = threadIdx.x; c < nc; c += NT) wl += geo.wc[c];
-    int wtot = 0;
-    (void)block_scan_excl<NT>((int)wl, s_wsum, &wtot);
-    int64_t U = (wtot + (int64_t)slots - 1) / slots;
-    if (U < 1) U = 1;
-    for (;;) {
-        int tl = 0;
-        for (int c = threadIdx.x; c < nc; c += NT) {
-            const int64_t n = (geo.wc[c] + U - 1) / U;
-            tl += n > 1 ? (int)n : 1;
-        }
-        int t = 0;
-        (void)block_scan_excl<NT>(tl, s_wsum, &t);
-        if (t <= target) break;   // block-uniform
-        U += U / 16 > 1 ? U / 16 : 1;
-    }
-    // offsets: thread t takes candidates [t * per, (t + 1) * per)
-    const int per = (nc + NT - 1) / NT;
-    int cnt = 0;
-    for (int c = threadIdx.x * per; c < nc && c < (int)(threadIdx.x + 1) * per; ++c) {
-        const int64_t n = (geo.wc[c] + U - 1) / U;
-        cnt += n > 1 ? (int)n : 1;
-    }
-    int total = 0;
-    int o = block_scan_excl<NT>(cnt, s_wsum, &total);
-    for (int c = threadIdx.x * per; c < nc && c < (int)(threadIdx.x + 1) * per; ++c) {
-        const int64_t n = (geo.wc[c] + U - 1) / U;
-        s_off[c] = o;
-        o += n > 1 ? (int)n : 1;
-    }
-    if (threadIdx.x == 0) s_off[nc] = total;
-    __syncthreads();
-    if (blockIdx.x == 0)
-        for (int c = threadIdx.x; c <= nc; c += NT) geo.item_off[c] = s_off[c];
-    return total;
-}
-
 // Lag-domain evaluation for the families with a moment form (SCV / LSCV):
 // runs of RL consecutive array positions of the circular row (see below),
 // their RL autocorrelation values loaded as one aligned block, and per run
@@ -746,9 +551,9 @@ __device__ __forceinline__ int balanced_plan(const RowGeom& geo, int slots, int*
 // rho reached at the end of a run are those of the next run's start, so only
 // the segment's first run (or a run after one that needed special handling)
 // evaluates exponentials.
-template <int D, int N, class Fun, int NT, int RUN, bool SCALED, bool COMPACT>
-__global__ __launch_bounds__(NT, D <= 2 ? (COMPACT ? 3 : 1) : 2) void k_lag_mom(const double* __restrict__ prm, RowGeom geo, int64_t nitems,
-                                            double* __restrict__ partial) {
+template <int D, int N, class Fun, int NT, int RUN, bool SCALED>
+__global__ __launch_bounds__(NT, D <= 2 ? 1 : 2) void k_lag_mom(const double* __restrict__ prm, RowGeom geo,
+                                                             int64_t nitems, double* __restrict__ partial) {
     constexpr int NG = Fun::NG;
     constexpr int NGS = Fun::NGAUSS;
     // Runs of RL consecutive array positions of the circular row: p in [0, N/2)
@@ -766,65 +571,10 @@ __global__ __launch_bounds__(NT, D <= 2 ? (COMPACT ? 3 : 1) : 2) void k_lag_mom(
     // row-major order; the pair is advanced incrementally (no division in the loop)
     constexpr int step_ro = NT / nseg, step_j = NT % nseg;
     const int ro0 = (int)threadIdx.x / nseg, j0 = (int)threadIdx.x % nseg;
-    // balanced plan (compacted walk, geo.nplan candidates): items are windows of
-    // the candidates' live segment lists, numbered by the plan
-    __shared__ int s_off[COMPACT ? MAX_PLAN + 1 : 1];
-    __shared__ int s_pw[NT / 64];
-    int64_t nit = nitems;
-    if constexpr (COMPACT) {
-        if (geo.nplan > 0) nit = balanced_plan<NT>(geo, (int)gridDim.x, s_off, s_pw);
-    }
-    // parameter blocks built in the launch (one block per work item, no plan):
-    // thread 0 computes the block's candidate's parameters into LDS before
-    // anything else is live, and the block of the candidate's first item also
-    // stores them for the final kernel
-    __shared__ double s_prm[COMPACT && !SCALED ? PRM : 1];
-    if constexpr (COMPACT && !SCALED) {
-        if (geo.setup.on) {
-            const int64_t h0 = blockIdx.x / geo.nchunks, ch0 = blockIdx.x - h0 * geo.nchunks;
-            if (threadIdx.x == 0) {
-                if (h0 < geo.setup.ncand)
-                    scv_params<D, false>(geo.setup.vechL, geo.setup.a, h0, geo.setup.ncand, geo.setup.npseudo, s_prm,
-                                         ch0 == 0 ? geo.setup.status : nullptr);
-                else
-                    pseudo_params<D>(geo.setup.a, (int)(h0 - geo.setup.ncand), s_prm);
-                if (ch0 == 0)
-                    for (int i = 0; i < PRM; ++i) geo.setup.prm_out[h0 * PRM + i] = s_prm[i];
-            }
-            __syncthreads();
-        }
-    }
-    for (int64_t item = blockIdx.x; item < nit; item += gridDim.x) {
-        int64_t h, ch = 0;
-        int part = 0, parts = 1;
-        if (COMPACT && geo.nplan > 0) {
-            int lo = 0, hi = geo.nplan - 1;   // the last candidate whose first item is <= item
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (s_off[mid] <= item)
-                    lo = mid;
-                else
-                    hi = mid - 1;
-            }
-            h = lo;
-            part = (int)(item - s_off[lo]);
-            parts = s_off[lo + 1] - s_off[lo];
-        } else {
-            h = item / geo.nchunks;
-            ch = item - h * geo.nchunks;
-        }
-        // the parameter block, uniform over the block: loaded from the
-        // parameter array (scalar loads), or taken from LDS into scalar
-        // registers when the launch built it
-        double pv[PRM];
-        if (COMPACT && !SCALED && geo.setup.on) {
-#pragma unroll
-            for (int i = 0; i < PRM; ++i) pv[i] = wave_uniform(s_prm[i]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < PRM; ++i) pv[i] = prm[h * PRM + i];
-        }
-        const double* pr = pv;
+    for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
+        const int64_t h = item / geo.nchunks;
+        const int64_t ch = item - h * geo.nchunks;
+        const double* pr = prm + h * PRM;
         Fun f;
         f.load(pr);
         double delta[D];
@@ -1043,18 +793,9 @@ __global__ __launch_bounds__(NT, D <= 2 ? (COMPACT ? 3 : 1) : 2) void k_lag_mom(
                 }
             }
         };
-        if constexpr (!COMPACT) {
-            for (int ro = ro0, sg = j0; ro < nro; ro += step_ro + (sg + step_j >= nseg ? 1 : 0),
-                     sg = sg + step_j >= nseg ? sg + step_j - nseg : sg + step_j)
-                seg_walk(row_info<D>(rbeg + ro, rend, geo, delta, nullptr), sg * SEG, SEG);
-        } else {
-            if (geo.nplan > 0)
-                live_window<D, N, RL, SEG, NT>(f, geo, part, parts, delta, seg_walk);
-            else   // the item's rows interleaved with its candidate's other items' (ch, ch + nchunks, ...):
-                   // every item gets a like share of the rows near the kernels' peaks
-                live_segments<D, N, RL, SEG, NT>(f, geo, ch, geo.nchunks, (geo.nrows - ch + geo.nchunks - 1) / geo.nchunks,
-                                                 delta, seg_walk);
-        }
+        for (int ro = ro0, sg = j0; ro < nro; ro += step_ro + (sg + step_j >= nseg ? 1 : 0),
+                 sg = sg + step_j >= nseg ? sg + step_j - nseg : sg + step_j)
+            seg_walk(row_info<D>(rbeg + ro, rend, geo, delta, nullptr), sg * SEG, SEG);
         double outv[NG];
         block_sum<NG, NT>(acc, red, outv);
         if (threadIdx.x == 0) store_item<NG>(pr, partial + item * NG, outv);
@@ -1068,26 +809,23 @@ template <class Fun>
 constexpr int lag_run_of() { return Fun::NG > 12 ? 1 : LAG_RUN; }
 
 
-template <int D, int N, class Fun, int NT, bool SCALED, bool COMPACT>
+template <int D, int N, class Fun, int NT, bool SCALED>
 constexpr auto select_lag() {
     if constexpr (HasMoments<Fun>::value)
-        return k_lag_mom<D, N, Fun, NT, mom_run_of<N>(), SCALED, COMPACT>;
+        return k_lag_mom<D, N, Fun, NT, mom_run_of<N>(), SCALED>;
     else
         return k_lag<D, N, Fun, NT, lag_run_of<Fun>()>;
 }
 
 // variant 3: lag walk, runs that rise from below the float64 range evaluated
-// lag by lag; 4: the same runs walked scaled by e^600; 5, 6: as 3, 4 with the
-// live runs of each row dealt to the threads (compacted).  The psi and eta
-// families (no moment form) run one lag-walk kernel for all four.
+// lag by lag; 4: the same runs walked scaled by e^600 (5 and 6 of the SCV
+// families are the column walk, cols.h).  The psi and eta families (no moment
+// form) run one lag-walk kernel for all.
 template <int D, int N, class Fun>
 hipError_t run_lag_t(const double* prm, RowGeom geo, int64_t nitems, double* partial, int grid_blocks,
                      hipStream_t s, int variant) {
     constexpr int NT = 256;
-    auto kern = variant == 4   ? select_lag<D, N, Fun, NT, true, false>()
-                : variant == 5 ? select_lag<D, N, Fun, NT, false, true>()
-                : variant == 6 ? select_lag<D, N, Fun, NT, true, true>()
-                               : select_lag<D, N, Fun, NT, false, false>();
+    auto kern = variant == 4 ? select_lag<D, N, Fun, NT, true>() : select_lag<D, N, Fun, NT, false>();
     int64_t blocks = nitems;
     if (grid_blocks > 0) {
         blocks = grid_blocks;
