@@ -568,6 +568,7 @@ int prepare_into(const double* X, int64_t n, const kdefft_grid& g, const double*
     for (int k = 0; k < g.d; ++k) {
         h.val.lo[k] = g.lo[k];
         h.val.delta[k] = g.delta[k];
+        h.val.reach[k] = g.M[k] - 1;
     }
     if (Gpilot)
         for (int i = 0; i < g.d; ++i)
@@ -1116,7 +1117,8 @@ int kdefft_dataset_transform(const kdefft_dataset* ds, void* stream) {
     hipStream_t s = S(stream);
     const int fs = fft_sched_for(g);
     HIPCHK(fft_prepare_nd(ds->counts, 0, nullptr, reinterpret_cast<double2*>(ds->spec),
-                          reinterpret_cast<double2*>(ds->wmix), g, s, fs),
+                          reinterpret_cast<double2*>(ds->wmix), g, s, fs,
+                          static_cast<DsDev*>(ds->rec)->reach),
            "count transform");
     HIPCHK(fft_autocorr_nd(reinterpret_cast<const double2*>(ds->wmix), ds->alag, g, s, fs), "count autocorrelation");
     return KDEFFT_OK;

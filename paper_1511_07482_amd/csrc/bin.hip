@@ -148,7 +148,7 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t s) {
 // delta = (hi - lo) / (M - 1); non-finite data give a NaN spacing, so every
 // point counts as out of the grid.  Called by all threads of a block.
 template <int D>
-__device__ __forceinline__ void grid_from_bounds(const HeaderArgs& h, double* lo, double* delta) {
+__device__ __forceinline__ void grid_from_bounds(const HeaderArgs& h, double* lo, double* delta, int* reach) {
 #pragma clang fp contract(off)
     __shared__ double scratch[32], red[8], sg[8];
     reduce_bounds(h.partial, h.nblk, D, scratch, red);
@@ -171,6 +171,10 @@ __device__ __forceinline__ void grid_from_bounds(const HeaderArgs& h, double* lo
     for (int k = 0; k < D; ++k) {
         lo[k] = sg[k];
         delta[k] = sg[4 + k];
+        // the counts' nodes span at most two spacings more than the data do (a
+        // non-finite span keeps the whole axis)
+        const double span = floor((red[4 + k] - red[k]) / delta[k]) + 2.0;
+        reach[k] = span < (double)(h.g.M[k] - 1) ? (int)span : h.g.M[k] - 1;
     }
 }
 
@@ -195,12 +199,14 @@ __global__ __launch_bounds__(256) void k_linbin(const double* __restrict__ X, in
         }
     }
     if (hdr.partial) {   // block-uniform
-        grid_from_bounds<D>(hdr, g.lo, g.delta);
+        int reach[D];
+        grid_from_bounds<D>(hdr, g.lo, g.delta, reach);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             DsDev v = hdr.val;
             for (int k = 0; k < D; ++k) {
                 v.lo[k] = g.lo[k];
                 v.delta[k] = g.delta[k];
+                v.reach[k] = reach[k];
             }
             *hdr.rec = v;
             if (hdr.prm) {

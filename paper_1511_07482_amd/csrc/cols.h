@@ -33,8 +33,9 @@
 // Live set: a lag is walked when its first Gaussian is at or above the cut of
 // its peak (LOG_REL_CUT).  The first Gaussian is the widest of its family
 // (2H + 2G against H + 2G, 2H against H), so it bounds the others; the walk
-// enumerates the box around its ellipsoid and each column's interval is found
-// in closed form.  Every start is at most RUN - 1 lags before a column's live
+// enumerates the box around its ellipsoid, cut to the lags the data reach (the
+// grid is wider by the kernel's padding: the autocorrelation is zero there),
+// and each column's interval is found in closed form.  Every start is at most RUN - 1 lags before a column's live
 // interval, so with u^2 < log 2 no value under- or overflows; a kernel narrower
 // than that is evaluated lag by lag.
 #pragma once
@@ -221,8 +222,8 @@ __device__ __forceinline__ int col_reach(double sd2, double delta, int lim) {
 // table entry.  For a candidate's first item the slots that the final kernel
 // reads are stored too.
 template <int D>
-__device__ __forceinline__ void col_scv_setup(const ScvSetup& s, int64_t h, bool first, const RowGeom& geo,
-                                              const double2* tab, ColItem<D, 2>* it) {
+__device__ __forceinline__ void col_scv_setup(const ScvSetup& s, int64_t h, bool first, const double2* tab,
+                                              ColItem<D, 2>* it) {
     const ScvBatchArgs& a = s.a;
     const bool pseudo = h >= s.ncand;
     int j = 0;
@@ -303,7 +304,7 @@ __device__ __forceinline__ void col_scv_setup(const ScvSetup& s, int64_t h, bool
             it->A = ds.alag;
 #pragma unroll
             for (int p = 0; p < D; ++p)
-                it->lm[p] = col_reach(ok ? sd[p] : 1.0, delta[col_axis(D, p)], geo.M[col_axis(D, p)] - 1);
+                it->lm[p] = col_reach(ok ? sd[p] : 1.0, delta[col_axis(D, p)], ds.reach[col_axis(D, p)]);
         } else if (first) {
             // what the final kernel reads
             double* p = s.prm_out + h * PRM;
@@ -420,7 +421,7 @@ __global__ __launch_bounds__(COL_NT, D <= 2 ? 4 : 3) void k_cols_scv(RowGeom geo
         int64_t h;
         int ch;
         col_item<D>(geo, item, nitems, &h, &ch);
-        if (tid < 64) col_scv_setup<D>(geo.setup, h, ch == 0, geo, s_exp, &s_it);
+        if (tid < 64) col_scv_setup<D>(geo.setup, h, ch == 0, s_exp, &s_it);
         __syncthreads();
         double uw[2];
         bool near1 = true;

@@ -90,6 +90,7 @@ struct CountSrc {
     int P[4];
     int slots;              // counts holds the binning's corner slots, gathered here
     int64_t* sum_out;       // the gathered counts, written when slots is set
+    int32_t* reach;         // if set, receives M - 1 per axis (block 0)
     int prune;              // only the rows inside the counts' box: row r of the launch is the counts'
                             // row r (leading indices over M), stored at its place in the padded grid;
                             // the padding's zero rows are not written (the next pass never reads them)
@@ -171,6 +172,7 @@ __global__ __launch_bounds__(NT) void k_r2c_last(const double* __restrict__ in, 
     twc.fetch(tw);
     const int64_t r0 = (int64_t)blockIdx.x * ROWS;
     const double2* src = reinterpret_cast<const double2*>(in);
+    if (cs.reach && blockIdx.x == 0 && threadIdx.x < (unsigned)cs.d) cs.reach[threadIdx.x] = cs.M[threadIdx.x] - 1;
     if (cs.counts) {
         const double quantum = 9.094947017729282379150390625e-13;  // 2^-40
         const int Ml = cs.M[cs.d - 1];
@@ -636,7 +638,7 @@ static hipError_t run_c2c(double2* buf, double2* out2, int64_t outer, int64_t in
     }
 
 static hipError_t r2c_last(const double* in, double2* out, int64_t rows, int N, const double2* tw, hipStream_t s,
-                           CountSrc cs = CountSrc{nullptr, 0, {0, 0, 0, 0}, {0, 0, 0, 0}, 0, nullptr, 0},
+                           CountSrc cs = CountSrc{nullptr, 0, {0, 0, 0, 0}, {0, 0, 0, 0}, 0, nullptr, nullptr, 0},
                            int fs = FS_AUTO) {
 #define CALL(NN) run_r2c_last<NN>(in, out, rows, tw, s, cs, fs)
     if (N < 4) return hipErrorInvalidValue;
@@ -719,12 +721,12 @@ hipError_t fft_c2r_nd(double2* inout, double* out, const kdefft_grid& g, hipStre
 }
 
 hipError_t fft_prepare_nd(const int64_t* src, int slots, int64_t* counts, double2* spec, double2* wmix,
-                          const kdefft_grid& g, hipStream_t s, int fs) {
+                          const kdefft_grid& g, hipStream_t s, int fs, int32_t* reach) {
     if (fs < 0 || fs >= FFT_SCHEDULES || !shape_ok(g)) return hipErrorInvalidValue;
     const double2* tw;
     hipError_t e = twiddles(&tw);
     if (e != hipSuccess) return e;
-    CountSrc cs{src, g.d, {1, 1, 1, 1}, {1, 1, 1, 1}, slots ? 1 : 0, counts, 1};
+    CountSrc cs{src, g.d, {1, 1, 1, 1}, {1, 1, 1, 1}, slots ? 1 : 0, counts, reach, 1};
     for (int k = 0; k < g.d; ++k) {
         cs.M[k] = g.M[k];
         cs.P[k] = g.P[k];

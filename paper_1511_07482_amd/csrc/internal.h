@@ -51,6 +51,7 @@ struct DsDev {
     double lo[4];      // grid origin and spacing (lo, delta contiguous: the
     double delta[4];   // binning kernel reads them from here on the device path)
     double G[16];   // pilot, row stride 4
+    int32_t reach[4];   // largest |lag| per axis at which the autocorrelation can differ from zero
 };
 
 // Kernel-argument views of a batch (no host-to-device copies per call).
@@ -187,8 +188,10 @@ constexpr int FFT_SCHEDULES = 6;
 // counts directly: src is the count grid itself (slots = 0) or the corner
 // slots of the binning (slots = 1), from which it gathers the counts exactly
 // and also writes them to counts.
+// reach (may be NULL): set to M - 1 per axis (counts that need not be those the
+// dataset was binned with).
 hipError_t fft_prepare_nd(const int64_t* src, int slots, int64_t* counts, double2* spec, double2* wmix,
-                          const kdefft_grid& g, hipStream_t s, int fs);
+                          const kdefft_grid& g, hipStream_t s, int fs, int32_t* reach = nullptr);
 // alag = inverse transform of |C|^2 = prod P times the count autocorrelation,
 // computed from the mixed spectrum (rows at negated leading indices).
 hipError_t fft_autocorr_nd(const double2* wmix, double* alag, const kdefft_grid& g, hipStream_t s, int fs);

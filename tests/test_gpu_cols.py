@@ -74,3 +74,25 @@ def test_column_walk_item_order(kf, gpu):
             assert torch.allclose(o, obj[s:e], rtol=1e-11, atol=0)
             assert torch.allclose(g, grad[s:e], rtol=1e-10, atol=1e-13 * float(g.abs().max()))
         at += b
+
+
+def test_transform_of_replaced_counts(kf, gpu):
+    """The walk is cut to the lags the binned data reach; after the counts are
+    replaced (to the grid's corners) and transformed again it covers them all."""
+    d, M, n = 2, [24, 30], 400
+    X = mixture_sample(n, d, 560)
+    G = spd(d, 561, 0.3)
+    ds = kf.Dataset(torch.from_numpy(X).to(gpu), G, M=M)
+    g = ds.grid
+    c = torch.zeros(M, dtype=torch.int64)
+    c[0, 0] = c[-1, -1] = c[0, -1] = c[-1, 0] = n // 4 << 40
+    at = ds.desc.counts - ds.mem.data_ptr()
+    ds.mem[at:at + 8 * c.numel()] = c.view(-1).view(torch.uint8).to(gpu)
+    ds.transform()
+    H = np.stack([np.eye(2) * s for s in (0.5, 40.0, 900.0)])
+    obj, grad = kf.scv([ds], torch.from_numpy(synth.vech_chol(H)).to(gpu))
+    A = oracle_autocorr(linbin.counts_to_real(c.numpy()))
+    go = grid.plan_auto(X, G, M)
+    assert list(g.M[:d]) == M
+    for b in range(len(H)):
+        check_scv(float(obj[b]), grad[b].cpu().numpy(), A, n, go, H[b], G, what=f"replaced counts b={b}")
