@@ -236,8 +236,10 @@ int nblk_dot(const kdefft_grid& g) {
 
 int64_t max_nchunks(const kdefft_grid& g, int kind, int r, int64_t ncand) {
     int64_t m = 1;
-    for (int v = 0; v < ROW_VARIANTS; ++v) m = std::max(m, make_geom(g, kind, r, ncand, v).nchunks);
-    return m;
+    // row kernels: the spectral variants 0-2, and the lag walks 3, 4
+    for (int v = 0; v < 5; ++v) m = std::max(m, make_geom(g, kind, r, ncand, v).nchunks);
+    const bool eta = kind == FUN_ETA1 || kind == FUN_ETA2;
+    return std::max(m, cols_geom(g, ncand, ng_of(kind, g.d, eta ? 2 : r), kind != FUN_PSI).nchunks);
 }
 
 // ---------------------------------------------------------------- launch choices
@@ -386,19 +388,9 @@ DsLayout carve_dataset(Arena& a, const kdefft_grid& g) {
     return L;
 }
 
-struct PrepScratch {
-    double* prm;
-    double* partial;
-    int64_t* slots;     // corner slots of the binning (2^d int64 per cell)
-    int32_t* counter;   // completion counter of the constant-term launch
-};
-PrepScratch carve_prepare(Arena& a, const kdefft_grid& g) {
-    PrepScratch p;
-    p.prm = a.take<double>(PRM);
-    p.partial = a.take<double>(max_nchunks(g, FUN_PSI, 0, 1));
-    p.slots = a.take<int64_t>(corner_slots(g.d) * sizes_of(g).prodM);
-    p.counter = a.take<int32_t>(1);
-    return p;
+// corner slots of the binning (2^min(d, 3) int64 per cell)
+int64_t* carve_prepare(Arena& a, const kdefft_grid& g) {
+    return a.take<int64_t>(corner_slots(g.d) * sizes_of(g).prodM);
 }
 
 struct PlainScratch {
@@ -430,26 +422,9 @@ PlainScratch carve_plain(Arena& a, const kdefft_grid& g, bool with_counts) {
 struct BatchScratch {
     double* prm;
     double* partial;
-    int32_t* counters;   // completion counters, one per candidate
     int32_t* wc;         // live run counts per candidate (kdefft_scv_walk_runs)
 };
 
-// Completion of a psi launch: fused into the row kernel for the lag-domain
-// variants when a candidate has few work items (every item of a candidate
-// counts on one device-scope counter, so thousands of items would queue on
-// it), else (FIN_NONE) a separate final kernel.
-constexpr int64_t FUSED_MAX_CHUNKS = 128;
-FinishArgs fin_psi(const RowLaunch& rl, const RowGeom& geo, int ng, int32_t* counters, double* psi, double* scal) {
-    FinishArgs f{};
-    if (rl.variant >= 3 && geo.nchunks <= FUSED_MAX_CHUNKS) {
-        f.mode = FIN_PSI;
-        f.ng = ng;
-        f.counters = counters;
-        f.out = psi;
-        f.scal = scal;
-    }
-    return f;
-}
 // Partial sums of the row kernels: sized for every family that may run in
 // this workspace (the SCV families differ in grids per item and chunking).
 BatchScratch carve_batch(Arena& a, const kdefft_grid& g, int kind, int r, int64_t ncand) {
@@ -465,7 +440,6 @@ BatchScratch carve_batch(Arena& a, const kdefft_grid& g, int kind, int r, int64_
             need = std::max<int64_t>(need, max_nchunks(g, k, 2, ncand) * ng_of(k, g.d, 2));
     }
     b.partial = a.take<double>(ncand * need);
-    b.counters = a.take<int32_t>(ncand);
     b.wc = a.take<int32_t>(ncand);
     return b;
 }
@@ -557,7 +531,7 @@ PsiBatchArgs psi_args(const kdefft_grid& g, int r, int n_ds, const DsDev* const*
 // bounds (g then carries the shape only) and the binning scratch was already
 // cleared by the bounds kernel; otherwise g's origin and spacing are used.
 int prepare_into(const double* X, int64_t n, const kdefft_grid& g, const double* Gpilot, const DsLayout& L,
-                 const PrepScratch& p, bool with_const, hipStream_t s, const double* partial = nullptr,
+                 int64_t* slots, hipStream_t s, const double* partial = nullptr,
                  int nblk = 0, const double* pad = nullptr) {
     HeaderArgs h{};
     h.rec = L.rec;
@@ -579,21 +553,16 @@ int prepare_into(const double* X, int64_t n, const kdefft_grid& g, const double*
     for (int k = 0; k < g.d; ++k) h.pad[k] = pad ? pad[k] : 0.0;
     h.n_out = L.n_out;
     h.scal = L.scal;
-    h.prodP = (double)sizes_of(g).prodP;
-    // the constant SCV term n^-2 sum sum phi_{2G} is evaluated by the batched SCV
-    // calls themselves (one more candidate per dataset), so the header writes
-    // no parameter block here
-    (void)with_const;
     if (partial) {
         // grid from the bound partials and the header inside the binning launch
         // (the bounds launch cleared the counter, the scalar block and the slots)
-        HIPCHK(launch_linbin_slots(X, n, g, p.slots, L.n_out, s, nullptr, true, &h), "linbin");
+        HIPCHK(launch_linbin_slots(X, n, g, slots, L.n_out, s, nullptr, true, &h), "linbin");
     } else {
         HIPCHK(launch_ds_header(h, s), "dataset header");
-        HIPCHK(launch_linbin_slots(X, n, g, p.slots, L.n_out, s, nullptr, false), "linbin");
+        HIPCHK(launch_linbin_slots(X, n, g, slots, L.n_out, s, nullptr, false), "linbin");
     }
     const int fs = fft_sched_for(g);
-    HIPCHK(fft_prepare_nd(p.slots, 1, L.counts, L.spec, L.wmix, g, s, fs), "count transform");
+    HIPCHK(fft_prepare_nd(slots, 1, L.counts, L.spec, L.wmix, g, s, fs), "count transform");
     HIPCHK(fft_autocorr_nd(L.wmix, L.alag, g, s, fs), "count autocorrelation");
     return KDEFFT_OK;
 }
@@ -668,19 +637,40 @@ struct RowTimer {
 };
 RowTimer g_timer;
 
-hipError_t timed_rows(int kind, int d, int r, const RowGeom& geo, const double* prm, int64_t ncand,
-                      double* partial, const RowLaunch& rl, hipStream_t s) {
+template <class Launch>
+hipError_t timed_launch(int kind, int r, hipStream_t s, Launch&& launch) {
     std::unique_lock<std::mutex> lk(g_timer.mu);
     if (!g_timer.armed || g_timer.used >= g_timer.cap) {
         lk.unlock();
-        return launch_rows(kind, d, r, geo, prm, ncand, partial, rl, s);
+        return launch();
     }
     const int k = g_timer.used++;
     g_timer.tag[k] = 16 * kind + r;
     hipError_t e = hipEventRecord(g_timer.ev[2 * k], s);
-    if (e == hipSuccess) e = launch_rows(kind, d, r, geo, prm, ncand, partial, rl, s);
+    if (e == hipSuccess) e = launch();
     if (e == hipSuccess) e = hipEventRecord(g_timer.ev[2 * k + 1], s);
     return e;
+}
+
+// psi_r of prepared datasets into psi: the column walk, or for the spectral
+// variants set-up, row kernel and final sums.
+int run_psi(const kdefft_grid& g, const PsiBatchArgs& args, const RowLaunch& rl, const BatchScratch& b, double* psi,
+            hipStream_t s) {
+    const int d = g.d, r = args.r, nu = (int)binom(d + r - 1, r);
+    if (rl.variant >= 3) {
+        const ColGeom geo = cols_geom(g, args.n_ds, nu, false);
+        HIPCHK(timed_launch(FUN_PSI, r, s,
+                            [&] { return launch_cols_psi(geo, args, rl.grid_blocks, b.prm, b.partial, psi, s); }),
+               "psi columns");
+        return KDEFFT_OK;
+    }
+    const RowGeom geo = make_geom(g, FUN_PSI, r, args.n_ds, rl.variant);
+    HIPCHK(launch_psi_setup(args, b.prm, s), "psi setup");
+    HIPCHK(timed_launch(FUN_PSI, r, s,
+                        [&] { return launch_rows(FUN_PSI, d, r, geo, b.prm, args.n_ds, b.partial, rl, s); }),
+           "psi rows");
+    HIPCHK(launch_psi_final(b.partial, geo, nu, b.prm, args.n_ds, psi, s), "psi final");
+    return KDEFFT_OK;
 }
 
 }  // namespace
@@ -911,22 +901,16 @@ int kdefft_psi(const double* X, int64_t n, const kdefft_grid* g, const double* G
     if (!rc) rc = check_rows(FUN_PSI, d, 0, g->P[d - 1]);
     if (rc) return rc;
     const DsLayout L2 = carve_dataset(a, *g);
-    const PrepScratch pp = carve_prepare(a, *g);
+    int64_t* slots = carve_prepare(a, *g);
     const BatchScratch b = carve_batch(a, *g, FUN_PSI, r, 1);
     rc = check_ws(a, ws_bytes);
     if (rc) return rc;
-    rc = prepare_into(X, n, *g, G_host, L2, pp, false, s);
+    rc = prepare_into(X, n, *g, G_host, L2, slots, s);
     if (rc) return rc;
     const DsDev* recs[1] = {L2.rec};
-    PsiBatchArgs args = psi_args(*g, r, 1, recs, G_host);
+    const PsiBatchArgs args = psi_args(*g, r, 1, recs, G_host);
     const RowLaunch rl = launch_for(FUN_PSI, d, r, g->P[d - 1]);
-    const RowGeom geo = make_geom(*g, FUN_PSI, r, 1, rl.variant);
-    args.fin = fin_psi(rl, geo, nu, b.counters, psi, nullptr);
-    HIPCHK(launch_psi_setup(args, b.prm, s), "psi setup");
-    HIPCHK(timed_rows(FUN_PSI, d, r, geo, b.prm, 1, b.partial, rl, s), "psi rows");
-    if (args.fin.mode == FIN_NONE)
-        HIPCHK(launch_psi_final(b.partial, geo, nu, b.prm, 1, psi, nullptr, s), "psi final");
-    return KDEFFT_OK;
+    return run_psi(*g, args, rl, b, psi, s);
 }
 
 int kdefft_fftl_plan(const kdefft_grid* g, const double* S_host, double tau, int32_t* L_host, int32_t* P_host) {
@@ -1029,10 +1013,10 @@ int kdefft_dataset_prepare(const double* X, int64_t n, const kdefft_grid* g, con
     const DsLayout dl = carve_dataset(da, *g);
     if (!da.fits()) return fail(KDEFFT_E_WORKSPACE, "dataset buffer of %zu bytes, need %zu", ds_bytes, da.off);
     Arena a(ws, ws_bytes, false);
-    const PrepScratch p = carve_prepare(a, *g);
+    int64_t* slots = carve_prepare(a, *g);
     rc = check_ws(a, ws_bytes);
     if (rc) return rc;
-    rc = prepare_into(X, n, *g, Gpilot_host, dl, p, true, S(stream));
+    rc = prepare_into(X, n, *g, Gpilot_host, dl, slots, S(stream));
     if (rc) return rc;
     kdefft_dataset o;
     std::memset(&o, 0, sizeof(o));
@@ -1077,7 +1061,7 @@ int kdefft_dataset_prepare_auto(const double* X, int64_t n, int d, const int32_t
     const DsLayout dl = carve_dataset(da, g);
     if (!da.fits()) return fail(KDEFFT_E_WORKSPACE, "dataset buffer of %zu bytes, need %zu", ds_bytes, da.off);
     Arena a(ws, ws_bytes, false);
-    const PrepScratch p = carve_prepare(a, g);
+    int64_t* slots = carve_prepare(a, g);
     const int64_t nb = bound_blocks(n);
     double* partial = a.take<double>(nb * 8);
     rc = check_ws(a, ws_bytes);
@@ -1089,10 +1073,10 @@ int kdefft_dataset_prepare_auto(const double* X, int64_t n, int d, const int32_t
         volatile double pk = pad_sd * sd;   // the same product as kdefft_grid_auto
         pad[k] = pk;
     }
-    HIPCHK(launch_bounds_partial(X, n, d, partial, (int)nb, s, p.slots,
+    HIPCHK(launch_bounds_partial(X, n, d, partial, (int)nb, s, slots,
                                  (size_t)(corner_slots(g.d) * sizes_of(g).prodM) * sizeof(int64_t), dl.n_out, dl.scal),
            "bounds");
-    rc = prepare_into(X, n, g, Gpilot_host, dl, p, true, s, partial, (int)nb, pad);
+    rc = prepare_into(X, n, g, Gpilot_host, dl, slots, s, partial, (int)nb, pad);
     if (rc) return rc;
     kdefft_dataset o;
     std::memset(&o, 0, sizeof(o));
@@ -1179,17 +1163,10 @@ static int psi_batch_common(const kdefft_dataset* ds, int n_ds, const double* G_
     if (rc) return rc;
     std::vector<const DsDev*> recs(n_ds);
     for (int j = 0; j < n_ds; ++j) recs[j] = static_cast<const DsDev*>(ds[j].rec);
-    PsiBatchArgs args = psi_args(g, r, n_ds, recs.data(), Gs.data());
+    const PsiBatchArgs args = psi_args(g, r, n_ds, recs.data(), Gs.data());
     hipStream_t s = S(stream);
     const RowLaunch rl = force ? *force : launch_for(FUN_PSI, d, r, g.P[d - 1]);
-    const int nu = (int)binom(d + r - 1, r);
-    const RowGeom geo = make_geom(g, FUN_PSI, r, n_ds, rl.variant);
-    args.fin = fin_psi(rl, geo, nu, b.counters, psi, nullptr);
-    HIPCHK(launch_psi_setup(args, b.prm, s), "psi setup");
-    HIPCHK(timed_rows(FUN_PSI, d, r, geo, b.prm, n_ds, b.partial, rl, s), "psi rows");
-    if (args.fin.mode == FIN_NONE)
-        HIPCHK(launch_psi_final(b.partial, geo, nu, b.prm, n_ds, psi, nullptr, s), "psi final");
-    return KDEFFT_OK;
+    return run_psi(g, args, rl, b, psi, s);
 }
 
 // Row-kernel family of a criterion: the two-Gaussian SCV families (with the
@@ -1246,12 +1223,9 @@ static int crit_common(const kdefft_dataset* ds, int n_ds, const int64_t* off, c
     // same launch, as one more candidate per dataset after the real ones
     const int npseudo = (crit == KDEFFT_CRIT_SCV && kind != FUN_SCV_GRAD) ? n_ds : 0;
     const int64_t nc = B + npseudo;
-    RowGeom geo = make_geom(g, kind, kr, nc, rl.variant);
-    // the criteria complete in their own kernel: fused into the row kernel the
-    // assembly lengthens the dominant launch by about what the separate
-    // launch costs in a replayed graph
     if (walk_runs) {
         // the live runs of every candidate (the compacted walk's work), summed
+        const RowGeom geo = make_geom(g, kind, kr, nc, 3);
         HIPCHK(launch_scv_setup(vechL, a, B, npseudo, b.prm, status, geo, b.wc, s), "criterion setup");
         std::vector<int32_t> wc((size_t)nc);
         HIPCHK(hipMemcpyAsync(wc.data(), b.wc, wc.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s), "readback");
@@ -1261,20 +1235,34 @@ static int crit_common(const kdefft_dataset* ds, int n_ds, const int64_t* off, c
         *walk_runs = t;
         return KDEFFT_OK;
     }
-    // the column walk (variants 5, 6) computes its parameters in its own launch
+    // the criteria complete in their own kernel: fused into the walk the
+    // assembly lengthens the dominant launch by about what the separate
+    // launch costs in a replayed graph
+    int64_t nchunks = 0;
     const bool mom = kind == FUN_SCV_OBJ || kind == FUN_SCV_OBJGRAD || kind == FUN_SCV_GRAD;
-    if (mom && rl.variant >= 5) {
-        geo.setup.npseudo = npseudo;
-        geo.setup.ncand = B;
-        geo.setup.vechL = vechL;
-        geo.setup.status = status;
-        geo.setup.prm_out = b.prm;
-        geo.setup.a = a;
+    if (mom ? rl.variant >= 5 : (rl.variant == 3 || rl.variant == 4) && cols_eta_ok(g.d, r)) {
+        // the column walk computes its parameters in its own launch
+        const ScvSetup setup{npseudo, B, vechL, status, b.prm, a};
+        const ColGeom geo = cols_geom(g, nc, ng_of(kind, g.d, 2), true);
+        nchunks = geo.nchunks;
+        HIPCHK(timed_launch(kind, kr, s,
+                            [&] {
+                                return mom ? launch_cols_scv(kind, g.d, geo, setup, nc * nchunks, b.partial,
+                                                             rl.grid_blocks, s)
+                                           : launch_cols_eta(kind, g.d, r, geo, setup, nc * nchunks, b.partial,
+                                                             rl.grid_blocks, s);
+                            }),
+               "criterion columns");
     } else {
+        const RowGeom geo = make_geom(g, kind, kr, nc, rl.variant);
+        nchunks = geo.nchunks;
         HIPCHK(launch_scv_setup(vechL, a, B, npseudo, b.prm, status, geo, nullptr, s), "criterion setup");
+        HIPCHK(timed_launch(kind, kr, s,
+                            [&] { return launch_rows(kind, g.d, kr, geo, b.prm, nc, b.partial, rl, s); }),
+               "criterion rows");
     }
-    HIPCHK(timed_rows(kind, g.d, kr, geo, b.prm, nc, b.partial, rl, s), "criterion rows");
-    HIPCHK(launch_scv_final(kind, b.partial, geo, b.prm, B, npseudo, grad_out, obj, grad, s), "criterion final");
+    HIPCHK(launch_scv_final(kind, g.d, b.partial, nchunks, b.prm, B, npseudo, grad_out, obj, grad, s),
+           "criterion final");
     return KDEFFT_OK;
 }
 

@@ -180,8 +180,7 @@ __device__ __forceinline__ void grid_from_bounds(const HeaderArgs& h, double* lo
 
 // hdr.partial set: the dataset header is computed here, not by a separate
 // launch: every block derives the grid origin and spacing from the bound
-// partials (grid_from_bounds), and block 0 writes the dataset record and the
-// parameter block of the constant SCV term for the later launches.
+// partials (grid_from_bounds), and block 0 writes the dataset record.
 template <int D>
 __global__ __launch_bounds__(256) void k_linbin(const double* __restrict__ X, int64_t n, kdefft_grid g,
                                                 const double* __restrict__ gdev,
@@ -209,10 +208,6 @@ __global__ __launch_bounds__(256) void k_linbin(const double* __restrict__ X, in
                 v.reach[k] = reach[k];
             }
             *hdr.rec = v;
-            if (hdr.prm) {
-                psi_params<D>(hdr.Gv2, v, hdr.prodP, hdr.prm);
-                put_finish(hdr.prm, hdr.fin, 0);
-            }
         }
     }
     int64_t stride[D];

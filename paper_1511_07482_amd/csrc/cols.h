@@ -205,25 +205,70 @@ __device__ __forceinline__ void col_start(double q, double u, double y, const do
     *r = col_exp(-ru, -fma(u, y, -ru), tab);
 }
 
-// log of the relative cut, doubled: lags with |y|^2 above it are dropped
-constexpr double COL_CUT2 = -2.0 * LOG_REL_CUT;
+// Lags with |y|^2 above this are dropped: exp(-|y|^2 / 2) below 1e-30, and for
+// families whose terms carry a polynomial of degree K in y (13^K at the cut)
+// below 1e-30 / 13^K, so that every dropped term is below 1e-30 of its
+// Gaussian's peak for all of them.
+__host__ __device__ constexpr double col_cut2(int K) { return -2.0 * LOG_REL_CUT + (K > 2 ? 5.2 * K : 0.0); }
 
 // Largest lag along an axis where the Gaussian of variance sd2 is above the
 // cut (hardware root and reciprocal, good to 1e-7: rounded up by that).
-__device__ __forceinline__ int col_reach(double sd2, double delta, int lim) {
-    const double v = 11.7540 * 1.00001 * __builtin_amdgcn_sqrt(sd2) * __builtin_amdgcn_rcp(delta);   // sqrt(COL_CUT2)
+__device__ __forceinline__ int col_reach(double cut2, double sd2, double delta, int lim) {
+    const double v = 1.00001 * __builtin_amdgcn_sqrt(cut2 * sd2) * __builtin_amdgcn_rcp(delta);
     return (int)fmin(fmax(floor(v) + 1.0, 0.0), (double)lim);   // fmax drops a NaN
 }
 
-// Parameters of candidate h of the SCV / LSCV criteria (h >= ncand: the
-// constant term of dataset h - ncand), as scv_params / pseudo_params define
-// them, by the block's first wavefront: its even lanes factor the first
-// Gaussian, its odd ones the second, and each pair of lanes writes another
-// table entry.  For a candidate's first item the slots that the final kernel
-// reads are stored too.
-template <int D>
-__device__ __forceinline__ void col_scv_setup(const ScvSetup& s, int64_t h, bool first, const double2* tab,
-                                              ColItem<D, 2>* it) {
+// An item's Gaussian k = lane & 1 (k < NGS; with one Gaussian both lanes of a
+// pair do the same) from its matrix S in walk order, by the block's first
+// wavefront: every lane factors, each pair of lanes writes another table entry,
+// lanes 0 and 1 the rest.  Returns the normal constant; *ok is false if S is
+// not positive definite (bad: not finite).
+template <int D, int NGS>
+__device__ __forceinline__ double col_gauss(double (&S)[D][D], const double* delta, bool bad, double cut2,
+                                            const DsDev& ds, const double2* tab, ColItem<D, NGS>* it, bool* ok,
+                                            double* li) {
+    const int k = NGS == 2 ? threadIdx.x & 1 : 0, t = threadIdx.x >> 1;
+    double sd[D], det;
+#pragma unroll
+    for (int p = 0; p < D; ++p) sd[p] = S[p][p];
+    *ok = col_factor<D>(S, bad, li, &det);
+    const double c = two_pi_pow(D) * det;
+    ColGauss<D>* g = &it->g[k];
+    // (the narrowest kernels are evaluated lag by lag and read no tables)
+    const double u = fmin(li[tri(D - 1, D - 1)] * delta[col_axis(D, D - 1)], 1.0);
+    const double2 v = col_exp_ku2(t < COL_RUN ? 0.5 * (double)(t * t) : (t == COL_RUN ? 8.0 : 32.0), u, tab);
+    if (t < COL_RUN) g->gt[t] = v.x;
+    if (t == COL_RUN || t == COL_RUN + 1) {
+        double* d = t == COL_RUN ? g->h : g->g8;
+        d[0] = v.x;
+        d[1] = v.y;
+    }
+    if (t == 0) {
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+#pragma unroll
+            for (int m = 0; m < D; ++m) {
+                if (m <= i) g->ld[tri(i, m)] = li[tri(i, m)] * delta[col_axis(D, m)];
+                g->li[i * D + m] = m <= i ? li[tri(i, m)] : 0.0;
+            }
+        g->c = c;
+        if (k == 0) {
+            it->A = ds.alag;
+#pragma unroll
+            for (int p = 0; p < D; ++p)
+                it->lm[p] = col_reach(cut2, *ok ? sd[p] : 1.0, delta[col_axis(D, p)], ds.reach[col_axis(D, p)]);
+        }
+    }
+    return c;
+}
+
+// Parameters of candidate h of a criterion (h >= ncand: the constant term of
+// dataset h - ncand), as scv_params / pseudo_params define them, by the block's
+// first wavefront.  R: order of eta_r (criteria other than SCV).  For a
+// candidate's first item the slots that the final kernel reads are stored too.
+template <int D, int NGS, int R>
+__device__ __forceinline__ void col_crit_setup(const ScvSetup& s, int64_t h, bool first, double cut2,
+                                               const double2* tab, ColItem<D, NGS>* it) {
     const ScvBatchArgs& a = s.a;
     const bool pseudo = h >= s.ncand;
     int j = 0;
@@ -239,11 +284,11 @@ __device__ __forceinline__ void col_scv_setup(const ScvSetup& s, int64_t h, bool
                 hi = mid - 1;
         }
     }
-    const int k = threadIdx.x & 1, t = threadIdx.x >> 1;
+    const int k = NGS == 2 ? threadIdx.x & 1 : 0, t = threadIdx.x >> 1;
     const DsDev& ds = *a.rec[j];
     constexpr int q = D * (D + 1) / 2;
-    const bool scv = a.crit == KDEFFT_CRIT_SCV;
-    const double gw = scv ? 2.0 : 0.0, hw = k == 0 ? 2.0 : 1.0;
+    const bool scv = a.crit == KDEFFT_CRIT_SCV, qr = a.crit == KDEFFT_CRIT_QR;
+    const double gw = scv ? 2.0 : 0.0, hw = k == 0 && !qr ? 2.0 : 1.0;
     double L[D][D], delta[D];
     bool sing = false;
     double ldet = 1.0;
@@ -272,46 +317,45 @@ __device__ __forceinline__ void col_scv_setup(const ScvSetup& s, int64_t h, bool
             for (int m = 0; m <= (i < c ? i : c); ++m) v = fma(L[i][m], L[c][m], v);
             S[pi][pj] = hw * v + gw * ds.G[i * 4 + c];
         }
-    double sd[D];
-#pragma unroll
-    for (int p = 0; p < D; ++p) sd[p] = S[p][p];
-    double li[q], det;
-    const bool ok = col_factor<D>(S, sing, li, &det);
+    double li[q];
+    bool ok;
+    const double c0 = col_gauss<D, NGS>(S, delta, sing, cut2, ds, tab, it, &ok, li);
     sing = __ballot(ok) != ~0ull;
     const double n = ds.n;
-    const double c0 = two_pi_pow(D) * det;
-    ColGauss<D>* g = &it->g[k];
-    // the narrowest kernels are evaluated lag by lag and read no tables
-    const double u = fmin(li[tri(D - 1, D - 1)] * delta[col_axis(D, D - 1)], 1.0);
-    const double2 v = col_exp_ku2(t < COL_RUN ? 0.5 * (double)(t * t) : (t == COL_RUN ? 8.0 : 32.0), u, tab);
-    if (t < COL_RUN) g->gt[t] = v.x;
-    if (t == COL_RUN || t == COL_RUN + 1) {
-        double* d = t == COL_RUN ? g->h : g->g8;
-        d[0] = v.x;
-        d[1] = v.y;
-    }
     if (t == 0) {
-#pragma unroll
-        for (int i = 0; i < D; ++i)
-#pragma unroll
-            for (int c = 0; c < D; ++c) {
-                if (c <= i) g->ld[tri(i, c)] = li[tri(i, c)] * delta[col_axis(D, c)];
-                g->li[i * D + c] = c <= i ? li[tri(i, c)] : 0.0;
-            }
         const bool exact = a.crit == KDEFFT_CRIT_LSCV_EXACT;
-        g->c = k == 1 && pseudo ? 0.0 : (k == 1 && exact ? c0 * (n / (n - 1.0)) : c0);
-        if (k == 0) {
-            it->A = ds.alag;
-#pragma unroll
-            for (int p = 0; p < D; ++p)
-                it->lm[p] = col_reach(ok ? sd[p] : 1.0, delta[col_axis(D, p)], ds.reach[col_axis(D, p)]);
-        } else if (first) {
+        const double sgn = !scv && !qr && (R & 1) ? -1.0 : 1.0;
+        if (k == 1 && pseudo) it->g[k].c = 0.0;
+        if (k == 1 && exact) it->g[k].c = c0 * (n / (n - 1.0));
+        if (k == 0) it->sign = sgn;
+        if (first && k == NGS - 1) {
             // what the final kernel reads
             double* p = s.prm_out + h * PRM;
-            double c4 = 1.0;   // (4 pi)^{-d/2}
+            double f = 0.0;
+            if (scv) {
+                double c4 = 1.0;   // (4 pi)^{-d/2}
 #pragma unroll
-            for (int m = 0; m < D; ++m) c4 *= 0.28209479177387814347;
-            const double f = scv ? c4 / (n * ldet) : (exact ? 2.0 / (n - 1.0) : 2.0 / n) * c0;
+                for (int m = 0; m < D; ++m) c4 *= 0.28209479177387814347;
+                f = c4 / (n * ldet);
+            } else if (!qr) {
+                // eta_r(0; H) / phi_H(0): 1, -tr Q, (tr Q)^2 + 2 tr Q^2 with Q = L^{-1} L^{-T}
+                double e0 = 1.0;
+                if constexpr (R > 0) {
+                    double tr = 0.0, tr2 = 0.0;
+#pragma unroll
+                    for (int x = 0; x < D; ++x)
+#pragma unroll
+                        for (int y = 0; y < D; ++y) {
+                            double v = 0.0;
+#pragma unroll
+                            for (int m = 0; m <= (x < y ? x : y); ++m) v = fma(li[tri(x, m)], li[tri(y, m)], v);
+                            if (x == y) tr += v;
+                            tr2 = fma(v, v, tr2);
+                        }
+                    e0 = R == 1 ? -tr : fma(tr, tr, 2.0 * tr2);
+                }
+                f = sgn * (exact ? 2.0 / (n - 1.0) : 2.0 / n) * c0 * e0;
+            }
             p[S_SCALE] = 1.0 / (n * n * a.prodP);
             p[S_FIRST] = pseudo ? 0.0 : f;
             p[S_SING] = sing ? 1.0 : 0.0;
@@ -323,6 +367,34 @@ __device__ __forceinline__ void col_scv_setup(const ScvSetup& s, int64_t h, bool
 #pragma unroll
                 for (int c = 0; c < D; ++c) p[S_L + i * 4 + c] = c <= i ? L[i][c] : 0.0;
         }
+    }
+}
+
+// Parameters of psi_r at dataset h's bandwidth; the first item stores what the
+// final kernel reads (L^{-1}, the normal constant times the scale of the sums).
+template <int D>
+__device__ __forceinline__ void col_psi_setup(const PsiBatchArgs& a, int64_t h, bool first, double cut2,
+                                              double* __restrict__ prm, const double2* tab, ColItem<D, 1>* it) {
+    const DsDev& ds = *a.rec[h];
+    double S[D][D], delta[D], li[D * (D + 1) / 2];
+#pragma unroll
+    for (int pi = 0; pi < D; ++pi) {
+        delta[pi] = ds.delta[pi];
+#pragma unroll
+        for (int pj = 0; pj <= pi; ++pj) {
+            const int x = col_axis(D, pi), y = col_axis(D, pj), i = x > y ? x : y, c = x > y ? y : x;
+            S[pi][pj] = a.Gv[h][c * D - c * (c - 1) / 2 + i - c];   // vech: columns of the lower triangle
+        }
+    }
+    bool ok;   // (the bandwidths were validated on the host)
+    const double c0 = col_gauss<D, 1>(S, delta, false, cut2, ds, tab, it, &ok, li);
+    if (first && threadIdx.x == 0) {
+        double* p = prm + h * PRM;
+        p[S_C] = c0 * (1.0 / (ds.n * ds.n * a.prodP));
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+#pragma unroll
+            for (int m = 0; m < D; ++m) p[S_P1 + i * D + m] = m <= i ? li[tri(i, m)] : 0.0;
     }
 }
 
@@ -387,7 +459,7 @@ struct ColUnits {
 // d = 4 launch of four datasets missed the L2 on 55 of its 70 million line
 // reads, 5.9 TB/s, and took 1200 us instead of 1048.)
 template <int D>
-__device__ __forceinline__ void col_item(const RowGeom& geo, int64_t item, int64_t nitems, int64_t* h, int* ch) {
+__device__ __forceinline__ void col_item(const ColGeom& geo, int64_t item, int64_t nitems, int64_t* h, int* ch) {
     if (D >= 3 && (geo.nchunks & 7) == 0) {
         const uint32_t ncand = (uint32_t)(nitems / geo.nchunks), i = (uint32_t)(item >> 3), g = i / ncand;
         *ch = (int)(g * 8 + (uint32_t)(item & 7));
@@ -398,273 +470,387 @@ __device__ __forceinline__ void col_item(const RowGeom& geo, int64_t item, int64
     }
 }
 
-// Families of the column walk: ScvFun's modes (0 objective, 1 objective and
-// gradient, 2 gradient).
-// SMALL: the walked axis has P < 16 (at most 7 lags): one segment, rows
-// addressed and masked one by one.
-template <int D, int MODE, bool SMALL>
-__global__ __launch_bounds__(COL_NT, D <= 2 ? 4 : 3) void k_cols_scv(RowGeom geo, int64_t nitems, double* __restrict__ partial) {
-    constexpr int NQ = D * (D + 1) / 2;
-    constexpr int NG = ScvFun<D, MODE>::NG;
-    constexpr int NA = MODE == 0 ? 1 : 1 + NQ;   // sums per Gaussian: sum w, sum w y_a y_b
-    constexpr int NV = 2 * NA;
-    constexpr int SEG = col_seg(D);
-    __shared__ ColItem<D, 2> s_it;
-    __shared__ double s_red[COL_NT / 16][NV], s_tot[NV];
-    __shared__ double2 s_exp[32];
-    const int tid = threadIdx.x, l16 = tid & 15;
-    const int N = geo.P[D - 1];
-    const int Pw = D >= 2 ? geo.P[D >= 2 ? D - 2 : 0] : 1;
+// Sums of the SCV families over columns, per Gaussian: sum w and (MODE != 0)
+// sum w y_a y_b.
+template <int D, int MODE>
+struct ColScvAcc {
+    static constexpr int NGS = 2;
+    static constexpr int NQ = D * (D + 1) / 2;
+    static constexpr int NA = MODE == 0 ? 1 : 1 + NQ;
+    double v[2][NA];
+    double m[2][3];   // of the current column: sum w y_w^p
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int i = 0; i < NA; ++i) v[k][i] = 0.0;
+    }
+    __device__ __forceinline__ void begin() {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) m[k][0] = m[k][1] = m[k][2] = 0.0;
+    }
+    // a run of COL_RUN rows: values a, start e and ratio r, y = yE + u (t + 1)
+    __device__ __forceinline__ void run(int k, const double* a, const double* g, double e, double r, double yE,
+                                        double u) {
+        double S0 = 0.0, S1 = 0.0, S2 = 0.0;
+#pragma unroll
+        for (int t = COL_RUN - 1; t >= 0; --t) {
+            const double p = t == 0 ? a[0] : a[t] * g[t];
+            S0 = t == COL_RUN - 1 ? p : fma(S0, r, p);
+            if constexpr (MODE != 0) {
+                S1 = t == COL_RUN - 1 ? p : fma(S1, r, S0);
+                S2 = t == COL_RUN - 1 ? p : fma(S2, r, S1);
+            }
+        }
+        S0 *= e;
+        m[k][0] += S0;
+        if constexpr (MODE != 0) {
+            // S1 = sum s w, S2 = sum s(s+1)/2 w, s = t + 1
+            const double us = u * e, b0 = yE * S0, b1 = us * S1;
+            m[k][1] += b0 + b1;
+            m[k][2] = fma(yE, fma(2.0, b1, b0), m[k][2]);
+            m[k][2] = fma(u * us, fma(2.0, S2, -S1), m[k][2]);
+        }
+    }
+    // one lag: weight w, walked component y
+    __device__ __forceinline__ void lag(int k, double w, double y) {
+        m[k][0] += w;
+        if constexpr (MODE != 0) {
+            m[k][1] = fma(w, y, m[k][1]);
+            m[k][2] = fma(w * y, y, m[k][2]);
+        }
+    }
+    // the end of a column: fixed components y, column weight rw
+    __device__ __forceinline__ void column(int k, double rw, const double* y) {
+        const double m0 = rw * m[k][0];
+        v[k][0] += m0;
+        if constexpr (MODE != 0) {
+            const double m1 = rw * m[k][1];
+#pragma unroll
+            for (int i = 0; i < D - 1; ++i) {
+                const double t0 = y[i] * m0;
+#pragma unroll
+                for (int j = 0; j <= i; ++j) v[k][1 + tri(i, j)] = fma(t0, y[j], v[k][1 + tri(i, j)]);
+                v[k][1 + tri(D - 1, i)] = fma(y[i], m1, v[k][1 + tri(D - 1, i)]);
+            }
+            v[k][1 + tri(D - 1, D - 1)] = fma(rw, m[k][2], v[k][1 + tri(D - 1, D - 1)]);
+        }
+    }
+};
 
+// Sums of the derivative families over columns, per Gaussian: with the
+// whitened Hermite tensors He_alpha(y) = prod_p He_{alpha_p}(y_p),
+// D^{(x)K} phi = (-1)^K (L^{-T})^{(x)K} He_K(y) phi, so the sums of order K need
+// only v_alpha = sum w He_alpha, |alpha| = K: the moments He_0..He_K of the
+// walked component along a column, and the products with the fixed ones' once
+// per column.
+template <int D, int K, int N_GS>
+struct ColHermAcc {
+    static constexpr int NGS = N_GS;
+    using T = HermTab<D, K>;
+    static constexpr int NA = T::NU;
+    double v[NGS][NA];
+    double m[NGS][K + 1];
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int k = 0; k < NGS; ++k)
+#pragma unroll
+            for (int i = 0; i < NA; ++i) v[k][i] = 0.0;
+    }
+    __device__ __forceinline__ void begin() {
+#pragma unroll
+        for (int k = 0; k < NGS; ++k)
+#pragma unroll
+            for (int i = 0; i <= K; ++i) m[k][i] = 0.0;
+    }
+    static __device__ __forceinline__ void hermite(double y, double* he) {
+        he[0] = 1.0;
+        if constexpr (K > 0) he[1] = y;
+#pragma unroll
+        for (int i = 2; i <= K; ++i) he[i] = i == 2 ? fma(y, y, -1.0) : fma(y, he[i - 1], -(double)(i - 1) * he[i - 2]);
+    }
+    __device__ __forceinline__ void lag(int k, double w, double y) {
+        double he[K + 1];
+        hermite(y, he);
+        m[k][0] += w;
+#pragma unroll
+        for (int i = 1; i <= K; ++i) m[k][i] = fma(w, he[i], m[k][i]);
+    }
+    __device__ __forceinline__ void run(int k, const double* a, const double* g, double e, double r, double yE,
+                                        double u) {
+#pragma unroll
+        for (int t = 0; t < COL_RUN; ++t) {
+            const double w = e * (t == 0 ? a[0] : a[t] * g[t]);
+            lag(k, w, fma(u, (double)(t + 1), yE));
+            e *= r;
+        }
+    }
+    template <int U, int... P>
+    static __device__ __forceinline__ double lead(const double (*he)[K + 1], std::integer_sequence<int, P...>) {
+        double x = 1.0;
+        ((T::tab.a[T::NB - T::NU + U][P] > 0 ? (x *= he[P][T::tab.a[T::NB - T::NU + U][P]]) : 0.0), ...);
+        return x;
+    }
+    template <int... U>
+    __device__ __forceinline__ void add(int k, double rw, const double (*he)[K + 1], std::integer_sequence<int, U...>) {
+        ((v[k][U] = fma(rw * lead<U>(he, std::make_integer_sequence<int, D - 1>{}),
+                        m[k][T::tab.a[T::NB - T::NU + U][D - 1]], v[k][U])),
+         ...);
+    }
+    __device__ __forceinline__ void column(int k, double rw, const double* y) {
+        double he[D > 1 ? D - 1 : 1][K + 1];
+#pragma unroll
+        for (int p = 0; p < D - 1; ++p) hermite(y[p], he[p]);
+        add(k, rw, he, std::make_integer_sequence<int, NA>{});
+    }
+};
+
+// Grid size for nitems work items (cols.hip).
+int64_t cols_blocks(int64_t nitems, int grid_blocks);
+
+// Part ch of an item's candidate, walked into acc (see the top).  SMALL: the
+// walked axis has P < 16 (at most 7 lags): one segment, rows addressed and
+// masked one by one.
+template <int D, bool SMALL, class Acc>
+__device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColItem<D, Acc::NGS>& it,
+                                         const double2* s_exp, double cut2, Acc& acc) {
+    constexpr int NGS = Acc::NGS;
+    const int tid = threadIdx.x, l16 = tid & 15;
+    double uw[NGS];
+    bool near1 = true;
+#pragma unroll
+    for (int k = 0; k < NGS; ++k) {
+        uw[k] = wave_uniform(it.g[k].ld[tri(D - 1, D - 1)]);
+        near1 = near1 && uw[k] * uw[k] < 0.69314718055994531;
+    }
+    // (a pointer taken from memory: named global so that its loads are not flat ones)
+    using gptr = const __attribute__((address_space(1))) char*;
+    const gptr A = reinterpret_cast<gptr>(static_cast<uintptr_t>(
+        __double_as_longlong(wave_uniform(__longlong_as_double((long long)(uintptr_t)it.A)))));
+    using gdbl = const __attribute__((address_space(1))) double*;
+    int lm[D];
+#pragma unroll
+    for (int p = 0; p < D; ++p) lm[p] = __builtin_amdgcn_readfirstlane(it.lm[p]);
+
+    if constexpr (D == 1) {
+        // one lag per lane, the mirror lag counted by weight 2
+        acc.begin();
+        for (int l = ch * COL_NT + tid; l <= lm[0]; l += (int)geo.nchunks * COL_NT) {
+            const double a = (l == 0 ? 1.0 : 2.0) * *reinterpret_cast<gdbl>(A + (size_t)l * 8);
+#pragma unroll
+            for (int k = 0; k < NGS; ++k) {
+                const double y = uw[k] * (double)l;
+                acc.lag(k, exp(-0.5 * y * y) * a, y);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NGS; ++k) acc.column(k, 1.0, nullptr);
+    } else {
+        constexpr int SEG = col_seg(D);
+        const int N = geo.P[D - 1], Pw = geo.P[D - 2];
+        // D >= 3: part ch takes the lags c0, 2 n0 - 1 - c0, 2 n0 + c0, ... of
+        // axis 0 (c0 = ch mod n0) and every nsub-th block step of their units;
+        // D = 2: every nchunks-th block step
+        const int n0 = D >= 3 ? geo.n0 : 1, c0 = D >= 3 ? ch % n0 : 0;
+        const int sub = D >= 3 ? ch / n0 : ch, nsub = (int)geo.nchunks / n0;
+        auto lag0 = [&](int j) { return j & 1 ? (j + 1) * n0 - 1 - c0 : j * n0 + c0; };
+        const int j0 = lm[0] / n0;
+        const ColUnits<D> un(lm, N, SMALL, D >= 3 ? j0 + (lag0(j0) <= lm[0] ? 1 : 0) : 1);
+        const double iu = 1.0 / uw[0];
+        double g[NGS][COL_RUN], hh[NGS][2], g8[NGS][2];
+#pragma unroll
+        for (int k = 0; k < NGS; ++k) {
+#pragma unroll
+            for (int t = 1; t < COL_RUN; ++t) g[k][t] = wave_uniform(it.g[k].gt[t]);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                hh[k][i] = wave_uniform(it.g[k].h[i]);
+                g8[k][i] = wave_uniform(it.g[k].g8[i]);
+            }
+        }
+        const uint32_t strideP = (uint32_t)Pw * (uint32_t)N;   // elements of a plane
+        for (int u = sub * 16 + (tid >> 4); u < un.total; u += nsub * 16) {
+            // decode: block fastest, then segment, then plane
+            const int rs = fdiv_small(u, un.rnb);
+            const int b = u - rs * un.nb;
+            const int pl = fdiv_small(rs, un.rnseg);
+            const int seg = rs - pl * un.nseg;
+            int lag[D];
+            double rw = 2.0;
+            uint32_t col = 0;   // element offset of the column in the half set (below 2^29: prod P <= 2^30)
+            if constexpr (D == 3) {
+                lag[0] = lag0(pl);
+                col += (uint32_t)lag[0] * strideP;
+            }
+            if constexpr (D == 4) {
+                const int i0 = fdiv_small(pl, un.rn1);
+                const int l1 = pl - i0 * un.n1 - lm[1];
+                lag[0] = lag0(i0);
+                lag[1] = l1;
+                col += ((uint32_t)lag[0] * (uint32_t)geo.P[1] + (uint32_t)(l1 & (geo.P[1] - 1))) * strideP;
+            }
+            if constexpr (D >= 3) rw = lag[0] == 0 ? 1.0 : 2.0;
+            const int idx = (b < un.nbp ? b * 16 : N - 16 * (b - un.nbp + 1)) + l16;
+            const bool inrow = idx < N;
+            lag[D - 2] = idx < N / 2 ? idx : idx - N;
+            col += inrow ? idx : 0;
+            const int wl = lm[D - 1];
+            const int s0 = SMALL ? (D >= 3 ? -wl : 0) : (seg - un.nsn) * SEG - (D == 2 ? 0 : SEG / 2);
+            // whitened fixed components (and, last, the walked one at lag 0)
+            auto whiten = [&](int k, double* y) {
+#pragma unroll
+                for (int p = 0; p < D; ++p) {
+                    double v = 0.0;
+#pragma unroll
+                    for (int j = 0; j <= (p < D - 1 ? p : D - 2); ++j) v = fma(it.g[k].ld[tri(p, j)], (double)lag[j], v);
+                    y[p] = v;
+                }
+            };
+            double yE[NGS], q[NGS];   // yE: the walked component at lag 0
+#pragma unroll
+            for (int k = 0; k < NGS; ++k) {
+                double y[D];
+                whiten(k, y);
+                q[k] = 0.0;
+#pragma unroll
+                for (int p = 0; p < D - 1; ++p) q[k] = fma(y[p], y[p], q[k]);
+                yE[k] = y[D - 1];
+            }
+            // live rows of this column, as runs of the segment
+            int ca = 127, cb = -1;
+            if (inrow && q[0] <= cut2) {
+                const double hw = sqrt(cut2 - q[0]) * iu, ctr = -yE[0] * iu;
+                const double lo = s0 > -wl ? s0 : -wl;
+                const double hi = SMALL || s0 + SEG - 1 > wl ? wl : s0 + SEG - 1;
+                const double fa = fmax(floor(ctr - hw), lo), fb = fmin(ceil(ctr + hw), hi);
+                if (fa <= fb) {
+                    ca = ((int)fa - s0) / COL_RUN;
+                    cb = ((int)fb - s0) / COL_RUN;
+                }
+            }
+            const int ga = min16(ca), gb = max16(cb);
+            if (gb < 0) continue;
+            // uniform base, 32-bit byte offset per lane
+            auto at = [&](int l, int t) {
+                const uint32_t off = (col + (uint32_t)(l & (Pw - 1)) * (uint32_t)N) * 8u;
+                return *reinterpret_cast<gdbl>(A + (size_t)t * N * 8 + off);
+            };
+            auto fetch = [&](int c, double* av) {
+                const int l = s0 + COL_RUN * c;
+#pragma unroll
+                for (int t = 0; t < COL_RUN; ++t) {
+                    if constexpr (SMALL)
+                        av[t] = l + t <= wl ? at(l + t, 0) : 0.0;
+                    else
+                        av[t] = at(l, t);
+                }
+                if (D == 2 && l == 0) av[0] *= 0.5;   // row 0 is its own mirror
+            };
+            acc.begin();
+            if (near1) {
+                double e[NGS], r[NGS];   // yE: from here the component at the row before the run
+                const double ls = (double)(s0 + COL_RUN * (cb >= 0 ? ca : 0));
+#pragma unroll
+                for (int k = 0; k < NGS; ++k) {
+                    const double ys = fma(uw[k], ls, yE[k]);
+                    col_start(q[k], uw[k], ys, s_exp, &e[k], &r[k]);
+                    yE[k] = ys - uw[k];
+                }
+                auto run = [&](int c, const double* av) {
+                    if (c < ca) return;   // the lane's column starts in a later run
+#pragma unroll
+                    for (int k = 0; k < NGS; ++k) {
+                        acc.run(k, av, g[k], e[k], r[k], yE[k], uw[k]);
+                        yE[k] = fma(uw[k], (double)COL_RUN, yE[k]);
+                        const double r2 = r[k] * r[k], r4 = r2 * r2, r8 = r4 * r4;
+                        e[k] *= fma(r8, g8[k][0], r8 * g8[k][1]);   // (exact products with the high parts)
+                        r[k] = fma(r[k], hh[k][0], r[k] * hh[k][1]);
+                    }
+                };
+                double a0[COL_RUN], a1[COL_RUN];   // the next run's loads are in flight over the current one
+                fetch(ga, a0);
+                for (int c = ga; c <= gb; c += 2) {
+                    fetch(c < gb ? c + 1 : gb, a1);
+                    run(c, a0);
+                    if (c >= gb) break;
+                    fetch(c + 1 < gb ? c + 2 : gb, a0);
+                    run(c + 1, a1);
+                }
+            } else if (cb >= 0) {
+                // narrow kernels: lag by lag
+#pragma unroll 1
+                for (int l = s0 + COL_RUN * ga; l < s0 + COL_RUN * (gb + 1); ++l) {
+                    double a = 0.0;
+                    if (!SMALL || l <= wl) a = at(l, 0);
+                    if (D == 2 && l == 0) a *= 0.5;
+#pragma unroll
+                    for (int k = 0; k < NGS; ++k) {
+                        const double yw = fma(uw[k], (double)l, yE[k]);
+                        acc.lag(k, exp(-0.5 * fma(yw, yw, q[k])) * a, yw);
+                    }
+                }
+            }
+            // the column's sums: products with the fixed components (formed
+            // again: kept over the walk they would cost registers)
+#pragma unroll
+            for (int p = 0; p < D - 1; ++p) asm volatile("" : "+v"(lag[p]));
+#pragma unroll
+            for (int k = 0; k < NGS; ++k) {
+                double y[D];
+                whiten(k, y);
+                acc.column(k, rw, y);
+            }
+        }
+    }
+}
+
+// Block sums of the accumulators, fixed order, into s_tot [NGS * NA].
+template <class Acc>
+__device__ __forceinline__ void col_reduce(const Acc& acc, double (*s_red)[Acc::NGS * Acc::NA], double* s_tot) {
+    constexpr int NV = Acc::NGS * Acc::NA;
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < Acc::NGS; ++k)
+#pragma unroll
+        for (int i = 0; i < Acc::NA; ++i) {
+            const double v = sum16(acc.v[k][i]);
+            if ((tid & 15) == 0) s_red[tid >> 4][k * Acc::NA + i] = v;
+        }
+    __syncthreads();
+    if (tid < NV) {
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int w = 0; w < COL_NT / 16; ++w) v[w & 3] += s_red[w][tid];
+        s_tot[tid] = (v[0] + v[1]) + (v[2] + v[3]);
+    }
+    __syncthreads();
+}
+
+// The SCV families: ScvFun's modes (0 objective, 1 objective and gradient,
+// 2 gradient).
+template <int D, int MODE, bool SMALL>
+__global__ __launch_bounds__(COL_NT, D <= 2 ? 4 : 3) void k_cols_scv(ColGeom geo, ScvSetup setup, int64_t nitems,
+                                                                     double* __restrict__ partial) {
+    using Acc = ColScvAcc<D, MODE>;
+    constexpr int NG = ScvFun<D, MODE>::NG, NA = Acc::NA;
+    constexpr double cut2 = col_cut2(2);
+    __shared__ ColItem<D, 2> s_it;
+    __shared__ double s_red[COL_NT / 16][2 * NA], s_tot[2 * NA];
+    __shared__ double2 s_exp[32];
+    const int tid = threadIdx.x;
     if (tid < 32) s_exp[tid] = COL_EXP2[tid];   // (the first wavefront's own, for the set-up)
     for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
         int64_t h;
         int ch;
         col_item<D>(geo, item, nitems, &h, &ch);
-        if (tid < 64) col_scv_setup<D>(geo.setup, h, ch == 0, s_exp, &s_it);
+        if (tid < 64) col_crit_setup<D, 2, 0>(setup, h, ch == 0, cut2, s_exp, &s_it);
         __syncthreads();
-        double uw[2];
-        bool near1 = true;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            uw[k] = wave_uniform(s_it.g[k].ld[tri(D - 1, D - 1)]);
-            near1 = near1 && uw[k] * uw[k] < 0.69314718055994531;
-        }
-        // (a pointer taken from memory: named global so that its loads are not flat ones)
-        using gptr = const __attribute__((address_space(1))) char*;
-        const gptr A = reinterpret_cast<gptr>(
-            static_cast<uintptr_t>(__double_as_longlong(wave_uniform(__longlong_as_double((long long)(uintptr_t)s_it.A)))));
-        int lm[D];
-#pragma unroll
-        for (int p = 0; p < D; ++p) lm[p] = __builtin_amdgcn_readfirstlane(s_it.lm[p]);
-        double acc[2][NA];
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-#pragma unroll
-            for (int i = 0; i < NA; ++i) acc[k][i] = 0.0;
-
-        if constexpr (D == 1) {
-            // one lag per lane, the mirror lag counted by weight 2
-            for (int l = ch * COL_NT + tid; l <= lm[0]; l += (int)geo.nchunks * COL_NT) {
-                const double a = (l == 0 ? 1.0 : 2.0) * *reinterpret_cast<const __attribute__((address_space(1))) double*>(A + (size_t)l * 8);
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    const double y = uw[k] * (double)l;
-                    const double w = exp(-0.5 * y * y) * a;
-                    acc[k][0] += w;
-                    if constexpr (MODE != 0) acc[k][1] += w * (y * y);
-                }
-            }
-        } else {
-            // D >= 3: item ch takes the lags c0, 2 n0 - 1 - c0, 2 n0 + c0, ... of
-            // axis 0 (c0 = ch mod n0) and every nsub-th block step of their
-            // units; D = 2: every nchunks-th block step
-            const int n0 = D >= 3 ? geo.n0 : 1, c0 = D >= 3 ? ch % n0 : 0;
-            const int sub = D >= 3 ? ch / n0 : ch, nsub = (int)geo.nchunks / n0;
-            auto lag0 = [&](int j) { return j & 1 ? (j + 1) * n0 - 1 - c0 : j * n0 + c0; };
-            const int j0 = lm[0] / n0;
-            const ColUnits<D> un(lm, N, SMALL, D >= 3 ? j0 + (lag0(j0) <= lm[0] ? 1 : 0) : 1);
-            const double iu = 1.0 / uw[0];
-            double g[2][COL_RUN], hh[2][2], g8[2][2];
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-#pragma unroll
-                for (int t = 1; t < COL_RUN; ++t) g[k][t] = wave_uniform(s_it.g[k].gt[t]);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    hh[k][i] = wave_uniform(s_it.g[k].h[i]);
-                    g8[k][i] = wave_uniform(s_it.g[k].g8[i]);
-                }
-            }
-            const uint32_t strideP = (uint32_t)Pw * (uint32_t)N;   // elements of a plane
-            for (int u = sub * 16 + (tid >> 4); u < un.total; u += nsub * 16) {
-                // decode: block fastest, then segment, then plane
-                int r = fdiv_small(u, un.rnb);
-                const int b = u - r * un.nb;
-                int pl = fdiv_small(r, un.rnseg);
-                const int seg = r - pl * un.nseg;
-                int lag[4] = {0, 0, 0, 0};
-                double rw = 2.0;
-                uint32_t col = 0;   // element offset of the column in the half set (below 2^29: prod P <= 2^30)
-                if constexpr (D == 3) {
-                    lag[0] = lag0(pl);
-                    col += (uint32_t)lag[0] * strideP;
-                }
-                if constexpr (D == 4) {
-                    const int i0 = fdiv_small(pl, un.rn1);
-                    const int l1 = pl - i0 * un.n1 - lm[1];
-                    lag[0] = lag0(i0);
-                    lag[1] = l1;
-                    col += ((uint32_t)lag[0] * (uint32_t)geo.P[1] + (uint32_t)(l1 & (geo.P[1] - 1))) * strideP;
-                }
-                if constexpr (D >= 3) rw = lag[0] == 0 ? 1.0 : 2.0;
-                const int idx = (b < un.nbp ? b * 16 : N - 16 * (b - un.nbp + 1)) + l16;
-                const bool inrow = idx < N;
-                lag[D - 2] = idx < N / 2 ? idx : idx - N;
-                col += inrow ? idx : 0;
-                const int wl = lm[D - 1];
-                const int s0 = SMALL ? (D >= 3 ? -wl : 0) : (seg - un.nsn) * SEG - (D == 2 ? 0 : SEG / 2);
-                // whitened fixed components (and, last, the walked one at lag 0)
-                auto whiten = [&](int k, double* y) {
-#pragma unroll
-                    for (int p = 0; p < D; ++p) {
-                        double v = 0.0;
-#pragma unroll
-                        for (int j = 0; j <= (p < D - 1 ? p : D - 2); ++j) v = fma(s_it.g[k].ld[tri(p, j)], (double)lag[j], v);
-                        y[p] = v;
-                    }
-                };
-                double yE[2], q[2];   // yE: the walked component at lag 0
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    double y[D];
-                    whiten(k, y);
-                    q[k] = 0.0;
-#pragma unroll
-                    for (int p = 0; p < D - 1; ++p) q[k] = fma(y[p], y[p], q[k]);
-                    yE[k] = y[D - 1];
-                }
-                // live rows of this column, as runs of the segment
-                int ca = 127, cb = -1;
-                if (inrow && q[0] <= COL_CUT2) {
-                    const double hw = sqrt(COL_CUT2 - q[0]) * iu, ctr = -yE[0] * iu;
-                    const double lo = s0 > -wl ? s0 : -wl;
-                    const double hi = SMALL || s0 + SEG - 1 > wl ? wl : s0 + SEG - 1;
-                    const double fa = fmax(floor(ctr - hw), lo), fb = fmin(ceil(ctr + hw), hi);
-                    if (fa <= fb) {
-                        ca = ((int)fa - s0) / COL_RUN;
-                        cb = ((int)fb - s0) / COL_RUN;
-                    }
-                }
-                const int ga = min16(ca), gb = max16(cb);
-                if (gb < 0) continue;
-                // uniform base, 32-bit byte offset per lane
-                auto at = [&](int l, int t) {
-                    const uint32_t off = (col + (uint32_t)(l & (Pw - 1)) * (uint32_t)N) * 8u;
-                    return *reinterpret_cast<const __attribute__((address_space(1))) double*>(A + (size_t)t * N * 8 + off);
-                };
-                auto fetch = [&](int c, double* av) {
-                    const int l = s0 + COL_RUN * c;
-#pragma unroll
-                    for (int t = 0; t < COL_RUN; ++t) {
-                        if constexpr (SMALL)
-                            av[t] = l + t <= wl ? at(l + t, 0) : 0.0;
-                        else
-                            av[t] = at(l, t);
-                    }
-                    if (D == 2 && l == 0) av[0] *= 0.5;   // row 0 is its own mirror
-                };
-                double m[2][3];
-#pragma unroll
-                for (int k = 0; k < 2; ++k) m[k][0] = m[k][1] = m[k][2] = 0.0;
-                if (near1) {
-                    double e[2], r[2];   // yE: from here the component at the row before the run
-                    const double ls = (double)(s0 + COL_RUN * (cb >= 0 ? ca : 0));
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        const double ys = fma(uw[k], ls, yE[k]);
-                        col_start(q[k], uw[k], ys, s_exp, &e[k], &r[k]);
-                        yE[k] = ys - uw[k];
-                    }
-                    auto run = [&](int c, const double* av) {
-                        if (c < ca) return;   // the lane's column starts in a later run
-#pragma unroll
-                        for (int k = 0; k < 2; ++k) {
-                            double S0 = 0.0, S1 = 0.0, S2 = 0.0;
-#pragma unroll
-                            for (int t = COL_RUN - 1; t >= 0; --t) {
-                                const double p = t == 0 ? av[0] : av[t] * g[k][t];
-                                S0 = t == COL_RUN - 1 ? p : fma(S0, r[k], p);
-                                if constexpr (MODE != 0) {
-                                    S1 = t == COL_RUN - 1 ? p : fma(S1, r[k], S0);
-                                    S2 = t == COL_RUN - 1 ? p : fma(S2, r[k], S1);
-                                }
-                            }
-                            S0 *= e[k];
-                            m[k][0] += S0;
-                            if constexpr (MODE != 0) {
-                                // y = yE + u s, s = t + 1: S1 = sum s w, S2 = sum s(s+1)/2 w
-                                const double us = uw[k] * e[k];
-                                const double b0 = yE[k] * S0, b1 = us * S1;
-                                m[k][1] += b0 + b1;
-                                m[k][2] = fma(yE[k], fma(2.0, b1, b0), m[k][2]);
-                                m[k][2] = fma(uw[k] * us, fma(2.0, S2, -S1), m[k][2]);
-                                yE[k] = fma(uw[k], (double)COL_RUN, yE[k]);
-                            }
-                            const double r2 = r[k] * r[k], r4 = r2 * r2, r8 = r4 * r4;
-                            e[k] *= fma(r8, g8[k][0], r8 * g8[k][1]);
-                            r[k] = fma(r[k], hh[k][0], r[k] * hh[k][1]);   // (the exact product with the high part)
-                        }
-                    };
-                    double a0[COL_RUN], a1[COL_RUN];   // the next run's loads are in flight over the current one
-                    fetch(ga, a0);
-                    for (int c = ga; c <= gb; c += 2) {
-                        fetch(c < gb ? c + 1 : gb, a1);
-                        run(c, a0);
-                        if (c >= gb) break;
-                        fetch(c + 1 < gb ? c + 2 : gb, a0);
-                        run(c + 1, a1);
-                    }
-                } else if (cb >= 0) {
-                    // narrow kernels: lag by lag
-#pragma unroll 1
-                    for (int l = s0 + COL_RUN * ga; l < s0 + COL_RUN * (gb + 1); ++l) {
-                        double a = 0.0;
-                        if (!SMALL || l <= wl) a = at(l, 0);
-                        if (D == 2 && l == 0) a *= 0.5;
-#pragma unroll
-                        for (int k = 0; k < 2; ++k) {
-                            const double yw = fma(uw[k], (double)l, yE[k]);
-                            const double w = exp(-0.5 * fma(yw, yw, q[k])) * a;
-                            m[k][0] += w;
-                            if constexpr (MODE != 0) {
-                                m[k][1] = fma(w, yw, m[k][1]);
-                                m[k][2] = fma(w * yw, yw, m[k][2]);
-                            }
-                        }
-                    }
-                }
-                // the column's sums: products with the fixed components
-                // (formed again: kept over the walk they would cost registers)
-#pragma unroll
-                for (int p = 0; p < D - 1; ++p) asm volatile("" : "+v"(lag[p]));
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    const double m0 = rw * m[k][0];
-                    acc[k][0] += m0;
-                    if constexpr (MODE != 0) {
-                        double y[D];
-                        whiten(k, y);
-                        const double m1 = rw * m[k][1];
-#pragma unroll
-                        for (int i = 0; i < D - 1; ++i) {
-                            const double t0 = y[i] * m0;
-#pragma unroll
-                            for (int j = 0; j <= i; ++j) acc[k][1 + tri(i, j)] = fma(t0, y[j], acc[k][1 + tri(i, j)]);
-                            acc[k][1 + tri(D - 1, i)] = fma(y[i], m1, acc[k][1 + tri(D - 1, i)]);
-                        }
-                        acc[k][1 + tri(D - 1, D - 1)] = fma(rw, m[k][2], acc[k][1 + tri(D - 1, D - 1)]);
-                    }
-                }
-            }
-        }
-        // block sums in a fixed order, then the outputs: c_k times the sums, the
-        // second-order ones transformed back by L^{-1}
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-#pragma unroll
-            for (int i = 0; i < NA; ++i) {
-                const double v = sum16(acc[k][i]);
-                if (l16 == 0) s_red[tid >> 4][k * NA + i] = v;
-            }
-        __syncthreads();
-        if (tid < NV) {
-            double v[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int w = 0; w < COL_NT / 16; ++w) v[w & 3] += s_red[w][tid];
-            s_tot[tid] = (v[0] + v[1]) + (v[2] + v[3]);
-        }
-        __syncthreads();
+        Acc acc;
+        acc.clear();
+        col_walk<D, SMALL>(geo, ch, s_it, s_exp, cut2, acc);
+        col_reduce(acc, s_red, s_tot);
+        // the outputs: c_k times the sums, the second-order ones transformed
+        // back by L^{-1}
         if (tid < NG) {
             double out;
             if (MODE != 2 && tid == 0) {
@@ -700,6 +886,187 @@ __global__ __launch_bounds__(COL_NT, D <= 2 ? 4 : 3) void k_cols_scv(RowGeom geo
                 out = hs[0] - hs[1];
             }
             partial[(h * geo.nchunks + ch) * NG + tid] = out;
+        }
+        __syncthreads();
+    }
+}
+
+template <int D, int R>
+constexpr int col_psi_occ() { return HermTab<D, R>::NU > 20 ? 2 : 3; }
+
+// psi_r: partial sums of the whitened tensor's unique entries (walk order);
+// k_cols_psi_final adds and transforms them.
+template <int D, int R, bool SMALL>
+__global__ __launch_bounds__(COL_NT, (col_psi_occ<D, R>())) void k_cols_psi(ColGeom geo, PsiBatchArgs args, int64_t nitems,
+                                                                           double* __restrict__ prm,
+                                                                           double* __restrict__ partial) {
+    using Acc = ColHermAcc<D, R, 1>;
+    constexpr int NA = Acc::NA;
+    constexpr double cut2 = col_cut2(R);
+    __shared__ ColItem<D, 1> s_it;
+    __shared__ double s_red[COL_NT / 16][NA], s_tot[NA];
+    __shared__ double2 s_exp[32];
+    const int tid = threadIdx.x;
+    if (tid < 32) s_exp[tid] = COL_EXP2[tid];
+    for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
+        int64_t h;
+        int ch;
+        col_item<D>(geo, item, nitems, &h, &ch);
+        if (tid < 64) col_psi_setup<D>(args, h, ch == 0, cut2, prm, s_exp, &s_it);
+        __syncthreads();
+        Acc acc;
+        acc.clear();
+        col_walk<D, SMALL>(geo, ch, s_it, s_exp, cut2, acc);
+        col_reduce(acc, s_red, s_tot);
+        if (tid < NA) partial[(h * geo.nchunks + ch) * NA + tid] = s_tot[tid];
+        __syncthreads();
+    }
+}
+
+__host__ __device__ constexpr int ipow(int b, int e) { return e == 0 ? 1 : b * ipow(b, e - 1); }
+
+// Index of the unique entry (walk order) of the full tensor's element e.
+template <int D, int R>
+struct ColTensor {
+    static constexpr int NF = ipow(D, R);
+    struct Tab {
+        unsigned char u[NF];
+    };
+    static constexpr Tab make() {
+        using T = HermTab<D, R>;
+        Tab t{};
+        for (int e = 0; e < NF; ++e) {
+            int cnt[4] = {0, 0, 0, 0}, x = e;
+            for (int m = 0; m < R; ++m) {
+                cnt[x % D] += 1;
+                x /= D;
+            }
+            for (int b = 0; b < T::NU; ++b) {
+                bool eq = true;
+                for (int p = 0; p < D; ++p) eq = eq && T::tab.a[T::NB - T::NU + b][p] == cnt[p];
+                if (eq) t.u[e] = (unsigned char)b;
+            }
+        }
+        return t;
+    }
+    static constexpr Tab tab = make();
+};
+template <int D, int R>
+static __device__ const typename ColTensor<D, R>::Tab COL_TENSOR = ColTensor<D, R>::make();
+// The full tensor's element of each unique entry (axis order, sorted tuples).
+template <int D, int R>
+struct ColUnique {
+    struct Tab {
+        short e[HermTab<D, R>::NU];
+    };
+    static constexpr Tab make() {
+        using T = HermTab<D, R>;
+        Tab t{};
+        for (int b = 0; b < T::NU; ++b) {
+            int e = 0;
+            for (int k = 0; k < D; ++k)
+                for (int m = 0; m < T::tab.a[T::NB - T::NU + b][k]; ++m) e = e * D + k;
+            t.e[b] = (short)e;
+        }
+        return t;
+    }
+};
+template <int D, int R>
+static __device__ const typename ColUnique<D, R>::Tab COL_UNIQUE = ColUnique<D, R>::make();
+
+// psi_r of dataset blockIdx.x: the parts' sums added in a fixed order, then the
+// tensor transformed by L^{-1} mode by mode.
+template <int D, int R>
+__global__ __launch_bounds__(COL_NT) void k_cols_psi_final(const double* __restrict__ partial, int64_t nchunks,
+                                                           const double* __restrict__ prm, double* __restrict__ psi) {
+    constexpr int NU = HermTab<D, R>::NU, NF = ipow(D, R), NR = COL_NT / NU;
+    __shared__ double s_part[NR * NU], s_t[2][NF], s_li[D * D];
+    const int tid = threadIdx.x;
+    const int64_t h = blockIdx.x;
+    if (tid < D * D) s_li[tid] = prm[h * PRM + S_P1 + tid];
+    const double scale = prm[h * PRM + S_C];
+    if (tid < NR * NU) {
+        const double* p = partial + h * nchunks * NU;
+        double s = 0.0;
+        for (int64_t e = tid; e < nchunks * NU; e += NR * NU) s += p[e];
+        s_part[tid] = s;
+    }
+    __syncthreads();
+    for (int e = tid; e < NU; e += COL_NT) {
+        double s = 0.0;
+        for (int r = 0; r < NR; ++r) s += s_part[r * NU + e];
+        s_t[1][e] = s;   // (unique entries; NU <= NF)
+    }
+    __syncthreads();
+    for (int e = tid; e < NF; e += COL_NT) s_t[0][e] = s_t[1][R > 0 ? COL_TENSOR<D, R>.u[e] : 0];
+    __syncthreads();
+    // each mode: positions (rows of L^{-1}) to axes
+    int cur = 0;
+    for (int m = 0, st = 1; m < R; ++m, st *= D) {
+        for (int e = tid; e < NF; e += COL_NT) {
+            const int i = (e / st) % D, base = e - i * st;
+            const int pi = D == 1 ? 0 : (i < D - 2 ? i : (i == D - 2 ? D - 1 : D - 2));   // position of axis i
+            double s = 0.0;
+#pragma unroll
+            for (int p = 0; p < D; ++p) s = fma(s_t[cur][base + p * st], s_li[p * D + pi], s);
+            s_t[cur ^ 1][e] = s;
+        }
+        __syncthreads();
+        cur ^= 1;
+    }
+    for (int e = tid; e < NU; e += COL_NT) psi[h * NU + e] = scale * s_t[cur][R > 0 ? COL_UNIQUE<D, R>.e[e] : 0];
+}
+
+// Scalar eta_r families (Q_r with one Gaussian, LSCV_r with two), r <= 2:
+// eta_r = (tr of the tensor pairs) = sum over pairs Q_{ab} .. He_{2r}, with
+// Q = L^{-1} L^{-T} in whitened coordinates.
+template <int D, int NGS, int R, bool SMALL>
+__global__ __launch_bounds__(COL_NT, 3) void k_cols_eta(ColGeom geo, ScvSetup setup, int64_t nitems,
+                                                        double* __restrict__ partial) {
+    constexpr int K = 2 * R, NF = ipow(D, K);
+    using Acc = ColHermAcc<D, K, NGS>;
+    constexpr int NA = Acc::NA;
+    constexpr double cut2 = col_cut2(K);
+    __shared__ ColItem<D, NGS> s_it;
+    __shared__ double s_red[COL_NT / 16][NGS * NA], s_tot[NGS * NA], s_q[NGS][D * D], s_w[COL_NT / 16];
+    __shared__ double2 s_exp[32];
+    const int tid = threadIdx.x;
+    if (tid < 32) s_exp[tid] = COL_EXP2[tid];
+    for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
+        int64_t h;
+        int ch;
+        col_item<D>(geo, item, nitems, &h, &ch);
+        if (tid < 64) col_crit_setup<D, NGS, R>(setup, h, ch == 0, cut2, s_exp, &s_it);
+        __syncthreads();
+        if (tid < NGS * D * D) {
+            const int k = tid / (D * D), a = (tid / D) % D, b = tid % D;
+            double v = 0.0;
+#pragma unroll
+            for (int m = 0; m < D; ++m) v = fma(s_it.g[k].li[a * D + m], s_it.g[k].li[b * D + m], v);
+            s_q[k][a * D + b] = v;
+        }
+        Acc acc;
+        acc.clear();
+        col_walk<D, SMALL>(geo, ch, s_it, s_exp, cut2, acc);
+        col_reduce(acc, s_red, s_tot);
+        // contraction: one element of the full tensor per thread
+        static_assert(NGS * NF <= COL_NT, "one element per thread");
+        double v = 0.0;
+        if (tid < NGS * NF) {
+            const int k = tid / NF, e = tid % NF;
+            v = (k == 0 ? 1.0 : -2.0) * s_it.g[k].c;
+            if constexpr (R == 0) v *= s_tot[k * NA];
+            if constexpr (R == 1) v *= s_q[k][e] * s_tot[k * NA + COL_TENSOR<D, K>.u[e]];
+            if constexpr (R == 2) v *= s_q[k][e % (D * D)] * s_q[k][e / (D * D)] * s_tot[k * NA + COL_TENSOR<D, K>.u[e]];
+        }
+        v = sum16(v);
+        if ((tid & 15) == 0) s_w[tid >> 4] = v;
+        __syncthreads();
+        if (tid == 0) {
+            double s = 0.0;
+#pragma unroll
+            for (int w = 0; w < COL_NT / 16; ++w) s += s_w[w];
+            partial[h * geo.nchunks + ch] = s_it.sign * s;
         }
         __syncthreads();
     }

@@ -10,7 +10,7 @@
 
 namespace kdefft {
 
-constexpr int PRM = 72;     // doubles per candidate parameter block
+constexpr int PRM = 68;     // doubles per candidate parameter block
 constexpr int NT_DEF = 256;  // threads per block of the simple kernels
 
 // Parameter block layout (float64 slots) shared by setup, row and finalize kernels.
@@ -24,22 +24,8 @@ constexpr int NT_DEF = 256;  // threads per block of the simple kernels
 enum Slot { S_P1 = 0, S_C = 16, S_P2 = 16, S_C1 = 32, S_C2 = 33, S_FIRST = 34, S_R = 35, S_SIGN = 36, S_PSEUDO = 37,
             S_ALAG = 38,
             S_WMIX = 39, S_DELTA = 40, S_N = 44, S_SCALE = 45, S_CONST = 46, S_SING = 47, S_L = 48,
-            // fused completion (FinishArgs): mode, grids, counter and output pointers
-            S_FIN_MODE = 64, S_FIN_NG = 65, S_FIN_CNT = 66, S_FIN_OUT = 67, S_FIN_SCAL = 68 };
+            S_FIN_SCAL = 64 };   // constant-term candidates: the dataset's scalar block
 
-// How a psi lag launch completes (written into every candidate's parameter
-// block by the setup kernels): FIN_NONE = a separate final kernel assembles
-// the results; FIN_PSI = the block that finishes a candidate's last work item
-// writes its psi entries.  counters: one int per candidate, cleared by the
-// setup kernel.
-enum FinMode { FIN_NONE = 0, FIN_PSI = 1 };
-struct FinishArgs {
-    int mode;
-    int ng;
-    int32_t* counters;
-    double* out;    // psi [n_ds, ng]
-    double* scal;   // psi[0, 0] also stored here (constant SCV term)
-};
 
 // Per-dataset record kept in the dataset's own device buffer (written by a
 // kernel at prepare time); batched calls pass pointers to these records.
@@ -71,7 +57,6 @@ struct PsiBatchArgs {
     double prodP;
     const DsDev* rec[KDEFFT_MAX_PSI_DS];
     double Gv[KDEFFT_MAX_PSI_DS][10];   // vech (columns of the lower triangle)
-    FinishArgs fin;
 };
 struct PiArgs {
     int n_ds;
@@ -106,9 +91,7 @@ struct RowGeom {
     int64_t nrows;     // rows of the half lag set with nonzero kernel values
     int64_t chunk;     // rows per work item
     int64_t nchunks;   // work items per candidate
-    int n0;            // column walk, d >= 3: groups of axis-0 lags (nchunks is a multiple)
     int Q;             // P[d-1]/2 + 1
-    ScvSetup setup;    // the column walk computes its parameters itself (set for variants 5, 6)
 };
 
 // Kinds of kernel families generated on the lag grid.
@@ -157,8 +140,7 @@ hipError_t launch_linbin_slots(const double* X, int64_t n, const kdefft_grid& g,
 // the grid origin and spacing from the data bounds when `partial` is set --
 // lo = min - pad, hi = max + pad, hi = lo + 1 for a degenerate axis,
 // delta = (hi - lo)/(M - 1), the same IEEE steps as the host planner), the
-// out-of-grid counter and scalar block cleared, and the parameter block of
-// the constant SCV term (psi_0 at 2G) when prm is set.
+// out-of-grid counter and scalar block cleared.
 struct HeaderArgs {
     DsDev* rec;
     DsDev val;
@@ -168,10 +150,6 @@ struct HeaderArgs {
     double pad[4];
     int32_t* n_out;
     double* scal;
-    double* prm;
-    double Gv2[10];   // vech of 2G (columns of the lower triangle)
-    double prodP;
-    FinishArgs fin;   // completion of the constant-term launch
 };
 hipError_t launch_ds_header(const HeaderArgs& h, hipStream_t s);
 hipError_t launch_fill_czp(const int64_t* counts, const kdefft_grid& g, double* czp, hipStream_t s);
@@ -227,12 +205,11 @@ constexpr int ROW_VARIANTS = 7;
 hipError_t launch_scv_setup(const double* vechL, const ScvBatchArgs& a, int64_t ncand, int npseudo, double* prm,
                             int32_t* status, const RowGeom& geo, int32_t* wc, hipStream_t s);
 hipError_t launch_psi_setup(const PsiBatchArgs& a, double* prm, hipStream_t s);
-hipError_t launch_scv_final(int kind, const double* partial, const RowGeom& geo,
+hipError_t launch_scv_final(int kind, int d, const double* partial, int64_t nchunks,
                             const double* prm, int64_t ncand, int npseudo, const double* grad_out,
                             double* obj, double* grad, hipStream_t s);
 hipError_t launch_psi_final(const double* partial, const RowGeom& geo, int ng,
-                            const double* prm, int64_t ncand, double* psi, double* scal_out,
-                            hipStream_t s);
+                            const double* prm, int64_t ncand, double* psi, hipStream_t s);
 
 // batched quasi-Newton minimiser (minimize.hip): per-candidate state of
 // min_state_doubles(q) doubles and min_state_ints() int32
@@ -246,13 +223,25 @@ hipError_t launch_min_final(int64_t B, int q, const double* st, const int32_t* i
 hipError_t launch_pi(const PiArgs& a, const double* psi4, const double* vechL, int64_t ncand, double* obj,
                      double* grad, int32_t* status, hipStream_t s);
 
-// Column walk of the SCV / LSCV families (cols.h); geo.setup describes the batch.
-hipError_t launch_cols_scv(int kind, const RowGeom& geo, int64_t nitems, double* partial, int grid_blocks,
-                           hipStream_t s);
-// Its work items: geo->nchunks and geo->n0.
-void cols_geom(const kdefft_grid& g, int64_t ncand, RowGeom* geo);
-// Resident blocks of its kernels on the current device.
-int cols_slots();
+// Column walk (cols.h): the SCV / LSCV families (variants 5, 6), psi_r
+// (variants from 3 on) and the eta_r families of low order (cols_eta_ok).
+struct ColGeom {
+    int M[4];
+    int P[4];
+    int n0;            // d >= 3: groups of axis-0 lags (nchunks is a multiple)
+    int64_t nchunks;   // work items per candidate
+};
+// ng: outputs per item; scv: the batch may have to fit the fixed scratch of the
+// call without a workspace.
+ColGeom cols_geom(const kdefft_grid& g, int64_t ncand, int ng, bool scv);
+bool cols_eta_ok(int d, int r);
+hipError_t launch_cols_scv(int kind, int d, const ColGeom& geo, const ScvSetup& setup, int64_t nitems,
+                           double* partial, int grid_blocks, hipStream_t s);
+hipError_t launch_cols_eta(int kind, int d, int r, const ColGeom& geo, const ScvSetup& setup, int64_t nitems,
+                           double* partial, int grid_blocks, hipStream_t s);
+// One block per item, then one per dataset; prm: PRM doubles per dataset.
+hipError_t launch_cols_psi(const ColGeom& geo, const PsiBatchArgs& a, int grid_blocks, double* prm, double* partial,
+                           double* psi, hipStream_t s);
 
 RowGeom make_geom(const kdefft_grid& g, int kind, int r, int64_t ncand, int variant);
 

@@ -22,16 +22,6 @@ __device__ __forceinline__ static void put_ptr(double* slot, const void* p) {
     *slot = __longlong_as_double(static_cast<long long>(reinterpret_cast<uintptr_t>(p)));
 }
 
-// Completion slots of candidate h's block; clears its counter when fused.
-__device__ __forceinline__ static void put_finish(double* p, const FinishArgs& f, int64_t h) {
-    p[S_FIN_MODE] = (double)f.mode;
-    p[S_FIN_NG] = (double)f.ng;
-    put_ptr(p + S_FIN_CNT, f.counters);
-    put_ptr(p + S_FIN_OUT, f.out);
-    put_ptr(p + S_FIN_SCAL, f.scal);
-    if (f.mode != FIN_NONE) f.counters[h] = 0;
-}
-
 // Parameter block of the psi_r family for bandwidth vech gv on dataset ds:
 // P = G^{-1}, c = (-1)^r (2 pi)^{-d/2} |G|^{-1/2} (even r: the sign is +1),
 // lag array, spacing, n and the scale of the lag sums.
@@ -47,7 +37,6 @@ __device__ __forceinline__ static void psi_params(const double* gv, const DsDev&
             G[jj * 4 + i] = gv[t];
             ++t;
         }
-    // every slot the psi kernels read is written here or by put_finish
     chol4<D>(G, L);
     chol_inv4<D>(L, p + S_P1);
     double det = 1.0;
@@ -117,11 +106,10 @@ __device__ static void scv_params(const double* __restrict__ vechL, const ScvBat
             S1[i * 4 + k2] = hw * H[i * 4 + k2] + gw * ds.G[i * 4 + k2];
             S2[i * 4 + k2] = H[i * 4 + k2] + gw * ds.G[i * 4 + k2];
         }
-    // every slot the row and final kernels read is written below; these three
-    // default to zero (no closed-form or constant term, separate final kernel)
+    // every slot the row and final kernels read is written below; these two
+    // default to zero (no closed-form or constant term)
     p[S_FIRST] = 0.0;
     p[S_CONST] = 0.0;
-    p[S_FIN_MODE] = 0.0;
     p[S_PSEUDO] = npseudo > 0 ? (double)(ncand + ds_index) : -1.0;
     const bool ok1 = chol4<D>(S1, L1);
     const bool ok2 = chol4<D>(S2, L2);
@@ -206,7 +194,6 @@ __device__ static void pseudo_params(const ScvBatchArgs& a, int j, double* __res
     p[S_R] = 0.0;
     p[S_SIGN] = 1.0;
     p[S_PSEUDO] = -1.0;
-    p[S_FIN_MODE] = 0.0;
     put_ptr(p + S_FIN_SCAL, ds.scal);
     put_ptr(p + S_WMIX, ds.wmix);
     put_ptr(p + S_ALAG, ds.alag);

@@ -120,12 +120,6 @@ RowGeom make_geom(const kdefft_grid& g, int kind, int r, int64_t ncand, int vari
     geo.Q = g.P[g.d - 1] / 2 + 1;
     int ri = rows_per_iter(kind, g.d, r, g.P[g.d - 1], variant);
     if (ri < 1) ri = 1;
-    const bool mom = kind == FUN_SCV_OBJ || kind == FUN_SCV_OBJGRAD || kind == FUN_SCV_GRAD;
-    if (variant >= 5 && mom) {
-        cols_geom(g, ncand, &geo);
-        geo.chunk = 0;
-        return geo;
-    }
     // lag kernel: larger items amortise the per-item set-up and block reduction
     const int64_t target = variant >= 3 ? 2048 : 8192;
     int64_t iters = (nrows * ncand + (int64_t)ri * target - 1) / ((int64_t)ri * target);
@@ -147,8 +141,6 @@ hipError_t launch_rows(int kind, int d, int r, const RowGeom& geo, const double*
     }
     const int64_t nitems = ncand * geo.nchunks;
     const int N = geo.P[d - 1];
-    const bool mom = kind == FUN_SCV_OBJ || kind == FUN_SCV_OBJGRAD || kind == FUN_SCV_GRAD;
-    if (mom && rl.variant >= 5) return launch_cols_scv(kind, geo, nitems, partial, rl.grid_blocks, s);
     if (kind == FUN_ETA1 || kind == FUN_ETA2) {
         switch (d) {
             case 1: return launch_rows_eta_d1(kind, r, N, rl.variant, prm, geo, nitems, partial, rl.grid_blocks, s);
@@ -237,7 +229,6 @@ __global__ void k_psi_setup(PsiBatchArgs a, double* __restrict__ prm) {
             for (int t = 0; t < 10; ++t) gv[t] = a.Gv[jj][t];
         }
     psi_params<D>(gv, *dsp, a.prodP, prm + (int64_t)j * PRM);
-    put_finish(prm + (int64_t)j * PRM, a.fin, j);
 }
 
 hipError_t launch_psi_setup(const PsiBatchArgs& a, double* prm, hipStream_t s) {
@@ -281,10 +272,6 @@ __global__ __launch_bounds__(256) void k_ds_header(HeaderArgs h) {
     *h.rec = v;
     if (h.n_out) *h.n_out = 0;
     for (int k = 0; k < 4; ++k) h.scal[k] = 0.0;
-    if (h.prm) {
-        psi_params<D>(h.Gv2, v, h.prodP, h.prm);
-        put_finish(h.prm, h.fin, 0);
-    }
 }
 
 hipError_t launch_ds_header(const HeaderArgs& h, hipStream_t s) {
@@ -322,15 +309,15 @@ __global__ __launch_bounds__(64) void k_scv_final(int kind, const double* __rest
     crit_finish<D>(kind, partial, h * nchunks, nchunks, ng, p, h, cst, grad_out, obj, grad);
 }
 
-hipError_t launch_scv_final(int kind, const double* partial, const RowGeom& geo, const double* prm, int64_t ncand,
-                            int npseudo, const double* grad_out, double* obj, double* grad, hipStream_t s) {
-    const int ng = ng_of(kind, geo.d, 2);
+hipError_t launch_scv_final(int kind, int d, const double* partial, int64_t nchunks, const double* prm,
+                            int64_t ncand, int npseudo, const double* grad_out, double* obj, double* grad, hipStream_t s) {
+    const int ng = ng_of(kind, d, 2);
     const dim3 grid((unsigned)(ncand + npseudo));
-    switch (geo.d) {
-        case 1: hipLaunchKernelGGL(k_scv_final<1>, grid, dim3(64), 0, s, kind, partial, geo.nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
-        case 2: hipLaunchKernelGGL(k_scv_final<2>, grid, dim3(64), 0, s, kind, partial, geo.nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
-        case 3: hipLaunchKernelGGL(k_scv_final<3>, grid, dim3(64), 0, s, kind, partial, geo.nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
-        case 4: hipLaunchKernelGGL(k_scv_final<4>, grid, dim3(64), 0, s, kind, partial, geo.nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
+    switch (d) {
+        case 1: hipLaunchKernelGGL(k_scv_final<1>, grid, dim3(64), 0, s, kind, partial, nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
+        case 2: hipLaunchKernelGGL(k_scv_final<2>, grid, dim3(64), 0, s, kind, partial, nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
+        case 3: hipLaunchKernelGGL(k_scv_final<3>, grid, dim3(64), 0, s, kind, partial, nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
+        case 4: hipLaunchKernelGGL(k_scv_final<4>, grid, dim3(64), 0, s, kind, partial, nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -449,21 +436,21 @@ hipError_t launch_pi(const PiArgs& a, const double* psi4, const double* vechL, i
 }
 
 // psi[h, g] = scale_h * sum over chunks (fixed order), one wavefront per
-// (candidate, grid); scal_out (if set) receives psi[0, 0] (the constant SCV
-// term of a dataset).
+// (candidate, grid).
 __global__ __launch_bounds__(64) void k_psi_final(const double* __restrict__ partial, int64_t nchunks, int ng,
                                                   const double* __restrict__ prm, int64_t ncand,
-                                                  double* __restrict__ psi, double* __restrict__ scal_out) {
+                                                  double* __restrict__ psi) {
     const int64_t e = blockIdx.x;
     if (e >= ncand * ng) return;
     const int64_t h = e / ng;
-    psi_finish(partial, nchunks, ng, prm + h * PRM, h, (int)(e - h * ng), psi, scal_out);
+    const double v = chunk_sum(partial, h, nchunks, ng, (int)(e - h * ng)) * prm[h * PRM + S_SCALE];
+    if (threadIdx.x == 0) psi[e] = v;
 }
 
 hipError_t launch_psi_final(const double* partial, const RowGeom& geo, int ng, const double* prm, int64_t ncand,
-                            double* psi, double* scal_out, hipStream_t s) {
+                            double* psi, hipStream_t s) {
     hipLaunchKernelGGL(k_psi_final, dim3((unsigned)(ncand * ng)), dim3(64), 0, s, partial, geo.nchunks, ng, prm,
-                       ncand, psi, scal_out);
+                       ncand, psi);
     return hipGetLastError();
 }
 

@@ -19,20 +19,19 @@ static hipError_t lag_3(int N, const double* prm, RowGeom geo, int64_t nitems, d
     }
 }
 
-// One kernel per order r, so a lag costs the work of its own order.
+// One kernel per order r, so a lag costs the work of its own order; the orders
+// that the column walk serves (cols_eta_ok) are left out.
 template <int NGS>
 static hipError_t eta_3(int r, int N, const double* prm, RowGeom geo, int64_t nitems, double* partial, int gb,
                          hipStream_t s) {
     switch (r) {
-        case 0: return lag_3<EtaFun<3, NGS, 0>>(N, prm, geo, nitems, partial, gb, s);
-        case 1: return lag_3<EtaFun<3, NGS, 1>>(N, prm, geo, nitems, partial, gb, s);
-        case 2: return lag_3<EtaFun<3, NGS, 2>>(N, prm, geo, nitems, partial, gb, s);
         case 3: return lag_3<EtaFun<3, NGS, 3>>(N, prm, geo, nitems, partial, gb, s);
         case 4: return lag_3<EtaFun<3, NGS, 4>>(N, prm, geo, nitems, partial, gb, s);
         case 5: return lag_3<EtaFun<3, NGS, 5>>(N, prm, geo, nitems, partial, gb, s);
         case 6: return lag_3<EtaFun<3, NGS, 6>>(N, prm, geo, nitems, partial, gb, s);
         case 7: return lag_3<EtaFun<3, NGS, 7>>(N, prm, geo, nitems, partial, gb, s);
-        default: return lag_3<EtaFun<3, NGS, ETA_RMAX>>(N, prm, geo, nitems, partial, gb, s);
+        case ETA_RMAX: return lag_3<EtaFun<3, NGS, ETA_RMAX>>(N, prm, geo, nitems, partial, gb, s);
+        default: return hipErrorInvalidValue;   // low orders are column walks (cols.h)
     }
 }
 

@@ -470,8 +470,10 @@ __global__ __launch_bounds__(NT) void k_lag(const double* __restrict__ prm, RowG
         }
         double outv[NG];
         block_sum<NG, NT>(acc, red, outv);
-        if (threadIdx.x == 0) store_item<NG>(pr, partial + item * NG, outv);
-        fused_finish<D>(pr, partial, geo.nchunks, h);
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int g = 0; g < NG; ++g) partial[item * NG + g] = outv[g];
+        }
     }
 }
 
@@ -798,8 +800,10 @@ __global__ __launch_bounds__(NT, D <= 2 ? 1 : 2) void k_lag_mom(const double* __
             seg_walk(row_info<D>(rbeg + ro, rend, geo, delta, nullptr), sg * SEG, SEG);
         double outv[NG];
         block_sum<NG, NT>(acc, red, outv);
-        if (threadIdx.x == 0) store_item<NG>(pr, partial + item * NG, outv);
-        fused_finish<D>(pr, partial, geo.nchunks, h);
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int g = 0; g < NG; ++g) partial[item * NG + g] = outv[g];
+        }
     }
 }
 

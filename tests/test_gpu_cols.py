@@ -1,5 +1,5 @@
-"""The column walk of the SCV families (launch variants 5 and 6) at the edges
-of its units -- 16-lag blocks of the last axis, runs of 8 rows, segments of 32
+"""The column walk (SCV families: launch variants 5 and 6; psi_r; eta_r of low
+order) at the edges of its units -- 16-lag blocks of the last axis, runs of 8 rows, segments of 32
 (d = 2) or 64 rows, walked axes shorter than a run -- against the oracle's
 binned criterion on the same counts, for narrow kernels (a fraction of a grid
 step: evaluated lag by lag), ordinary and wide ones.
@@ -12,9 +12,9 @@ import pytest
 import torch
 
 import synth
-from oracle import grid, linbin
+from oracle import binned, eta, grid, linbin, multiindex
 
-from _gpu_util import check_scv, log, mixture_sample, oracle_autocorr, spd
+from _gpu_util import assert_psi_close, check_scv, check_z16, log, mixture_sample, oracle_autocorr, spd
 
 pytestmark = pytest.mark.gpu
 
@@ -53,6 +53,39 @@ def test_column_walk_edges(kf, gpu, M):
         for b in range(len(H)):
             check_scv(float(obj[b]), grad[b].cpu().numpy(), A, n, g, H[b], G, what=f"M={M} b={b}")
             check_scv(float(only[b]), (adj[b] / w[b]).cpu().numpy(), A, n, g, H[b], G, what=f"M={M} b={b} adjoint")
+
+
+@pytest.mark.parametrize("M", SHAPES, ids=lambda m: "x".join(map(str, m)))
+def test_derivative_families_edges(kf, gpu, M):
+    """psi_r up to the largest order, Q_r and LSCV_r of the orders the walk serves."""
+    d = len(M)
+    n = 300
+    X = mixture_sample(n, d, 570 + d)
+    G = spd(d, 571 + d, 0.05)
+    g = grid.plan_auto(X, G, M)
+    counts, _ = linbin.linbin(X, g)
+    A = oracle_autocorr(linbin.counts_to_real(counts))
+    ds = kf.Dataset(torch.from_numpy(X).to(gpu), G, M=M)
+    S = [G * s for s in (1e-3, 1.0, 40.0)]
+    for r in (0, 2, {1: 8, 2: 8, 3: 6, 4: 4}[d]):
+        for k, got in enumerate(kf.psi_batch([ds] * 3, S, r).cpu().numpy()):
+            log(f"[cols] psi M={M} r={r} {k}")
+            sabs = binned.abs_scale(A, n, g, S[k], multiindex.unique_alphas(d, r))
+            assert_psi_close(got, binned.psi(A, n, g, S[k], r), sabs, what=f"M={M} r={r} {k}")
+    v = torch.from_numpy(synth.vech_chol(np.stack(S))).to(gpu)
+    for r in (0, 1, 2):
+        q = kf.crit([ds], v, "qr", r, grad=False).cpu().numpy()
+        for k in range(3):
+            log(f"[cols] Q_{r} M={M} {k}")
+            check_z16([q[k]], [eta.qr_binned(A, n, g, S[k], r)],
+                      [eta.vstat_binned(A, n, g, [(1.0, S[k])], r, absval=True)], what=f"Q_{r} {k}")
+        for exact in (False, True):
+            if r == 0:
+                continue
+            c = kf.crit([ds], v, "lscv_exact" if exact else "lscv", r, grad=False).cpu().numpy()
+            for k in range(3):
+                check_z16([c[k]], [eta.lscv_r_binned(A, n, g, S[k], r, exact)],
+                          [eta.lscv_abs_scale(A, n, g, S[k], r, exact)], what=f"LSCV_{r} {exact} {k}")
 
 
 def test_column_walk_item_order(kf, gpu):
