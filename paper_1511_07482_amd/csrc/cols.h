@@ -52,17 +52,18 @@
 namespace kdefft {
 
 constexpr int COL_RUN = 8;    // rows per run
-// Rows per segment (one start with exponentials each): D = 2 has few columns
-// to deal out, so they are cut shorter.
-__host__ __device__ constexpr int col_seg(int D) { return D == 2 ? 32 : 64; }
+// Rows per segment: one start with exponentials each (at d = 2, where the columns
+// are few, 32 rows measured 27.5 and 25.0 us for 64 candidates at M = 256 and 101
+// at M = 203, 64 rows 24.2 and 22.5; 256 candidates the same).
+constexpr int COL_SEG = 64;
 // Segments of an axis with lags up to lw: D = 2 from lag 0 on (half set);
 // D >= 3 around lag 0, segment s of [-n, n] covering the rows from
-// col_seg * s - col_seg / 2.
+// COL_SEG * s - COL_SEG / 2.
 __host__ __device__ constexpr int col_side_segs(int D, int lw) {
-    return D == 2 || lw < col_seg(D) / 2 ? 0 : (lw - col_seg(D) / 2) / col_seg(D) + 1;
+    return D == 2 || lw < COL_SEG / 2 ? 0 : (lw - COL_SEG / 2) / COL_SEG + 1;
 }
 __host__ __device__ constexpr int col_segs(int D, int lw) {
-    return D == 2 ? lw / col_seg(D) + 1 : 2 * col_side_segs(D, lw) + 1;
+    return D == 2 ? lw / COL_SEG + 1 : 2 * col_side_segs(D, lw) + 1;
 }
 constexpr int COL_NT = 256;
 static_assert(COL_RUN == 8, "the run's powers and tables are written for 8 rows");
@@ -646,7 +647,7 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
 #pragma unroll
         for (int k = 0; k < NGS; ++k) acc.column(k, 1.0, nullptr);
     } else {
-        constexpr int SEG = col_seg(D);
+        constexpr int SEG = COL_SEG;
         const int N = geo.P[D - 1], Pw = geo.P[D - 2];
         // D >= 3: part ch takes the lags c0, 2 n0 - 1 - c0, 2 n0 + c0, ... of
         // axis 0 (c0 = ch mod n0) and every nsub-th block step of their units;
@@ -987,22 +988,31 @@ __global__ __launch_bounds__(COL_NT) void k_cols_psi_final(const double* __restr
     const double scale = prm[h * PRM + S_C];
     if (tid < NR * NU) {
         const double* p = partial + h * nchunks * NU;
-        double s = 0.0;
-        for (int64_t e = tid; e < nchunks * NU; e += NR * NU) s += p[e];
-        s_part[tid] = s;
+        const int n = (int)nchunks * NU;
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        int e = tid;
+        for (; e + 3 * NR * NU < n; e += 4 * NR * NU) {   // (four loads in flight)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] += p[e + i * NR * NU];
+        }
+        for (; e < n; e += NR * NU) s[0] += p[e];
+        s_part[tid] = (s[0] + s[1]) + (s[2] + s[3]);
     }
     __syncthreads();
     for (int e = tid; e < NU; e += COL_NT) {
-        double s = 0.0;
-        for (int r = 0; r < NR; ++r) s += s_part[r * NU + e];
-        s_t[1][e] = s;   // (unique entries; NU <= NF)
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+        for (int r = 0; r < NR; ++r) s[r & 3] += s_part[r * NU + e];
+        s_t[1][e] = (s[0] + s[1]) + (s[2] + s[3]);   // (unique entries; NU <= NF)
     }
     __syncthreads();
     for (int e = tid; e < NF; e += COL_NT) s_t[0][e] = s_t[1][R > 0 ? COL_TENSOR<D, R>.u[e] : 0];
     __syncthreads();
     // each mode: positions (rows of L^{-1}) to axes
     int cur = 0;
-    for (int m = 0, st = 1; m < R; ++m, st *= D) {
+    int st = 1;
+#pragma unroll
+    for (int m = 0; m < R; ++m, st *= D) {   // (unrolled: divisions by constants)
         for (int e = tid; e < NF; e += COL_NT) {
             const int i = (e / st) % D, base = e - i * st;
             const int pi = D == 1 ? 0 : (i < D - 2 ? i : (i == D - 2 ? D - 1 : D - 2));   // position of axis i
