@@ -387,8 +387,8 @@ int kdefft_expand_full(int d, int r, const double* unique_host, double* full_hos
 
 /* One candidate H at a time by the paper's literal steps: for the objective
  * grid and each of the q Hessian grids, kernel grid -> R2C -> multiply by the
- * prepared count spectrum -> C2R -> scale -> contract with the counts, each a
- * separate launch.  out: device [1 + q] = (SCV(H), d SCV / d vechL).
+ * prepared count spectrum -> C2R -> scale -> contract with the counts (the
+ * grids of one H together, several steps to a launch).  out: device [1 + q] = (SCV(H), d SCV / d vechL).
  * H_host: d x d row-major.  Workspace: KDEFFT_OP_SCV_PLAIN. */
 int kdefft_scv_plain(const kdefft_dataset* ds_host, const double* H_host, double* out,
                      void* ws, size_t ws_bytes, void* stream);

@@ -229,11 +229,6 @@ Sizes sizes_of(const kdefft_grid& g) {
 // the binning launch reduces their partials again, so they are kept few.
 int64_t bound_blocks(int64_t n) { return std::min<int64_t>(std::max<int64_t>((n + 1023) / 1024, 1), 128); }
 
-int nblk_dot(const kdefft_grid& g) {
-    const int64_t b = (sizes_of(g).prodM + 255) / 256;
-    return (int)std::min<int64_t>(std::max<int64_t>(b, 1), 1024);
-}
-
 int64_t max_nchunks(const kdefft_grid& g, int kind, int r, int64_t ncand) {
     int64_t m = 1;
     // row kernels: the spectral variants 0-2, and the lag walks 3, 4
@@ -396,25 +391,46 @@ int64_t* carve_prepare(Arena& a, const kdefft_grid& g) {
 struct PlainScratch {
     int64_t* counts;
     int32_t* n_out;
-    double* czp;
+    int64_t* slots;
     double2* C;
-    double* kreal;
-    double2* K;
+    double* kreal;     // batch kernel grids: the slices l_0 >= 0
+    double2* K;        // their spectra
     double* partial;
     double* sums;
+    int batch;         // kernel grids taken together
 };
-PlainScratch carve_plain(Arena& a, const kdefft_grid& g, bool with_counts) {
+// How many of nent kernel grids are taken together: as many as 64 MiB hold.
+int plain_batch(const kdefft_grid& g, int nent) {
+    const Sizes s = sizes_of(g);
+    const int64_t m = g.d > 1 ? g.M[0] : 1, p0 = g.d > 1 ? g.P[0] : 1;
+    const int64_t fit = (64LL << 20) / (s.prodP / p0 * m * 8 + s.spec / p0 * m * 16);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(nent, fit));
+}
+// fft-L: the largest padded grid Eq. (27) can ask for on g (L_k = M_k - 1).
+kdefft_grid fftl_largest(const kdefft_grid& g) {
+    kdefft_grid gm = g;
+    for (int k = 0; k < g.d; ++k) {
+        int p = 4;
+        while (p < 3 * g.M[k] - 3) p *= 2;
+        gm.P[k] = p;
+    }
+    return gm;
+}
+PlainScratch carve_plain(Arena& a, const kdefft_grid& g, int batch, bool with_counts) {
     const Sizes s = sizes_of(g);
     PlainScratch p{};
     if (with_counts) {
         p.counts = a.take<int64_t>(s.prodM);
         p.n_out = a.take<int32_t>(1);
-        p.czp = a.take<double>(s.prodP);
+        p.slots = a.take<int64_t>(corner_slots(g.d) * s.prodM);
         p.C = a.take<double2>(s.spec);
     }
-    p.kreal = a.take<double>(s.prodP);
-    p.K = a.take<double2>(s.spec);
-    p.partial = a.take<double>(nblk_dot(g));
+    const int64_t m = g.d > 1 ? g.M[0] : 1, p0 = g.d > 1 ? g.P[0] : 1;
+    const int64_t real = s.prodP / p0 * m, spec = s.spec / p0 * m;
+    p.batch = batch;
+    p.kreal = a.take<double>(p.batch * real);
+    p.K = a.take<double2>(p.batch * spec);
+    p.partial = a.take<double>((int64_t)p.batch * conv_blocks(g));
     p.sums = a.take<double>(16);
     return p;
 }
@@ -451,7 +467,7 @@ int plan_bytes(const kdefft_grid& g, int op, int r, int64_t batch, Arena& a) {
             a.take<double>(nb * 8);
             return KDEFFT_OK;
         }
-        case KDEFFT_OP_PSI_PLAIN: carve_plain(a, g, true); return KDEFFT_OK;
+        case KDEFFT_OP_PSI_PLAIN: carve_plain(a, g, plain_batch(g, (int)binom(g.d + r - 1, r)), true); return KDEFFT_OK;
         case KDEFFT_OP_PSI_FUSED:
             carve_dataset(a, g);
             carve_prepare(a, g);
@@ -467,16 +483,10 @@ int plan_bytes(const kdefft_grid& g, int op, int r, int64_t batch, Arena& a) {
         case KDEFFT_OP_SCV_BATCH:
             carve_batch(a, g, FUN_SCV_OBJGRAD, 2, std::max<int64_t>(batch, 1));
             return KDEFFT_OK;
-        case KDEFFT_OP_SCV_PLAIN: carve_plain(a, g, false); return KDEFFT_OK;
+        case KDEFFT_OP_SCV_PLAIN: carve_plain(a, g, plain_batch(g, 1 + g.d * (g.d + 1) / 2), false); return KDEFFT_OK;
         case KDEFFT_OP_PSI_FFTL: {
-            // the largest padded grid Eq. (27) can ask for (L_k = M_k - 1)
-            kdefft_grid gm = g;
-            for (int k = 0; k < g.d; ++k) {
-                int p = 4;
-                while (p < 3 * g.M[k] - 3) p *= 2;
-                gm.P[k] = p;
-            }
-            carve_plain(a, gm, true);
+            const kdefft_grid gm = fftl_largest(g);
+            carve_plain(a, gm, plain_batch(gm, (int)binom(g.d + r - 1, r)), true);
             return KDEFFT_OK;
         }
         case KDEFFT_OP_AUTOTUNE: {
@@ -499,14 +509,11 @@ int plan_bytes(const kdefft_grid& g, int op, int r, int64_t batch, Arena& a) {
 
 hipStream_t S(void* stream) { return static_cast<hipStream_t>(stream); }
 
-// Bin X into counts (zeroed first) and build the circular real count array.
-int bin_and_fill(const double* X, int64_t n, const kdefft_grid& g, int64_t* counts, int32_t* n_out, double* czp,
-                 hipStream_t s, const double* gdev = nullptr) {
-    const Sizes sz = sizes_of(g);
-    HIPCHK(launch_zero(counts, sz.prodM * sizeof(int64_t), s), "zero counts");
-    if (n_out) HIPCHK(launch_zero(n_out, sizeof(int32_t), s), "zero n_out");
-    HIPCHK(launch_linbin(X, n, g, counts, n_out, s, gdev), "linbin");
-    if (czp) HIPCHK(launch_fill_czp(counts, g, czp, s), "fill czp");
+// Step 1 of the plain path: bin X, and the spectrum of the counts.
+int bin_and_transform(const double* X, int64_t n, const kdefft_grid& g, const PlainScratch& p, hipStream_t s) {
+    HIPCHK(launch_zero(p.n_out, sizeof(int32_t), s), "zero n_out");
+    HIPCHK(launch_linbin_slots(X, n, g, p.slots, p.n_out, s, nullptr, false), "linbin");
+    HIPCHK(fft_counts_nd(p.slots, p.counts, p.C, g, s), "R2C counts");
     return KDEFFT_OK;
 }
 
@@ -843,7 +850,11 @@ int kdefft_linbin(const double* X, int64_t n, const kdefft_grid* g, int64_t* cou
     rc = check_n(n);
     if (rc) return rc;
     if (!X || !counts) return fail(KDEFFT_E_ARG, "NULL X or counts");
-    return bin_and_fill(X, n, *g, counts, n_out_dev, nullptr, S(stream));
+    hipStream_t s = S(stream);
+    HIPCHK(launch_zero(counts, sizes_of(*g).prodM * sizeof(int64_t), s), "zero counts");
+    if (n_out_dev) HIPCHK(launch_zero(n_out_dev, sizeof(int32_t), s), "zero n_out");
+    HIPCHK(launch_linbin(X, n, *g, counts, n_out_dev, s), "linbin");
+    return KDEFFT_OK;
 }
 
 int kdefft_check_binning(const int32_t* n_out_dev, int32_t* n_out_host, void* stream) {
@@ -877,23 +888,19 @@ int kdefft_psi(const double* X, int64_t n, const kdefft_grid* g, const double* G
     hipStream_t s = S(stream);
     Arena a(ws, ws_bytes, false);
     if (mode == KDEFFT_PSI_PLAIN) {
-        const PlainScratch p = carve_plain(a, *g, true);
+        const PlainScratch p = carve_plain(a, *g, plain_batch(*g, nu), true);
         rc = check_ws(a, ws_bytes);
         if (rc) return rc;
         ParamBlock prm{};
         chol_inv_host(L, d, prm.v + S_P1);
         prm.v[S_C] = normal_const(L, d);
-        rc = bin_and_fill(X, n, *g, p.counts, p.n_out, p.czp, s);
+        rc = bin_and_transform(X, n, *g, p, s);
         if (rc) return rc;
-        HIPCHK(fft_r2c_nd(p.czp, p.C, *g, s), "R2C counts");
-        const int nb = nblk_dot(*g);
-        for (int u = 0; u < nu; ++u) {
-            HIPCHK(launch_kgrid_psi(p.kreal, *g, r, prm, u, s), "kernel grid");
-            HIPCHK(fft_r2c_nd(p.kreal, p.K, *g, s), "R2C kernel");
-            HIPCHK(launch_cmul(p.K, p.C, sz.spec, s), "spectrum product");
-            HIPCHK(fft_c2r_nd(p.K, p.kreal, *g, s), "C2R");
-            HIPCHK(launch_dot_counts(p.counts, p.kreal, *g, p.partial, nb, s), "count contraction");
-            HIPCHK(launch_sum_scale(p.partial, nb, scale, psi + u, s), "final sum");
+        for (int u = 0; u < nu; u += p.batch) {
+            const int ne = std::min(p.batch, nu - u);
+            HIPCHK(launch_kgrid_psi(p.kreal, *g, g->M[0], r, prm, u, ne, s), "kernel grids");
+            HIPCHK(conv_sums(*g, g->M[0], ne, p.kreal, p.K, p.C, p.counts, p.partial, scale, psi + u, s),
+                   "convolution");
         }
         return KDEFFT_OK;
     }
@@ -962,23 +969,18 @@ int kdefft_psi_fftl(const double* X, int64_t n, const kdefft_grid* g, const doub
     const int nu = (int)binom(d + r - 1, r);
     hipStream_t s = S(stream);
     Arena a(ws, ws_bytes, false);
-    const PlainScratch p = carve_plain(a, g2, true);
+    const PlainScratch p = carve_plain(a, g2, plain_batch(fftl_largest(*g), nu), true);
     rc = check_ws(a, ws_bytes);
     if (rc) return rc;
     ParamBlock prm{};
     chol_inv_host(L, d, prm.v + S_P1);
     prm.v[S_C] = normal_const(L, d);
-    rc = bin_and_fill(X, n, g2, p.counts, p.n_out, p.czp, s);
+    rc = bin_and_transform(X, n, g2, p, s);
     if (rc) return rc;
-    HIPCHK(fft_r2c_nd(p.czp, p.C, g2, s), "R2C counts");
-    const int nb = nblk_dot(g2);
-    for (int u = 0; u < nu; ++u) {
-        HIPCHK(launch_kgrid_psi(p.kreal, gk, r, prm, u, s), "truncated kernel grid");
-        HIPCHK(fft_r2c_nd(p.kreal, p.K, g2, s), "R2C kernel");
-        HIPCHK(launch_cmul(p.K, p.C, sz.spec, s), "spectrum product");
-        HIPCHK(fft_c2r_nd(p.K, p.kreal, g2, s), "C2R");
-        HIPCHK(launch_dot_counts(p.counts, p.kreal, g2, p.partial, nb, s), "count contraction");
-        HIPCHK(launch_sum_scale(p.partial, nb, scale, psi + u, s), "final sum");
+    for (int u = 0; u < nu; u += p.batch) {
+        const int ne = std::min(p.batch, nu - u);
+        HIPCHK(launch_kgrid_psi(p.kreal, gk, g2.M[0], r, prm, u, ne, s), "truncated kernel grids");
+        HIPCHK(conv_sums(g2, gk.M[0], ne, p.kreal, p.K, p.C, p.counts, p.partial, scale, psi + u, s), "convolution");
     }
     return KDEFFT_OK;
 }
@@ -1518,21 +1520,17 @@ int kdefft_scv_plain(const kdefft_dataset* ds, const double* H_host, double* out
     fin.v[32] = c4 / (double)ds->n;
     if (!ws) return fail(KDEFFT_E_ARG, "workspace is NULL");
     Arena a(ws, ws_bytes, false);
-    const PlainScratch p = carve_plain(a, g, false);
+    const PlainScratch p = carve_plain(a, g, plain_batch(g, 1 + q), false);
     rc = check_ws(a, ws_bytes);
     if (rc) return rc;
     const Sizes sz = sizes_of(g);
     const double scale = 1.0 / ((double)ds->n * (double)ds->n * (double)sz.prodP);
-    const int nb = nblk_dot(g);
     hipStream_t s = S(stream);
     const double2* C = reinterpret_cast<const double2*>(ds->spec);
-    for (int e = 0; e <= q; ++e) {
-        HIPCHK(launch_kgrid_scv(p.kreal, g, kp, e, s), "kernel grid");
-        HIPCHK(fft_r2c_nd(p.kreal, p.K, g, s), "R2C kernel");
-        HIPCHK(launch_cmul(p.K, C, sz.spec, s), "spectrum product");
-        HIPCHK(fft_c2r_nd(p.K, p.kreal, g, s), "C2R");
-        HIPCHK(launch_dot_counts(ds->counts, p.kreal, g, p.partial, nb, s), "count contraction");
-        HIPCHK(launch_sum_scale(p.partial, nb, scale, p.sums + e, s), "final sum");
+    for (int e = 0; e <= q; e += p.batch) {
+        const int ne = std::min(p.batch, 1 + q - e);
+        HIPCHK(launch_kgrid_scv(p.kreal, g, g.M[0], kp, e, ne, s), "kernel grids");
+        HIPCHK(conv_sums(g, g.M[0], ne, p.kreal, p.K, C, ds->counts, p.partial, scale, p.sums + e, s), "convolution");
     }
     HIPCHK(launch_scv_plain_final(p.sums, fin, d, out, s), "scv assembly");
     return KDEFFT_OK;

@@ -1,5 +1,4 @@
-// Step 1 of Sec. 4: data bounds, linear binning into int64 fixed-point counts,
-// and the zero-padded real count array of the circular layout.
+// Step 1 of Sec. 4: data bounds and linear binning into int64 fixed-point counts.
 #include <hip/hip_runtime.h>
 
 #include "dev_common.h"
@@ -331,48 +330,6 @@ hipError_t launch_linbin(const double* X, int64_t n, const kdefft_grid& g, int64
         case 2: hipLaunchKernelGGL(k_linbin<2>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, gdev, c, n_out, 0, h); break;
         case 3: hipLaunchKernelGGL(k_linbin<3>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, gdev, c, n_out, 0, h); break;
         case 4: hipLaunchKernelGGL(k_linbin<4>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, gdev, c, n_out, 0, h); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ counts -> c_zp
-// Real array of the circular layout: c at [0, M)^d, zero elsewhere in P^d.
-template <int D>
-__global__ void k_fill_czp(const int64_t* __restrict__ counts, kdefft_grid g, int64_t total,
-                           double* __restrict__ czp) {
-    const double quantum = 9.094947017729282379150390625e-13;  // 2^-40
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        int64_t rem = e, cflat = 0;
-        bool in = true;
-        int idx[D];
-#pragma unroll
-        for (int k = D - 1; k >= 0; --k) {
-            idx[k] = (int)(rem % g.P[k]);
-            rem /= g.P[k];
-            in = in && idx[k] < g.M[k];
-        }
-        if (in) {
-#pragma unroll
-            for (int k = 0; k < D; ++k) cflat = cflat * g.M[k] + idx[k];
-            czp[e] = (double)counts[cflat] * quantum;
-        } else {
-            czp[e] = 0.0;
-        }
-    }
-}
-
-hipError_t launch_fill_czp(const int64_t* counts, const kdefft_grid& g, double* czp, hipStream_t s) {
-    int64_t total = 1;
-    for (int k = 0; k < g.d; ++k) total *= g.P[k];
-    int64_t blocks = (total + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
-    switch (g.d) {
-        case 1: hipLaunchKernelGGL(k_fill_czp<1>, dim3((unsigned)blocks), dim3(256), 0, s, counts, g, total, czp); break;
-        case 2: hipLaunchKernelGGL(k_fill_czp<2>, dim3((unsigned)blocks), dim3(256), 0, s, counts, g, total, czp); break;
-        case 3: hipLaunchKernelGGL(k_fill_czp<3>, dim3((unsigned)blocks), dim3(256), 0, s, counts, g, total, czp); break;
-        case 4: hipLaunchKernelGGL(k_fill_czp<4>, dim3((unsigned)blocks), dim3(256), 0, s, counts, g, total, czp); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -369,6 +369,7 @@ struct Prune {
     int P[3];     // their extents (outer index digits, major first)
     int M[3];     // their count extents
     int nlive;    // entries of a live column that can be nonzero
+    int nstore;   // entries of a column that are stored (0: all)
 };
 
 // MODE 0: in-place transform.  MODE 1: forward transform stored in place
@@ -415,7 +416,7 @@ __global__ __launch_bounds__(NT) void k_c2c_strided(double2* __restrict__ buf, d
     fft_lds<N, T, NT, DIR, RADIX, N>(lds, PS, twl);
     for (int e = threadIdx.x; e < N * T; e += NT) {
         const int t = e % T, p = e / T;
-        if (i0 + t < inner) base[(int64_t)p * inner + t] = lds[t * PS + p];
+        if (i0 + t < inner && p < pr.nstore) base[(int64_t)p * inner + t] = lds[t * PS + p];
     }
     if constexpr (MODE == 1) {
         for (int e = threadIdx.x; e < N * T; e += NT) {
@@ -653,8 +654,9 @@ static hipError_t c2r_last(const double2* in, double* out, int64_t rows, int N, 
 #undef CALL
 }
 static hipError_t c2c(double2* buf, double2* out2, int64_t outer, int N, int64_t inner, int dir, int mode,
-                      const double2* tw, hipStream_t s, int fs = FS_AUTO, Prune pr = Prune{0, {1, 1, 1}, {1, 1, 1}, 0}) {
+                      const double2* tw, hipStream_t s, int fs = FS_AUTO, Prune pr = Prune{0, {1, 1, 1}, {1, 1, 1}, 0, 0}) {
     if (pr.nlive <= 0 || pr.nlive > N) pr.nlive = N;
+    if (pr.nstore <= 0 || pr.nstore > N) pr.nstore = N;
     if (pr.na > 0) {   // the launch covers the live columns only
         outer = 1;
         for (int k = 0; k < pr.na; ++k) outer *= pr.M[k];
@@ -682,46 +684,50 @@ static void axis_shape(const kdefft_grid& g, int axis, int64_t* outer, int64_t* 
     *inner = in;
 }
 
-hipError_t fft_c2c_axis(double2* buf, const kdefft_grid& g, int axis, int dir, hipStream_t s) {
+// Axes d-1..1 of real arrays of `slices` slices along axis 0 (the axis-0 index,
+// or several arrays' ones, leads): in [slices, P_1, .., P_{d-1}] -> out
+// [slices, P_1, .., Q].
+hipError_t fft_slices_forward(const double* in, double2* out, const kdefft_grid& g, int64_t slices, hipStream_t s) {
     if (!shape_ok(g)) return hipErrorInvalidValue;
     const double2* tw;
     hipError_t e = twiddles(&tw);
     if (e != hipSuccess) return e;
-    int64_t outer, inner;
-    axis_shape(g, axis, &outer, &inner);
-    return c2c(buf, nullptr, outer, g.P[axis], inner, dir, 0, tw, s);
-}
-
-hipError_t fft_r2c_nd(const double* in, double2* out, const kdefft_grid& g, hipStream_t s) {
-    if (!shape_ok(g)) return hipErrorInvalidValue;
-    const double2* tw;
-    hipError_t e = twiddles(&tw);
-    if (e != hipSuccess) return e;
-    e = r2c_last(in, out, lead_count(g), g.P[g.d - 1], tw, s);
-    for (int ax = g.d - 2; ax >= 0 && e == hipSuccess; --ax) {
-        int64_t outer, inner;
-        axis_shape(g, ax, &outer, &inner);
-        e = c2c(out, nullptr, outer, g.P[ax], inner, -1, 0, tw, s);
+    int64_t rows = slices;
+    for (int k = 1; k + 1 < g.d; ++k) rows *= g.P[k];
+    e = r2c_last(in, out, rows, g.P[g.d - 1], tw, s);
+    int64_t inner = g.P[g.d - 1] / 2 + 1;
+    for (int ax = g.d - 2; ax >= 1 && e == hipSuccess; --ax) {
+        rows /= g.P[ax];
+        e = c2c(out, nullptr, rows, g.P[ax], inner, -1, 0, tw, s);
+        inner *= g.P[ax];
     }
     return e;
 }
 
-hipError_t fft_c2r_nd(double2* inout, double* out, const kdefft_grid& g, hipStream_t s) {
-    if (!shape_ok(g)) return hipErrorInvalidValue;
+// The inverse along axes 1..d-2 in place, for the nodes inside the counts' box:
+// of each axis only the entries below M are stored and, along the next one,
+// visited.
+hipError_t fft_slices_inverse(double2* buf, const kdefft_grid& g, int64_t slices, hipStream_t s) {
+    if (!shape_ok(g) || slices >= (int64_t(1) << 31)) return hipErrorInvalidValue;
     const double2* tw;
     hipError_t e = twiddles(&tw);
     if (e != hipSuccess) return e;
-    for (int ax = 0; ax + 1 < g.d && e == hipSuccess; ++ax) {
-        int64_t outer, inner;
-        axis_shape(g, ax, &outer, &inner);
-        e = c2c(inout, nullptr, outer, g.P[ax], inner, 1, 0, tw, s);
+    for (int ax = 1; ax + 1 < g.d && e == hipSuccess; ++ax) {
+        int64_t inner = g.P[g.d - 1] / 2 + 1;
+        for (int k = ax + 1; k + 1 < g.d; ++k) inner *= g.P[k];
+        Prune pr{ax, {(int)slices, 1, 1}, {(int)slices, 1, 1}, 0, g.M[ax]};
+        for (int k = 1; k < ax; ++k) {
+            pr.P[k] = g.P[k];
+            pr.M[k] = g.M[k];
+        }
+        e = c2c(buf, nullptr, slices, g.P[ax], inner, 1, 0, tw, s, FS_AUTO, pr);
     }
-    if (e != hipSuccess) return e;
-    return c2r_last(inout, out, lead_count(g), g.P[g.d - 1], tw, s);
+    return e;
 }
 
-hipError_t fft_prepare_nd(const int64_t* src, int slots, int64_t* counts, double2* spec, double2* wmix,
-                          const kdefft_grid& g, hipStream_t s, int fs, int32_t* reach) {
+// wmix set: as fft_prepare_nd; NULL: the count spectrum alone.
+static hipError_t counts_forward(const int64_t* src, int slots, int64_t* counts, double2* spec, double2* wmix,
+                                 const kdefft_grid& g, hipStream_t s, int fs, int32_t* reach) {
     if (fs < 0 || fs >= FFT_SCHEDULES || !shape_ok(g)) return hipErrorInvalidValue;
     const double2* tw;
     hipError_t e = twiddles(&tw);
@@ -737,30 +743,41 @@ hipError_t fft_prepare_nd(const int64_t* src, int slots, int64_t* counts, double
     for (int k = 0; k + 1 < g.d; ++k) rows_live *= g.M[k];
     e = r2c_last(nullptr, spec, rows_live, g.P[g.d - 1], tw, s, cs, fs);
     if (e != hipSuccess) return e;
-    if (g.d == 1) {
-        const int64_t cnt = g.P[0] / 2 + 1;
-        hipLaunchKernelGGL(k_abs2, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, spec, wmix, cnt);
-        return hipGetLastError();
-    }
     // forward passes over the counts' spectrum, pruned: before the pass along
     // axis a only columns with i_k < M_k (k < a) are nonzero, and only their
     // first M_a entries
     for (int ax = g.d - 2; ax >= 1 && e == hipSuccess; --ax) {
         int64_t outer, inner;
         axis_shape(g, ax, &outer, &inner);
-        Prune pr{ax, {1, 1, 1}, {1, 1, 1}, g.M[ax]};
+        Prune pr{ax, {1, 1, 1}, {1, 1, 1}, g.M[ax], 0};
         for (int k = 0; k < ax; ++k) {
             pr.P[k] = g.P[k];
             pr.M[k] = g.M[k];
         }
         e = c2c(spec, nullptr, outer, g.P[ax], inner, -1, 0, tw, s, fs, pr);
     }
+    if (e != hipSuccess || g.d == 1) return e;
+    int64_t outer, inner;
+    axis_shape(g, 0, &outer, &inner);
+    return c2c(spec, wmix, outer, g.P[0], inner, -1, wmix ? 1 : 0, tw, s, fs,
+               Prune{0, {1, 1, 1}, {1, 1, 1}, g.M[0], 0});
+}
+
+hipError_t fft_counts_nd(const int64_t* slots, int64_t* counts, double2* spec, const kdefft_grid& g, hipStream_t s) {
+    return counts_forward(slots, 1, counts, spec, nullptr, g, s, FS_AUTO, nullptr);
+}
+
+hipError_t fft_prepare_nd(const int64_t* src, int slots, int64_t* counts, double2* spec, double2* wmix,
+                          const kdefft_grid& g, hipStream_t s, int fs, int32_t* reach) {
+    hipError_t e = counts_forward(src, slots, counts, spec, wmix, g, s, fs, reach);
     if (e != hipSuccess) return e;
-    {
-        int64_t outer, inner;
-        axis_shape(g, 0, &outer, &inner);
-        e = c2c(spec, wmix, outer, g.P[0], inner, -1, 1, tw, s, fs, Prune{0, {1, 1, 1}, {1, 1, 1}, g.M[0]});
+    if (g.d == 1) {
+        const int64_t cnt = g.P[0] / 2 + 1;
+        hipLaunchKernelGGL(k_abs2, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, spec, wmix, cnt);
+        return hipGetLastError();
     }
+    const double2* tw;
+    e = twiddles(&tw);
     for (int ax = 1; ax + 1 < g.d && e == hipSuccess; ++ax) {
         int64_t outer, inner;
         axis_shape(g, ax, &outer, &inner);

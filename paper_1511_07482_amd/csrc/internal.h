@@ -152,12 +152,14 @@ struct HeaderArgs {
     double* scal;
 };
 hipError_t launch_ds_header(const HeaderArgs& h, hipStream_t s);
-hipError_t launch_fill_czp(const int64_t* counts, const kdefft_grid& g, double* czp, hipStream_t s);
 
 
-// Multi-dimensional transforms over the circular-layout arrays.
-hipError_t fft_r2c_nd(const double* in, double2* out, const kdefft_grid& g, hipStream_t s);
-hipError_t fft_c2r_nd(double2* inout, double* out, const kdefft_grid& g, hipStream_t s);
+// Transforms along all axes but the first of arrays of slices (fft.hip).
+hipError_t fft_slices_forward(const double* in, double2* out, const kdefft_grid& g, int64_t slices, hipStream_t s);
+hipError_t fft_slices_inverse(double2* buf, const kdefft_grid& g, int64_t slices, hipStream_t s);
+// spec = R2C of the counts gathered from the binning's corner slots (also
+// written to counts).
+hipError_t fft_counts_nd(const int64_t* slots, int64_t* counts, double2* spec, const kdefft_grid& g, hipStream_t s);
 // FFT-stage schedules of the count transform (launch shapes and radix order
 // of its passes; fft.hip FS_*): fs in [0, FFT_SCHEDULES), 0 the default.
 constexpr int FFT_SCHEDULES = 6;
@@ -174,16 +176,20 @@ hipError_t fft_prepare_nd(const int64_t* src, int slots, int64_t* counts, double
 // computed from the mixed spectrum (rows at negated leading indices).
 hipError_t fft_autocorr_nd(const double2* wmix, double* alag, const kdefft_grid& g, hipStream_t s, int fs);
 
-// Paper-literal path, one grid per launch.
-hipError_t launch_kgrid_psi(double* out, const kdefft_grid& g, int r, const ParamBlock& prm,
-                            int entry, hipStream_t s);
-hipError_t launch_kgrid_scv(double* out, const kdefft_grid& g, const ParamBlock& prm, int entry,
+// Paper-literal path.  Step 2: the kernel grids of entries [first, first + nent)
+// of a family at the slices l_0 = 0..m-1 (m = M_0; d = 1: the whole row) of the
+// circular layout, kreal [nent, m, P_1, .., P_{d-1}]; the support is |l_k| < g.M[k].
+hipError_t launch_kgrid_psi(double* kreal, const kdefft_grid& g, int m, int r, const ParamBlock& prm, int first,
+                            int nent, hipStream_t s);
+hipError_t launch_kgrid_scv(double* kreal, const kdefft_grid& g, int m, const ParamBlock& prm, int first, int nent,
                             hipStream_t s);
-hipError_t launch_cmul(double2* K, const double2* C, int64_t count, hipStream_t s);
-hipError_t launch_dot_counts(const int64_t* counts, const double* sreal, const kdefft_grid& g,
-                             double* partial, int nblk, hipStream_t s);
-hipError_t launch_sum_scale(const double* partial, int nblk, double scale, double* out,
-                            hipStream_t s);
+// Steps 3 and 4 (conv.hip): transform of kreal into K [nent, m, P_1, .., Q],
+// product with the count spectrum C, inverse, and out[e] = scale * sum over the
+// nodes of counts times convolution.  mk: the kernels' support along axis 0
+// (l_0 < mk).  partial: nent * conv_blocks(g) values.
+int conv_blocks(const kdefft_grid& g);
+hipError_t conv_sums(const kdefft_grid& g, int mk, int nent, double* kreal, double2* K, const double2* C,
+                     const int64_t* counts, double* partial, double scale, double* out, hipStream_t s);
 hipError_t launch_scv_plain_final(const double* sums, const ParamBlock& fin, int d, double* out,
                                   hipStream_t s);
 
