@@ -512,8 +512,14 @@ hipStream_t S(void* stream) { return static_cast<hipStream_t>(stream); }
 // Step 1 of the plain path: bin X, and the spectrum of the counts.
 int bin_and_transform(const double* X, int64_t n, const kdefft_grid& g, const PlainScratch& p, hipStream_t s) {
     HIPCHK(launch_zero(p.n_out, sizeof(int32_t), s), "zero n_out");
-    HIPCHK(launch_linbin_slots(X, n, g, p.slots, p.n_out, s, nullptr, false), "linbin");
-    HIPCHK(fft_counts_nd(p.slots, p.counts, p.C, g, s), "R2C counts");
+    const bool bands = linbin_in_bands(n, g);
+    if (bands) {
+        HIPCHK(launch_zero(p.counts, sizes_of(g).prodM * sizeof(int64_t), s), "zero counts");
+        HIPCHK(launch_linbin_bands(X, n, g, p.counts, p.n_out, s), "linbin");
+    } else {
+        HIPCHK(launch_linbin_slots(X, n, g, p.slots, p.n_out, s, nullptr, false), "linbin");
+    }
+    HIPCHK(fft_counts_nd(bands ? p.counts : p.slots, bands ? 0 : 1, p.counts, p.C, g, s), "R2C counts");
     return KDEFFT_OK;
 }
 
@@ -560,16 +566,20 @@ int prepare_into(const double* X, int64_t n, const kdefft_grid& g, const double*
     for (int k = 0; k < g.d; ++k) h.pad[k] = pad ? pad[k] : 0.0;
     h.n_out = L.n_out;
     h.scal = L.scal;
-    if (partial) {
-        // grid from the bound partials and the header inside the binning launch
-        // (the bounds launch cleared the counter, the scalar block and the slots)
-        HIPCHK(launch_linbin_slots(X, n, g, slots, L.n_out, s, nullptr, true, &h), "linbin");
+    const bool bands = linbin_in_bands(n, g);   // counts directly, without the corner slots
+    // with partials: the grid and the header inside the binning launch (the
+    // bounds launch cleared the counter, the scalar block and the target)
+    if (!partial) HIPCHK(launch_ds_header(h, s), "dataset header");
+    if (bands) {
+        if (!partial) HIPCHK(launch_zero(L.counts, sizes_of(g).prodM * sizeof(int64_t), s), "zero counts");
+        HIPCHK(launch_linbin_bands(X, n, g, L.counts, L.n_out, s, partial ? &h : nullptr), "linbin");
     } else {
-        HIPCHK(launch_ds_header(h, s), "dataset header");
-        HIPCHK(launch_linbin_slots(X, n, g, slots, L.n_out, s, nullptr, false), "linbin");
+        HIPCHK(launch_linbin_slots(X, n, g, slots, L.n_out, s, nullptr, partial != nullptr, partial ? &h : nullptr),
+               "linbin");
     }
     const int fs = fft_sched_for(g);
-    HIPCHK(fft_prepare_nd(slots, 1, L.counts, L.spec, L.wmix, g, s, fs), "count transform");
+    HIPCHK(fft_prepare_nd(bands ? L.counts : slots, bands ? 0 : 1, L.counts, L.spec, L.wmix, g, s, fs),
+           "count transform");
     HIPCHK(fft_autocorr_nd(L.wmix, L.alag, g, s, fs), "count autocorrelation");
     return KDEFFT_OK;
 }
@@ -853,7 +863,10 @@ int kdefft_linbin(const double* X, int64_t n, const kdefft_grid* g, int64_t* cou
     hipStream_t s = S(stream);
     HIPCHK(launch_zero(counts, sizes_of(*g).prodM * sizeof(int64_t), s), "zero counts");
     if (n_out_dev) HIPCHK(launch_zero(n_out_dev, sizeof(int32_t), s), "zero n_out");
-    HIPCHK(launch_linbin(X, n, *g, counts, n_out_dev, s), "linbin");
+    if (linbin_in_bands(n, *g))
+        HIPCHK(launch_linbin_bands(X, n, *g, counts, n_out_dev, s), "linbin");
+    else
+        HIPCHK(launch_linbin(X, n, *g, counts, n_out_dev, s), "linbin");
     return KDEFFT_OK;
 }
 
@@ -1075,8 +1088,13 @@ int kdefft_dataset_prepare_auto(const double* X, int64_t n, int d, const int32_t
         volatile double pk = pad_sd * sd;   // the same product as kdefft_grid_auto
         pad[k] = pk;
     }
-    HIPCHK(launch_bounds_partial(X, n, d, partial, (int)nb, s, slots,
-                                 (size_t)(corner_slots(g.d) * sizes_of(g).prodM) * sizeof(int64_t), dl.n_out, dl.scal),
+    // clears the binning's target: the counts (to a multiple of 16 bytes, inside
+    // their 256-byte aligned place) or the slots
+    const size_t cells = (size_t)sizes_of(g).prodM;
+    const bool bands = linbin_in_bands(n, g);
+    HIPCHK(launch_bounds_partial(X, n, d, partial, (int)nb, s, bands ? dl.counts : slots,
+                                 bands ? (cells + 1) / 2 * 16 : (size_t)corner_slots(g.d) * cells * sizeof(int64_t),
+                                 dl.n_out, dl.scal),
            "bounds");
     rc = prepare_into(X, n, g, Gpilot_host, dl, slots, s, partial, (int)nb, pad);
     if (rc) return rc;

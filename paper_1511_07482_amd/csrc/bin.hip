@@ -177,6 +177,70 @@ __device__ __forceinline__ void grid_from_bounds(const HeaderArgs& h, double* lo
     }
 }
 
+// Origin and spacing from the bound partials into g; block 0 writes the
+// dataset record.  Called by all threads of a block.
+template <int D>
+__device__ __forceinline__ void dataset_header(const HeaderArgs& hdr, kdefft_grid& g) {
+    int reach[D];
+    grid_from_bounds<D>(hdr, g.lo, g.delta, reach);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        DsDev v = hdr.val;
+        for (int k = 0; k < D; ++k) {
+            v.lo[k] = g.lo[k];
+            v.delta[k] = g.delta[k];
+            v.reach[k] = reach[k];
+        }
+        *hdr.rec = v;
+    }
+}
+
+// One point's increments (the contract above) and the flat index of its lowest
+// corner; false when the point lies outside the grid (q and fb then unset).
+// Corner b: bit k set = upper node along axis k.  The integers are formed as
+// doubles, exactly: w * 2^40 is a scaling, below 2^52, so adding 2^52 rounds
+// it to the nearest integer (ties to even); differences and sums of these
+// integers stay below 2^53; and 2^52 + q holds q in its low mantissa bits.
+template <int D, class I>
+__device__ __forceinline__ bool point_increments(const double* x, const kdefft_grid& g, const I* stride, long long* q,
+                                                 I& fb) {
+#pragma clang fp contract(off)
+    constexpr int NC = 1 << D;
+    const double one_q = 1099511627776.0, big = 4503599627370496.0;   // 2^40, 2^52
+    double w0[D], w1[D];
+    I f0 = 0;
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        const double t = (x[k] - g.lo[k]) / g.delta[k];
+        ok = ok && (t >= 0.0) && (t <= (double)(g.M[k] - 1));
+        const double jf = fmin(floor(t), (double)(g.M[k] - 2));   // M - 1 -> M - 2
+        const double f = t - jf;
+        w0[k] = 1.0 - f;
+        w1[k] = f;
+        f0 += (I)(int)jf * stride[k];
+    }
+    fb = f0;
+    double v[NC], top, sum;
+#pragma unroll
+    for (int b = 0; b < NC; ++b) {
+        double w = (b & 1) ? w1[0] : w0[0];
+#pragma unroll
+        for (int k = 1; k < D; ++k) w = w * (((b >> k) & 1) ? w1[k] : w0[k]);
+        v[b] = fma(w, one_q, big) - big;
+        top = b ? fmax(top, v[b]) : v[b];
+        sum = b ? sum + v[b] : v[b];
+    }
+    const double fix = one_q - (sum - top);
+    bool taken = false;
+#pragma unroll
+    for (int b = 0; b < NC; ++b) {
+        const bool m = v[b] == top && !taken;
+        taken = taken || m;
+        q[b] = __double_as_longlong((m ? fix : v[b]) + big) & 0xfffffffffffffLL;
+    }
+    return ok;
+}
+
 // hdr.partial set: the dataset header is computed here, not by a separate
 // launch: every block derives the grid origin and spacing from the bound
 // partials (grid_from_bounds), and block 0 writes the dataset record.
@@ -196,25 +260,12 @@ __global__ __launch_bounds__(256) void k_linbin(const double* __restrict__ X, in
             g.delta[k] = gdev[4 + k];
         }
     }
-    if (hdr.partial) {   // block-uniform
-        int reach[D];
-        grid_from_bounds<D>(hdr, g.lo, g.delta, reach);
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            DsDev v = hdr.val;
-            for (int k = 0; k < D; ++k) {
-                v.lo[k] = g.lo[k];
-                v.delta[k] = g.delta[k];
-                v.reach[k] = reach[k];
-            }
-            *hdr.rec = v;
-        }
-    }
+    if (hdr.partial) dataset_header<D>(hdr, g);   // block-uniform
     int64_t stride[D];
     stride[D - 1] = 1;
 #pragma unroll
     for (int k = D - 2; k >= 0; --k) stride[k] = stride[k + 1] * g.M[k + 1];
     const int lane = threadIdx.x & 63, w0ff = threadIdx.x & ~63;
-    const double one_q = 1099511627776.0;  // 2^40
     for (int64_t i0 = blockIdx.x * 256LL; i0 < n; i0 += (int64_t)gridDim.x * 256) {   // block-uniform
         const int64_t i = i0 + threadIdx.x;
         long long q[NC];
@@ -222,40 +273,13 @@ __global__ __launch_bounds__(256) void k_linbin(const double* __restrict__ X, in
         for (int b = 0; b < NC; ++b) q[b] = 0;
         int64_t fb = 0;
         if (i < n) {
-            double w0[D], w1[D];
-            int64_t j[D];
-            bool ok = true;
+            double x[D];
 #pragma unroll
-            for (int k = 0; k < D; ++k) {
-                const double t = (X[i * D + k] - g.lo[k]) / g.delta[k];
-                ok = ok && (t >= 0.0) && (t <= (double)(g.M[k] - 1));
-                double jf = floor(t);
-                if (jf == (double)(g.M[k] - 1)) jf = (double)(g.M[k] - 2);
-                const double f = t - jf;
-                w0[k] = 1.0 - f;
-                w1[k] = f;
-                j[k] = (int64_t)jf;
-            }
-            if (!ok) {
+            for (int k = 0; k < D; ++k) x[k] = X[i * D + k];
+            if (!point_increments<D>(x, g, stride, q, fb)) {
+#pragma unroll
+                for (int b = 0; b < NC; ++b) q[b] = 0;
                 if (n_out) atomicAdd(n_out, 1);
-            } else {
-                // corner b: bit k set = upper node along axis k
-                int best = 0;
-#pragma unroll
-                for (int b = 0; b < NC; ++b) {
-                    double w = (b & 1) ? w1[0] : w0[0];
-#pragma unroll
-                    for (int k = 1; k < D; ++k) w = w * (((b >> k) & 1) ? w1[k] : w0[k]);
-                    q[b] = (long long)rint(w * one_q);
-                    if (q[b] > q[best]) best = b;
-                }
-                long long rest = 0;
-#pragma unroll
-                for (int b = 0; b < NC; ++b)
-                    if (b != best) rest += q[b];
-                q[best] = (1LL << 40) - rest;
-#pragma unroll
-                for (int k = 0; k < D; ++k) fb += j[k] * stride[k];
             }
         }
         // issue order c = bit-reversed b: bit 0 of c is the last axis
@@ -292,6 +316,117 @@ __global__ __launch_bounds__(256) void k_linbin(const double* __restrict__ X, in
         }
         __syncthreads();
     }
+}
+
+// The same increments summed in LDS first.  The scattered atomics above run
+// at the memory side's rate of about 11e9 records a second, whatever the
+// grid's size; a sample much larger than its grid is cheaper to add up on the
+// compute units.  A block holds one band of BAND consecutive nodes and adds
+// its part of the points to it, skipping the corners of other bands, then adds
+// the band to the counts, neighbouring lanes to neighbouring nodes.  Bound by
+// the per-point arithmetic, about 135 instructions for d = 2, repeated once
+// per band: 2e6 points on 256 x 256 nodes (4 bands), whole preparation 205 ->
+// 74 us.  (Passing on only the points that reach the band, through a queue per
+// wavefront, measured the same: the middle bands take half of the points.)
+// The bands of one part of the points run on one XCD (blocks b and b + 8 share
+// it), which reads the part from memory once.  Counts as above, bit for bit:
+// the sums are integers.  The count grid must be zero on entry.
+constexpr int BAND = 20416;   // 160 KB less the header's scratch
+template <int D>
+__global__ __launch_bounds__(1024) void k_linbin_bands(const double* __restrict__ X, int64_t n, kdefft_grid g,
+                                                       unsigned long long* __restrict__ counts,
+                                                       int32_t* __restrict__ n_out, int nodes, int band_nodes,
+                                                       int nbands, int64_t part_points, HeaderArgs hdr) {
+    constexpr int NC = 1 << D, U = D < 3 ? 4 : 2;
+    __shared__ unsigned long long acc[BAND];
+    if (hdr.partial) {
+        dataset_header<D>(hdr, g);
+        __syncthreads();
+    }
+    const int band = (int)(blockIdx.x / 8) % nbands;
+    const int64_t part = (int64_t)(blockIdx.x / (8 * nbands)) * 8 + blockIdx.x % 8;
+    const int first = band * band_nodes, len = min(band_nodes, nodes - first);
+    for (int i = threadIdx.x; i < len; i += 1024) acc[i] = 0;
+    int stride[D];
+    stride[D - 1] = 1;
+#pragma unroll
+    for (int k = D - 2; k >= 0; --k) stride[k] = stride[k + 1] * g.M[k + 1];
+    __syncthreads();
+    const int64_t p0 = part * part_points, p1 = p0 + part_points < n ? p0 + part_points : n;
+    int out = 0;
+    for (int64_t i0 = p0 + threadIdx.x; i0 < p1; i0 += 1024 * U) {
+        double x[U][D];   // U points' loads in flight
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = i0 + 1024 * u < p1 ? i0 + 1024 * u : i0;
+#pragma unroll
+            for (int k = 0; k < D; ++k) x[u][k] = X[i * D + k];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i0 + 1024 * u >= p1) break;
+            long long q[NC];
+            int fb;
+            const bool ok = point_increments<D>(x[u], g, stride, q, fb);
+            out += !ok;
+#pragma unroll
+            for (int b = 0; b < NC; ++b) {
+                int off = -first;
+#pragma unroll
+                for (int k = 0; k < D; ++k) off += ((b >> k) & 1) * stride[k];
+                const int c = fb + off;
+                if (ok && (unsigned)c < (unsigned)len) atomicAdd(&acc[c], (unsigned long long)q[b]);
+            }
+        }
+    }
+    if (out && band == 0 && n_out) atomicAdd(n_out, out);
+    __syncthreads();
+    for (int i = threadIdx.x; i < len; i += 1024) {
+        const unsigned long long v = acc[i];
+        if (v) atomicAdd(counts + first + i, v);
+    }
+}
+
+// Bands or scattered atomics.  A block's flush costs its band's nodes, the
+// scattered records n; the repeated arithmetic costs n times the bands.  Whole
+// preparations, us, scattered -> bands (normal data): d = 1, M = 500: n = 1e4
+// 31.5 -> 31.3, 1e5 76 -> 34, 2e6 1103 -> 44; d = 2, M = 200 (2 bands): 5e4
+// 37.5 -> 39.0, 1e5 41.9 -> 42.1, 2e5 52.8 -> 46.4, 2e6 218 -> 68; M = 300
+// (5 bands): 2e5 70 -> 76, 5e5 85 -> 80; d = 3, M = 27 (1 band): 2e4 47.9 ->
+// 47.8, 1e5 57 -> 49; M = 54 (8 bands): 1e5 87.4 -> 87.8, 2e6 215 -> 179;
+// d = 4, M = 16 (4 bands): 1e4 75 -> 68, 2e6 739 -> 159.  Hence bands from
+// 10000 points and from 3 points a node for d <= 2, one for d = 3 and a
+// quarter for d = 4 (2^d increments a point).
+constexpr int MAX_BANDS = 8;
+bool linbin_in_bands(int64_t n, const kdefft_grid& g) {
+    int64_t nodes = 1;
+    for (int k = 0; k < g.d; ++k) nodes *= g.M[k];
+    return nodes <= MAX_BANDS * BAND && n >= 10000 && (g.d == 4 ? 4 * n : n) >= (g.d <= 2 ? 3 * nodes : nodes);
+}
+
+hipError_t launch_linbin_bands(const double* X, int64_t n, const kdefft_grid& g, int64_t* counts, int32_t* n_out,
+                               hipStream_t s, const HeaderArgs* hdr) {
+    int64_t nodes = 1;
+    for (int k = 0; k < g.d; ++k) nodes *= g.M[k];
+    if (nodes > MAX_BANDS * BAND) return hipErrorInvalidValue;
+    const int nbands = (int)((nodes + BAND - 1) / BAND), band_nodes = (int)((nodes + nbands - 1) / nbands);
+    // parts in eights (one per XCD), at most one block per compute unit and at
+    // least 1024 points each (8192: d = 4, M = 8, n = 1e5 58 us, 1024: 44 us)
+    int64_t parts = 256 / nbands / 8 * 8;
+    while (parts > 8 && n / parts < 1024) parts -= 8;
+    const int64_t part_points = (n + parts - 1) / parts;
+    HeaderArgs h{};
+    if (hdr) h = *hdr;
+    const dim3 grid((unsigned)(parts * nbands));
+    auto* c = reinterpret_cast<unsigned long long*>(counts);
+    switch (g.d) {
+        case 1: hipLaunchKernelGGL(k_linbin_bands<1>, grid, dim3(1024), 0, s, X, n, g, c, n_out, (int)nodes, band_nodes, nbands, part_points, h); break;
+        case 2: hipLaunchKernelGGL(k_linbin_bands<2>, grid, dim3(1024), 0, s, X, n, g, c, n_out, (int)nodes, band_nodes, nbands, part_points, h); break;
+        case 3: hipLaunchKernelGGL(k_linbin_bands<3>, grid, dim3(1024), 0, s, X, n, g, c, n_out, (int)nodes, band_nodes, nbands, part_points, h); break;
+        case 4: hipLaunchKernelGGL(k_linbin_bands<4>, grid, dim3(1024), 0, s, X, n, g, c, n_out, (int)nodes, band_nodes, nbands, part_points, h); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_linbin_slots(const double* X, int64_t n, const kdefft_grid& g, int64_t* slots, int32_t* n_out,

@@ -236,22 +236,24 @@ __device__ __forceinline__ void block_sum(double* vals, double* scratch, double*
 __device__ __forceinline__ void reduce_bounds(const double* __restrict__ partial, int nblk, int d,
                                               double* scratch, double* red) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    if (wid < 4) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        double mn = INFINITY, mx = -INFINITY;
-        if (k < d)
-            for (int b = threadIdx.x; b < nblk; b += 256) {
-                mn = fmin(mn, partial[b * 8 + k]);
-                mx = fmax(mx, partial[b * 8 + 4 + k]);
+        for (int k = 0; k < 4; ++k) {
+            double mn = INFINITY, mx = -INFINITY;
+            if (k < d)
+                for (int b = threadIdx.x; b < nblk; b += 256) {
+                    mn = fmin(mn, partial[b * 8 + k]);
+                    mx = fmax(mx, partial[b * 8 + 4 + k]);
+                }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                mn = fmin(mn, __shfl_xor(mn, off, 64));
+                mx = fmax(mx, __shfl_xor(mx, off, 64));
             }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            mn = fmin(mn, __shfl_xor(mn, off, 64));
-            mx = fmax(mx, __shfl_xor(mx, off, 64));
-        }
-        if (lane == 0) {
-            scratch[wid * 8 + k] = mn;
-            scratch[wid * 8 + 4 + k] = mx;
+            if (lane == 0) {
+                scratch[wid * 8 + k] = mn;
+                scratch[wid * 8 + 4 + k] = mx;
+            }
         }
     }
     __syncthreads();

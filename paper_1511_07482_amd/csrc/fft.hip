@@ -763,8 +763,9 @@ static hipError_t counts_forward(const int64_t* src, int slots, int64_t* counts,
                Prune{0, {1, 1, 1}, {1, 1, 1}, g.M[0], 0});
 }
 
-hipError_t fft_counts_nd(const int64_t* slots, int64_t* counts, double2* spec, const kdefft_grid& g, hipStream_t s) {
-    return counts_forward(slots, 1, counts, spec, nullptr, g, s, FS_AUTO, nullptr);
+hipError_t fft_counts_nd(const int64_t* src, int slots, int64_t* counts, double2* spec, const kdefft_grid& g,
+                         hipStream_t s) {
+    return counts_forward(src, slots, counts, spec, nullptr, g, s, FS_AUTO, nullptr);
 }
 
 hipError_t fft_prepare_nd(const int64_t* src, int slots, int64_t* counts, double2* spec, double2* wmix,

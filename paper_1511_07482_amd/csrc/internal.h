@@ -135,6 +135,11 @@ struct HeaderArgs;
 // the grid from the bound partials and writes the dataset header (block 0).
 hipError_t launch_linbin_slots(const double* X, int64_t n, const kdefft_grid& g, int64_t* slots, int32_t* n_out,
                                hipStream_t s, const double* gdev, bool slots_zeroed, const HeaderArgs* hdr = nullptr);
+// Binning straight into the count grid (zero on entry) by bands of nodes in
+// LDS: for the samples and grids that linbin_in_bands accepts.
+bool linbin_in_bands(int64_t n, const kdefft_grid& g);
+hipError_t launch_linbin_bands(const double* X, int64_t n, const kdefft_grid& g, int64_t* counts, int32_t* n_out,
+                               hipStream_t s, const HeaderArgs* hdr = nullptr);
 
 // One small launch at the start of a dataset's preparation: the record (with
 // the grid origin and spacing from the data bounds when `partial` is set --
@@ -157,9 +162,10 @@ hipError_t launch_ds_header(const HeaderArgs& h, hipStream_t s);
 // Transforms along all axes but the first of arrays of slices (fft.hip).
 hipError_t fft_slices_forward(const double* in, double2* out, const kdefft_grid& g, int64_t slices, hipStream_t s);
 hipError_t fft_slices_inverse(double2* buf, const kdefft_grid& g, int64_t slices, hipStream_t s);
-// spec = R2C of the counts gathered from the binning's corner slots (also
-// written to counts).
-hipError_t fft_counts_nd(const int64_t* slots, int64_t* counts, double2* spec, const kdefft_grid& g, hipStream_t s);
+// spec = R2C of the counts: src, or gathered from the binning's corner slots
+// in src (slots set; then also written to counts).
+hipError_t fft_counts_nd(const int64_t* src, int slots, int64_t* counts, double2* spec, const kdefft_grid& g,
+                         hipStream_t s);
 // FFT-stage schedules of the count transform (launch shapes and radix order
 // of its passes; fft.hip FS_*): fs in [0, FFT_SCHEDULES), 0 the default.
 constexpr int FFT_SCHEDULES = 6;
