@@ -35,7 +35,7 @@ UNITS = ["api.cpp", "noalloc.hip", "minimize.hip", "fft.hip", "bin.hip", "plain.
          "rows_d1.hip", "rows_d2.hip", "rows_d3.hip", "rows_d4.hip",
          "rows_eta_d1.hip", "rows_eta_d2.hip", "rows_eta_d3.hip", "rows_eta_d4.hip"]
 HEADERS = ["dev_common.h", "dev_kernels.h", "eta_fun.h", "finish.h", "internal.h", "params.h", "rows_impl.h",
-           "rows_dispatch.h", "cols.h"]
+           "rows_dispatch.h", "cols.h", "minstep.h"]
 
 
 def _newest_header():

@@ -1203,7 +1203,7 @@ static int crit_kind(int crit, int r, bool want_grad, bool adjoint) {
 static int crit_common(const kdefft_dataset* ds, int n_ds, const int64_t* off, const double* vechL, int crit,
                        int r, int kind, const double* grad_out, double* obj, double* grad, int32_t* status,
                        void* ws, size_t ws_bytes, void* stream, const RowLaunch* force,
-                       int64_t* walk_runs = nullptr) {
+                       int64_t* walk_runs = nullptr, const MinStep* step = nullptr) {
     int rc = check_batch_ds(ds, n_ds, KDEFFT_MAX_BATCH_DS);
     if (rc) return rc;
     if (crit < KDEFFT_CRIT_SCV || crit > KDEFFT_CRIT_QR) return fail(KDEFFT_E_ARG, "crit=%d", crit);
@@ -1281,7 +1281,7 @@ static int crit_common(const kdefft_dataset* ds, int n_ds, const int64_t* off, c
                             [&] { return launch_rows(kind, g.d, kr, geo, b.prm, nc, b.partial, rl, s); }),
                "criterion rows");
     }
-    HIPCHK(launch_scv_final(kind, g.d, b.partial, nchunks, b.prm, B, npseudo, grad_out, obj, grad, s),
+    HIPCHK(launch_scv_final(kind, g.d, b.partial, nchunks, b.prm, B, npseudo, grad_out, obj, grad, step, s),
            "criterion final");
     return KDEFFT_OK;
 }
@@ -1451,15 +1451,17 @@ int kdefft_minimize(const kdefft_dataset* ds, int n_ds, const int64_t* off, int 
     const size_t crit_bytes = ws_bytes - (size_t)(crit_ws - static_cast<char*>(ws));
     hipStream_t s = S(stream);
     HIPCHK(launch_min_init(B, q, vechL0, m.xt, m.ist, s), "minimiser init");
+    const MinStep step{tol, m.st, m.ist, m.stt, m.xt};
     for (int e = 0; e < evals; ++e) {
         if (pi) {
             rc = kdefft_pi_batch(d, n_ds, n_host, psi4, off, m.xt, m.ft, m.gt, m.stt, stream);
+            if (rc) return rc;
+            HIPCHK(launch_min_step(B, q, step, m.ft, m.gt, s), "minimiser step");
         } else {
             rc = crit_common(ds, n_ds, off, m.xt, crit, 0, FUN_SCV_OBJGRAD, nullptr, m.ft, m.gt, m.stt, crit_ws,
-                             crit_bytes, stream, nullptr);
+                             crit_bytes, stream, nullptr, nullptr, &step);
+            if (rc) return rc;
         }
-        if (rc) return rc;
-        HIPCHK(launch_min_step(B, q, tol, m.st, m.ist, m.ft, m.gt, m.stt, m.xt, s), "minimiser step");
     }
     HIPCHK(launch_min_final(B, q, m.st, m.ist, vechL_out, obj_out, info, s), "minimiser final");
     return KDEFFT_OK;

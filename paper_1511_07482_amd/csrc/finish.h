@@ -73,58 +73,71 @@ __device__ static double chunk_sum(const double* __restrict__ partial, int64_t h
     return wave_sum(s);
 }
 
-// Sum of grid g of the count items from item `first` (partial sums of NG = ng
-// values per item), by one wavefront in the same fixed order as chunk_sum.
-__device__ static double item_sum(const double* __restrict__ partial, int64_t first, int64_t count, int ng, int g) {
+// Sums of the first NG grids of the count items from item `first` (partial
+// sums of ng values per item; a grid from ng on gives 0), by one wavefront in
+// the same fixed order as chunk_sum; the grids' loads and trees in flight
+// together.
+template <int NG>
+__device__ __forceinline__ static void item_sums(const double* __restrict__ partial, int64_t first, int64_t count,
+                                                 int ng, double* T) {
     const int lane = threadIdx.x & 63;
-    double s = 0.0;
-    for (int64_t c = lane; c < count; c += 64) s += partial[(first + c) * ng + g];
-    return wave_sum(s);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) T[g] = 0.0;
+    for (int64_t c = lane; c < count; c += 64) {
+        const double* row = partial + (first + c) * ng;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) T[g] += row[g < ng ? g : 0];
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) T[g] += __shfl_xor(T[g], off, 64);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) T[g] = g < ng ? T[g] : 0.0;
 }
 
-// Criterion assembly for candidate h by one wavefront (p: its parameter
-// block).  kind: FUN_SCV_OBJ or FUN_ETA* (obj only), FUN_SCV_OBJGRAD (obj +
-// grad), FUN_SCV_GRAD (adjoint: grad scaled by grad_out).
-// The candidate's work items are `count` items from `first`; cst is the
-// constant term added to the objective (the SCV phi_{2G} sum, else 0).
+// Criterion assembly for a candidate (p: its parameter block, T: its sums over
+// the lags).  kind: FUN_SCV_OBJ or FUN_ETA* (objective only), FUN_SCV_OBJGRAD
+// (objective + gradient), FUN_SCV_GRAD (adjoint: gradient scaled by gscale).
+// cst is the constant term added to the objective (the SCV phi_{2G} sum, else
+// 0).  Returns the objective; gv: the gradient in vech(L) order, if kind has one.
 template <int D>
-__device__ __forceinline__ static void crit_finish(int kind, const double* __restrict__ partial, int64_t first,
-                                                   int64_t count, int ng, const double* __restrict__ p, int64_t h,
-                                                   double cst, const double* __restrict__ grad_out,
-                                                   double* __restrict__ obj, double* __restrict__ grad) {
+__device__ __forceinline__ static double crit_finish(int kind, const double* T, const double* __restrict__ p,
+                                                     double cst, double gscale, bool want_grad, double* gv) {
     constexpr int d = D;
-    constexpr int q = d * (d + 1) / 2;
-    double T[1 + q];
-#pragma unroll
-    for (int g = 0; g < 1 + q; ++g) T[g] = g < ng ? item_sum(partial, first, count, ng, g) * p[S_SCALE] : 0.0;
-    if ((threadIdx.x & 63) != 0) return;
     const bool sing = p[S_SING] != 0.0;
     const double nan = __longlong_as_double(0x7ff8000000000000LL);
-    const double* L = p + S_L;
     // closed-form term: proportional to |H|^{-1/2} for every criterion with a
     // gradient, so its matrix gradient is -1/2 first H^{-1}
-    const double t0 = p[S_FIRST];
-    if (kind != FUN_SCV_GRAD) obj[h] = sing ? nan : t0 + T[0] + cst;
-    if (kind == FUN_SCV_OBJ || kind == FUN_ETA1 || kind == FUN_ETA2 || grad == nullptr) return;
-    const int off = kind == FUN_SCV_OBJGRAD ? 1 : 0;
-    double Hinv[16];
+    const double t0 = p[S_FIRST], scale = p[S_SCALE];
+    const double obj = sing ? nan : t0 + T[0] * scale + cst;
+    if (!want_grad) return obj;
+    double L[16], Hinv[16], gH[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) L[i] = p[S_L + i];
     chol_inv4<D>(L, Hinv);
-    double gH[16];
-    int t = off;
+    const bool both = kind == FUN_SCV_OBJGRAD;   // T[0] is the objective's sum
+    int t = 0;
+#pragma unroll
     for (int i = 0; i < d; ++i)
+#pragma unroll
         for (int j = i; j < d; ++j) {
-            const double v = -0.5 * t0 * Hinv[i * 4 + j] + T[t++];
+            const double v = -0.5 * t0 * Hinv[i * 4 + j] + (both ? T[t + 1] : T[t]) * scale;
+            ++t;
             gH[i * 4 + j] = v;
             gH[j * 4 + i] = v;
         }
-    const double sc = kind == FUN_SCV_GRAD ? grad_out[h] : 1.0;
     int o = 0;
+#pragma unroll
     for (int j = 0; j < d; ++j)
+#pragma unroll
         for (int i = j; i < d; ++i) {
             double s = 0.0;
-            for (int k = 0; k < d; ++k) s += gH[i * 4 + k] * L[k * 4 + j];
-            grad[h * q + o++] = sing ? nan : 2.0 * s * sc;
+#pragma unroll
+            for (int k = j; k < d; ++k) s += gH[i * 4 + k] * L[k * 4 + j];
+            gv[o++] = sing ? nan : 2.0 * s * gscale;
         }
+    return obj;
 }
 
 __device__ __forceinline__ static void* slot_ptr(double v) {

@@ -217,19 +217,29 @@ constexpr int ROW_VARIANTS = 7;
 hipError_t launch_scv_setup(const double* vechL, const ScvBatchArgs& a, int64_t ncand, int npseudo, double* prm,
                             int32_t* status, const RowGeom& geo, int32_t* wc, hipStream_t s);
 hipError_t launch_psi_setup(const PsiBatchArgs& a, double* prm, hipStream_t s);
+// State of a batch of minimisations (minstep.h): per candidate
+// min_state_doubles(q) doubles and min_state_ints() int32, the criterion's
+// status (may be NULL) and the trial points.
+struct MinStep {
+    double tol;
+    double* st;
+    int32_t* ist;
+    const int32_t* stt;
+    double* xt;
+};
+// step (may be NULL; FUN_SCV_OBJGRAD): the values and gradients go to one
+// update of the minimiser instead of obj and grad.
 hipError_t launch_scv_final(int kind, int d, const double* partial, int64_t nchunks,
                             const double* prm, int64_t ncand, int npseudo, const double* grad_out,
-                            double* obj, double* grad, hipStream_t s);
+                            double* obj, double* grad, const MinStep* step, hipStream_t s);
 hipError_t launch_psi_final(const double* partial, const RowGeom& geo, int ng,
                             const double* prm, int64_t ncand, double* psi, hipStream_t s);
 
-// batched quasi-Newton minimiser (minimize.hip): per-candidate state of
-// min_state_doubles(q) doubles and min_state_ints() int32
+// batched quasi-Newton minimiser (minimize.hip)
 int min_state_doubles(int q);
 int min_state_ints();
 hipError_t launch_min_init(int64_t B, int q, const double* x0, double* xt, int32_t* ist, hipStream_t s);
-hipError_t launch_min_step(int64_t B, int q, double tol, double* st, int32_t* ist, const double* ft,
-                           const double* gt, const int32_t* stt, double* xt, hipStream_t s);
+hipError_t launch_min_step(int64_t B, int q, const MinStep& a, const double* ft, const double* gt, hipStream_t s);
 hipError_t launch_min_final(int64_t B, int q, const double* st, const int32_t* ist, double* x_out, double* f_out,
                             int32_t* info, hipStream_t s);
 hipError_t launch_pi(const PiArgs& a, const double* psi4, const double* vechL, int64_t ncand, double* obj,

@@ -8,6 +8,7 @@
 #include "dev_kernels.h"
 #include "eta_fun.h"
 #include "finish.h"
+#include "minstep.h"
 #include "internal.h"
 #include "params.h"
 #include "rows_impl.h"
@@ -288,38 +289,68 @@ hipError_t launch_ds_header(const HeaderArgs& h, hipStream_t s) {
 // Criterion assembly, one wavefront per candidate (see crit_finish); the
 // npseudo constant-term candidates after the real ones store their term in
 // their dataset's scalar block.  Work items of candidate c: c * nchunks + [0, nchunks).
-template <int D>
+// STEP: the value and the gradient go straight to the minimiser's
+// update of the candidate (d = 2, 4 candidates, us per evaluation: assembly and
+// update as two launches 14.5, together 4.3).
+template <int D, bool STEP>
 __global__ __launch_bounds__(64) void k_scv_final(int kind, const double* __restrict__ partial, int64_t nchunks, int ng,
                                                   const double* __restrict__ prm, int64_t ncand, int npseudo,
                                                   const double* __restrict__ grad_out, double* __restrict__ obj,
-                                                  double* __restrict__ grad) {
+                                                  double* __restrict__ grad, MinStep step) {
+    constexpr int Q = D * (D + 1) / 2;
     const int64_t h = blockIdx.x;
     if (h >= ncand + npseudo) return;
     const double* p = prm + h * PRM;
     if (h >= ncand) {
-        const double v = item_sum(partial, h * nchunks, nchunks, ng, 0) * p[S_SCALE];
-        if (threadIdx.x == 0) static_cast<double*>(slot_ptr(p[S_FIN_SCAL]))[0] = v;
+        double v[1];
+        item_sums<1>(partial, h * nchunks, nchunks, ng, v);
+        if (threadIdx.x == 0) static_cast<double*>(slot_ptr(p[S_FIN_SCAL]))[0] = v[0] * p[S_SCALE];
         return;
     }
-    double cst = 0.0;
+    double T[1 + Q], C[1] = {0.0};
+    double cscale = 0.0;
     if (p[S_PSEUDO] >= 0.0) {
         const int64_t c = (int64_t)p[S_PSEUDO];
-        cst = item_sum(partial, c * nchunks, nchunks, ng, 0) * prm[c * PRM + S_SCALE];
+        item_sums<1>(partial, c * nchunks, nchunks, ng, C);
+        cscale = prm[c * PRM + S_SCALE];
     }
-    crit_finish<D>(kind, partial, h * nchunks, nchunks, ng, p, h, cst, grad_out, obj, grad);
+    item_sums<1 + Q>(partial, h * nchunks, nchunks, ng, T);
+    if (threadIdx.x != 0) return;
+    const bool grads = kind == FUN_SCV_OBJGRAD || kind == FUN_SCV_GRAD;
+    double gv[Q];
+    const double f = crit_finish<D>(kind, T, p, C[0] * cscale, kind == FUN_SCV_GRAD ? grad_out[h] : 1.0,
+                                    STEP || (grads && grad != nullptr), gv);
+    if constexpr (STEP) {
+        min_step<Q>(step, h, f, gv, step.stt && step.stt[h] != 0);
+        return;
+    }
+    if (kind != FUN_SCV_GRAD) obj[h] = f;
+    if (grads && grad != nullptr)
+#pragma unroll
+        for (int i = 0; i < Q; ++i) grad[h * Q + i] = gv[i];
 }
 
 hipError_t launch_scv_final(int kind, int d, const double* partial, int64_t nchunks, const double* prm,
-                            int64_t ncand, int npseudo, const double* grad_out, double* obj, double* grad, hipStream_t s) {
+                            int64_t ncand, int npseudo, const double* grad_out, double* obj, double* grad,
+                            const MinStep* step, hipStream_t s) {
     const int ng = ng_of(kind, d, 2);
     const dim3 grid((unsigned)(ncand + npseudo));
+    if (step && kind != FUN_SCV_OBJGRAD) return hipErrorInvalidValue;
+#define FINAL(DD)                                                                                                   \
+    if (step)                                                                                                       \
+        hipLaunchKernelGGL((k_scv_final<DD, true>), grid, dim3(64), 0, s, kind, partial, nchunks, ng, prm, ncand,   \
+                           npseudo, grad_out, obj, grad, *step);                                                    \
+    else                                                                                                            \
+        hipLaunchKernelGGL((k_scv_final<DD, false>), grid, dim3(64), 0, s, kind, partial, nchunks, ng, prm, ncand,  \
+                           npseudo, grad_out, obj, grad, MinStep{})
     switch (d) {
-        case 1: hipLaunchKernelGGL(k_scv_final<1>, grid, dim3(64), 0, s, kind, partial, nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
-        case 2: hipLaunchKernelGGL(k_scv_final<2>, grid, dim3(64), 0, s, kind, partial, nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
-        case 3: hipLaunchKernelGGL(k_scv_final<3>, grid, dim3(64), 0, s, kind, partial, nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
-        case 4: hipLaunchKernelGGL(k_scv_final<4>, grid, dim3(64), 0, s, kind, partial, nchunks, ng, prm, ncand, npseudo, grad_out, obj, grad); break;
+        case 1: FINAL(1); break;
+        case 2: FINAL(2); break;
+        case 3: FINAL(3); break;
+        case 4: FINAL(4); break;
         default: return hipErrorInvalidValue;
     }
+#undef FINAL
     return hipGetLastError();
 }
 
