@@ -81,8 +81,9 @@ hipError_t twiddles(const double2** out) {
 //    or gathered from the binning's corner slots (c = count 2^-40 at [0, M)^d
 //    of the circular layout, zero elsewhere), so the zero-padded real array is
 //    never materialised.
-//  * RowFlip: the C2R pass reads input row -l' (each leading index negated
-//    modulo P) for output row l'.
+//  * RowFlip: the C2R pass writes input row l (l_0 in [0, P_0/2] only) to
+//    output row -l, and, as the real output f is even, f(l) = f(-l), that row
+//    reversed to output row l.
 struct CountSrc {
     const int64_t* counts;  // nullptr: read the real input array
     int d;
@@ -142,17 +143,21 @@ struct RowFlip {
     int M[3];    // last axis: mlast, of the leading ones: M); rows of zeros are not read
 };
 
-// Row indices of the passes are below 2^31 (checked on the host), so rows
-// are decoded with 32-bit divisions.
-// -1: a row of zeros.
-__device__ __forceinline__ int64_t flip_row(int64_t row, const RowFlip& f) {
+// Output row -l of source row l (each leading index negated modulo P); zero:
+// both are rows of zeros; inner: 0 < l_0 < P_0 / 2, so that row l is not
+// itself read.  Row indices of the passes are below 2^31 (checked on the
+// host), so rows are decoded with 32-bit divisions.
+__device__ __forceinline__ int64_t flip_row(int64_t row, const RowFlip& f, bool& zero, bool& inner) {
     uint32_t r = (uint32_t)row, out = 0, mul = 1;
+    zero = false;
+    inner = false;
     for (int k = f.nlead - 1; k >= 0; --k) {
         const uint32_t p = (uint32_t)f.P[k], i = r % p;
         r /= p;
-        if (f.mlast > 0 && i >= (uint32_t)f.M[k] && i <= p - (uint32_t)f.M[k]) return -1;
+        if (f.mlast > 0 && i >= (uint32_t)f.M[k] && i <= p - (uint32_t)f.M[k]) zero = true;
         out += (i == 0 ? 0u : p - i) * mul;
         mul *= p;
+        if (k == 0) inner = i > 0 && i < p / 2;
     }
     return out;
 }
@@ -283,13 +288,18 @@ __global__ __launch_bounds__(NT) void k_c2r_last(const double2* __restrict__ in,
     constexpr int PS = H + 1;
     __shared__ double2 buf[ROWS * PS];
     __shared__ double2 twl[N];
-    __shared__ int64_t rsrc[ROWS];   // source row of each row (-1: past the end or zeros), decoded once per row
+    // source row (-1: past the end or zeros) and destination rows (-1: none), decoded once per row
+    __shared__ int64_t rsrc[ROWS], rdst[ROWS], rmir[ROWS];
     TwiddleCopy<N, NT> twc;
     twc.fetch(tw);
     const int64_t r0 = (int64_t)blockIdx.x * ROWS;
     for (int rr = threadIdx.x; rr < ROWS; rr += NT) {
         const int64_t row = r0 + rr;
-        rsrc[rr] = row < rows ? (fl.on ? flip_row(row, fl) : row) : -1;
+        bool zero = false, inner = false;
+        const int64_t dst = fl.on ? flip_row(row, fl, zero, inner) : row;
+        rsrc[rr] = row < rows && !zero ? row : -1;
+        rdst[rr] = row < rows ? dst : -1;
+        rmir[rr] = row < rows && inner ? row : -1;
     }
     __syncthreads();
     {
@@ -334,16 +344,19 @@ __global__ __launch_bounds__(NT) void k_c2r_last(const double2* __restrict__ in,
     double2* dst = reinterpret_cast<double2*>(out);
     for (int e = threadIdx.x; e < ROWS * H; e += NT) {
         const int rr = e / H, m = e - rr * H;
-        const int64_t row = r0 + rr;
-        if (row >= rows) continue;
+        const int64_t row = rdst[rr], mir = rmir[rr];
+        if (row < 0) continue;
         double2 v = c_scale(buf[rr * PS + m], 2.0);
+        // positions -2m and -2m - 1 (modulo N) of the row
+        double2 w = make_double2(2.0 * buf[rr * PS + (m == 0 ? 0 : H - m)].x, 2.0 * buf[rr * PS + H - 1 - m].y);
         if (fl.mlast > 0) {
             // positions 2m, 2m + 1 hold lags p (p < N/2) or p - N
             const int p0 = 2 * m, p1 = 2 * m + 1;
-            if (p0 > fl.mlast - 1 && p0 < N - (fl.mlast - 1)) v.x = 0.0;
-            if (p1 > fl.mlast - 1 && p1 < N - (fl.mlast - 1)) v.y = 0.0;
+            if (p0 > fl.mlast - 1 && p0 < N - (fl.mlast - 1)) v.x = w.x = 0.0;
+            if (p1 > fl.mlast - 1 && p1 < N - (fl.mlast - 1)) v.y = w.y = 0.0;
         }
         dst[row * H + m] = v;
+        if (mir >= 0) dst[mir * H + m] = w;
     }
 }
 
@@ -370,11 +383,19 @@ struct Prune {
     int M[3];     // their count extents
     int nlive;    // entries of a live column that can be nonzero
     int nstore;   // entries of a column that are stored (0: all)
+    int nstore2;  // MODE 1: entries of a column of out2 that are stored (0: all)
+    uint32_t blocks = 0;   // tiles of the launch (set there)
 };
 
 // MODE 0: in-place transform.  MODE 1: forward transform stored in place
 // (the finished count spectrum C), then |C|^2 transformed forward again and
-// stored to out2.
+// stored to out2.  MODE 2: the last forward pass of |C|^2 along the leading
+// axes: that transform W of real values is Hermitian, W(-l) = conj W(l) over
+// the leading indices, so the launch visits the columns with l_0 in [0, P_0/2]
+// (na the axes before the pass's, M_0 = P_0/2 + 1) and stores those with 0 <
+// l_0 < P_0/2 at -l too.  The passes stream at the rate of a copy, so the bytes
+// they skip are the gain: d = 4, P = 64 (138 MB a spectrum), transform and
+// autocorrelation 309 us with every column transformed and read, 221 so.
 template <int N, int NT, int DIR, int MODE, int T, int RADIX>
 __global__ __launch_bounds__(NT) void k_c2c_strided(double2* __restrict__ buf, double2* __restrict__ out2,
                                                     int64_t inner, int64_t tiles,
@@ -384,20 +405,34 @@ __global__ __launch_bounds__(NT) void k_c2c_strided(double2* __restrict__ buf, d
     __shared__ double2 twl[N];
     TwiddleCopy<N, NT> twc;
     twc.fetch(tw);
+    // Narrow tiles share cache lines with their neighbours, and consecutive
+    // blocks run on different XCDs (of 8, each with its own L2): deal each XCD a
+    // contiguous range of tiles instead (d = 2, P = 512, 257 single columns: 10.3
+    // -> 7.6 us; d = 3, P = 256, 8 columns: whole transform 222 -> 187; tiles of 16
+    // columns gain nothing).  The grid is then a multiple
+    // of 8.
+    uint32_t bid = blockIdx.x;
+    if constexpr (T <= 8) {
+        bid = (bid % 8) * (gridDim.x / 8) + bid / 8;
+        if (bid >= pr.blocks) return;
+    }
     // block indices and outer indices are below 2^32: 32-bit divisions
-    const uint32_t ol = blockIdx.x / (uint32_t)tiles;
-    uint32_t o = ol;
+    const uint32_t ol = bid / (uint32_t)tiles;
+    uint32_t o = ol, om = 0;   // om: -o
+    bool mirror = false;
     if (pr.na > 0) {   // live column ol (extents M) -> its outer index in the buffer (extents P)
         uint32_t rem = ol, mul = 1;
         o = 0;
         for (int k = pr.na - 1; k >= 0; --k) {
-            const uint32_t m = (uint32_t)pr.M[k];
-            o += (rem % m) * mul;
+            const uint32_t m = (uint32_t)pr.M[k], p = (uint32_t)pr.P[k], i = rem % m;
+            o += i * mul;
+            om += (i == 0 ? 0u : p - i) * mul;
             rem /= m;
-            mul *= (uint32_t)pr.P[k];
+            mul *= p;
+            if (k == 0) mirror = i > 0 && i < p / 2;
         }
     }
-    const int64_t i0 = (int64_t)(blockIdx.x - ol * (uint32_t)tiles) * T;
+    const int64_t i0 = (int64_t)(bid - ol * (uint32_t)tiles) * T;
     double2* base = buf + (int64_t)o * N * inner + i0;
     {
         constexpr int PE = (N * T + NT - 1) / NT;   // unrolled: the loads in flight together
@@ -418,6 +453,15 @@ __global__ __launch_bounds__(NT) void k_c2c_strided(double2* __restrict__ buf, d
         const int t = e % T, p = e / T;
         if (i0 + t < inner && p < pr.nstore) base[(int64_t)p * inner + t] = lds[t * PS + p];
     }
+    if constexpr (MODE == 2) {
+        if (mirror) {
+            double2* b2 = buf + (int64_t)om * N * inner + i0;
+            for (int e = threadIdx.x; e < N * T; e += NT) {
+                const int t = e % T, p = e / T;
+                if (i0 + t < inner) b2[(int64_t)p * inner + t] = c_conj(lds[t * PS + (p == 0 ? 0 : N - p)]);
+            }
+        }
+    }
     if constexpr (MODE == 1) {
         for (int e = threadIdx.x; e < N * T; e += NT) {
             const int t = e % T, p = e / T;
@@ -429,7 +473,7 @@ __global__ __launch_bounds__(NT) void k_c2c_strided(double2* __restrict__ buf, d
         double2* b2 = out2 + (int64_t)o * N * inner + i0;
         for (int e = threadIdx.x; e < N * T; e += NT) {
             const int t = e % T, p = e / T;
-            if (i0 + t < inner) b2[(int64_t)p * inner + t] = lds[t * PS + p];
+            if (i0 + t < inner && p < pr.nstore2) b2[(int64_t)p * inner + t] = lds[t * PS + p];
         }
     }
 }
@@ -548,11 +592,15 @@ static hipError_t run_c2r_last(const double2* in, double* out, int64_t rows, con
 
 template <int N, int NT, int T, int RADIX>
 static void launch_c2c_t(double2* buf, double2* out2, int64_t outer, int64_t inner, int dir, int mode,
-                         const double2* tw, hipStream_t s, const Prune& pr) {
-    const int64_t tiles = (inner + T - 1) / T;
-    const dim3 grid((unsigned)(outer * tiles));
+                         const double2* tw, hipStream_t s, Prune pr) {
+    const int64_t tiles = (inner + T - 1) / T, blocks = outer * tiles;
+    pr.blocks = (uint32_t)blocks;
+    const dim3 grid((unsigned)(T <= 8 ? (blocks + 7) / 8 * 8 : blocks));
     if (mode == 1)
         hipLaunchKernelGGL((k_c2c_strided<N, NT, -1, 1, T, RADIX>), grid, dim3(NT), 0, s, buf, out2, inner, tiles,
+                           tw, pr);
+    else if (mode == 2)
+        hipLaunchKernelGGL((k_c2c_strided<N, NT, -1, 2, T, RADIX>), grid, dim3(NT), 0, s, buf, out2, inner, tiles,
                            tw, pr);
     else if (dir < 0)
         hipLaunchKernelGGL((k_c2c_strided<N, NT, -1, 0, T, RADIX>), grid, dim3(NT), 0, s, buf, out2, inner, tiles,
@@ -589,6 +637,17 @@ static void run_c2c_r(double2* buf, double2* out2, int64_t outer, int64_t inner,
                 launch_c2c_t<N, 256, 17, RADIX>(buf, out2, outer, inner, dir, mode, tw, s, pr);
                 return;
             }
+        }
+    }
+    // Four columns (half a cache line) where the full tiles make few blocks and
+    // these enough: d = 3, P = 128, passes over 64 or 65 rows of 65 columns, us,
+    // single columns -> four: 14.7 -> 6.3 and 28.2 -> 9.1; axis 0 (520 full
+    // tiles), transform and autocorrelation 57.2 -> 54.6.
+    if constexpr (N >= 64 && T > 4) {
+        if (fs != FS_NARROW && fs != FS_HALF && fs != FS_DEEP && fs != FS_WIDE &&
+            outer * ((inner + T - 1) / T) < 2 * kMinBlocks && outer * ((inner + 3) / 4) >= kMinBlocks) {
+            launch_c2c_t<N, 256, 4, RADIX>(buf, out2, outer, inner, dir, mode, tw, s, pr);
+            return;
         }
     }
     if constexpr (TS < T) {
@@ -654,9 +713,10 @@ static hipError_t c2r_last(const double2* in, double* out, int64_t rows, int N, 
 #undef CALL
 }
 static hipError_t c2c(double2* buf, double2* out2, int64_t outer, int N, int64_t inner, int dir, int mode,
-                      const double2* tw, hipStream_t s, int fs = FS_AUTO, Prune pr = Prune{0, {1, 1, 1}, {1, 1, 1}, 0, 0}) {
+                      const double2* tw, hipStream_t s, int fs = FS_AUTO, Prune pr = Prune{0, {1, 1, 1}, {1, 1, 1}, 0, 0, 0}) {
     if (pr.nlive <= 0 || pr.nlive > N) pr.nlive = N;
     if (pr.nstore <= 0 || pr.nstore > N) pr.nstore = N;
+    if (pr.nstore2 <= 0 || pr.nstore2 > N) pr.nstore2 = N;
     if (pr.na > 0) {   // the launch covers the live columns only
         outer = 1;
         for (int k = 0; k < pr.na; ++k) outer *= pr.M[k];
@@ -715,7 +775,7 @@ hipError_t fft_slices_inverse(double2* buf, const kdefft_grid& g, int64_t slices
     for (int ax = 1; ax + 1 < g.d && e == hipSuccess; ++ax) {
         int64_t inner = g.P[g.d - 1] / 2 + 1;
         for (int k = ax + 1; k + 1 < g.d; ++k) inner *= g.P[k];
-        Prune pr{ax, {(int)slices, 1, 1}, {(int)slices, 1, 1}, 0, g.M[ax]};
+        Prune pr{ax, {(int)slices, 1, 1}, {(int)slices, 1, 1}, 0, g.M[ax], 0};
         for (int k = 1; k < ax; ++k) {
             pr.P[k] = g.P[k];
             pr.M[k] = g.M[k];
@@ -749,7 +809,7 @@ static hipError_t counts_forward(const int64_t* src, int slots, int64_t* counts,
     for (int ax = g.d - 2; ax >= 1 && e == hipSuccess; --ax) {
         int64_t outer, inner;
         axis_shape(g, ax, &outer, &inner);
-        Prune pr{ax, {1, 1, 1}, {1, 1, 1}, g.M[ax], 0};
+        Prune pr{ax, {1, 1, 1}, {1, 1, 1}, g.M[ax], 0, 0};
         for (int k = 0; k < ax; ++k) {
             pr.P[k] = g.P[k];
             pr.M[k] = g.M[k];
@@ -760,7 +820,7 @@ static hipError_t counts_forward(const int64_t* src, int slots, int64_t* counts,
     int64_t outer, inner;
     axis_shape(g, 0, &outer, &inner);
     return c2c(spec, wmix, outer, g.P[0], inner, -1, wmix ? 1 : 0, tw, s, fs,
-               Prune{0, {1, 1, 1}, {1, 1, 1}, g.M[0], 0});
+               Prune{0, {1, 1, 1}, {1, 1, 1}, g.M[0], 0, g.d > 2 ? g.P[0] / 2 + 1 : 0});
 }
 
 hipError_t fft_counts_nd(const int64_t* src, int slots, int64_t* counts, double2* spec, const kdefft_grid& g,
@@ -782,7 +842,18 @@ hipError_t fft_prepare_nd(const int64_t* src, int slots, int64_t* counts, double
     for (int ax = 1; ax + 1 < g.d && e == hipSuccess; ++ax) {
         int64_t outer, inner;
         axis_shape(g, ax, &outer, &inner);
-        e = c2c(wmix, nullptr, outer, g.P[ax], inner, -1, 0, tw, s, fs);
+        // l_0 in [0, P_0/2]; the last of these passes fills in the rest
+        const int h0 = g.P[0] / 2 + 1;
+        Prune pr{0, {1, 1, 1}, {1, 1, 1}, 0, 0, 0};
+        const bool last = ax + 2 == g.d;
+        if (last) {
+            pr.na = ax;
+            for (int k = 0; k < ax; ++k) {
+                pr.P[k] = g.P[k];
+                pr.M[k] = k == 0 ? h0 : g.P[k];
+            }
+        }
+        e = c2c(wmix, nullptr, outer / g.P[0] * h0, g.P[ax], inner, -1, last ? 2 : 0, tw, s, fs, pr);
     }
     return e;
 }
@@ -794,15 +865,17 @@ hipError_t fft_autocorr_nd(const double2* wmix, double* alag, const kdefft_grid&
     hipError_t e = twiddles(&tw);
     if (e != hipSuccess) return e;
     // inverting |C|^2 along the leading axes = the forward transform (wmix)
-    // read at negated leading indices; then the last-axis inverse.  Lags with
-    // |l| >= M along any axis are zero in exact arithmetic (the counts occupy
-    // [0, M)) and are stored as exact zeros.
+    // read at negated leading indices; then the last-axis inverse.  The result
+    // is even, so the rows l_0 in [0, P_0/2] give it all.  Lags with |l| >= M
+    // along any axis are zero in exact arithmetic (the counts occupy [0, M))
+    // and are stored as exact zeros.
     RowFlip fl{g.d > 1 ? 1 : 0, g.d - 1, {1, 1, 1}, g.M[g.d - 1], {1, 1, 1}};
     for (int k = 0; k + 1 < g.d; ++k) {
         fl.P[k] = g.P[k];
         fl.M[k] = g.M[k];
     }
-    return c2r_last(wmix, alag, lead_count(g), g.P[g.d - 1], tw, s, fl, fs);
+    const int64_t rows = g.d > 1 ? lead_count(g) / g.P[0] * (g.P[0] / 2 + 1) : 1;
+    return c2r_last(wmix, alag, rows, g.P[g.d - 1], tw, s, fl, fs);
 }
 
 }  // namespace kdefft
