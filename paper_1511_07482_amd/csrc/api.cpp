@@ -825,22 +825,31 @@ int kdefft_grid_auto(const double* X, int64_t n, int d, const double* G_host, co
     for (int k = 0; k < d; ++k) { probe.M[k] = 2; probe.P[k] = 4; probe.delta[k] = 1.0; }
     Arena a(ws, ws_bytes, false);
     const int64_t nb = std::min<int64_t>(std::max<int64_t>((n + 255) / 256, 1), 1024);
-    double* partial = a.take<double>(nb * 8);
-    double* dout = a.take<double>(8);
+    a.take<double>(nb * 8);   // the documented size; the bounds themselves need none of it
+    a.take<double>(8);
     if (!ws) return fail(KDEFFT_E_ARG, "workspace is NULL");
     rc = check_ws(a, ws_bytes);
     if (rc) return rc;
     hipStream_t s = S(stream);
-    HIPCHK(launch_bounds(X, n, d, partial, (int)nb, dout, s), "bounds");
-    // 8 doubles of pinned host memory per thread, allocated once, so the
-    // readback is a direct DMA rather than a staged pageable copy
+    // the kernel's per-block bounds go straight to pinned host memory (one
+    // buffer per thread, allocated once) and are reduced here
+    constexpr int NB = 256;
     static thread_local double* pinned = nullptr;
-    if (!pinned) HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&pinned), 8 * sizeof(double), hipHostMallocDefault),
+    if (!pinned) HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&pinned), NB * 8 * sizeof(double), hipHostMallocDefault),
                         "pinned readback buffer");
-    HIPCHK(hipMemcpyAsync(pinned, dout, 8 * sizeof(double), hipMemcpyDeviceToHost, s), "bounds readback");
+    const int nblk = (int)std::min<int64_t>(nb, NB);
+    HIPCHK(launch_bounds_partial(X, n, d, pinned, nblk, s, nullptr, 0), "bounds");
     HIPCHK(hipStreamSynchronize(s), "bounds sync");
     double host[8];
-    for (int k = 0; k < 8; ++k) host[k] = pinned[k];
+    for (int k = 0; k < 4; ++k) {
+        host[k] = std::numeric_limits<double>::infinity();
+        host[4 + k] = -host[k];
+    }
+    for (int j = 0; j < nblk; ++j)
+        for (int k = 0; k < d; ++k) {
+            host[k] = std::fmin(host[k], pinned[j * 8 + k]);
+            host[4 + k] = std::fmax(host[4 + k], pinned[j * 8 + 4 + k]);
+        }
     double lo[4], hi[4];
     for (int k = 0; k < d; ++k) {
         const double sd = std::sqrt(G_host[k * d + k]);

@@ -10,7 +10,9 @@ namespace kdefft {
 // ------------------------------------------------------------------ bounds
 // Per-block min/max of each column of X [n, D] into partial[block * 8 + k]
 // (min) and partial[block * 8 + 4 + k] (max); min/max are exact, so the
-// result does not depend on the reduction order.  Also clears zero16 16-byte
+// result does not depend on the reduction order.  partial may be pinned host
+// memory (the host plans the grid: it reduces the partials itself, which saves
+// a reducing launch and a copy before the wait).  Also clears zero16 16-byte
 // words at zero_ptr (the binning's scratch), so the preparation needs no
 // separate clearing launch.
 template <int D>
@@ -67,17 +69,6 @@ __global__ __launch_bounds__(256) void k_bounds(const double* __restrict__ X, in
     }
 }
 
-// Reduction of the per-block partials into out (min[4], max[4]); one block.
-__global__ __launch_bounds__(256) void k_bounds_final(const double* __restrict__ partial, int nblk, int d,
-                                                      double* __restrict__ out) {
-    __shared__ double scratch[32], red[8];
-    reduce_bounds(partial, nblk, d, scratch, red);
-    if (threadIdx.x < (unsigned)d) {
-        out[threadIdx.x] = red[threadIdx.x];
-        out[4 + threadIdx.x] = red[4 + threadIdx.x];
-    }
-}
-
 hipError_t launch_bounds_partial(const double* X, int64_t n, int d, double* partial, int nblk, hipStream_t s,
                                  void* zero_ptr, size_t zero_bytes, int32_t* n_out, double* scal) {
     if (zero_bytes % 16 || (reinterpret_cast<uintptr_t>(zero_ptr) & 15)) return hipErrorInvalidValue;
@@ -90,14 +81,6 @@ hipError_t launch_bounds_partial(const double* X, int64_t n, int d, double* part
         case 4: hipLaunchKernelGGL(k_bounds<4>, dim3(nblk), dim3(256), 0, s, X, n, partial, z, z16, n_out, scal); break;
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_bounds(const double* X, int64_t n, int d, double* partial, int nblk, double* out,
-                         hipStream_t s) {
-    hipError_t e = launch_bounds_partial(X, n, d, partial, nblk, s, nullptr, 0, nullptr, nullptr);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bounds_final, dim3(1), dim3(256), 0, s, partial, nblk, d, out);
     return hipGetLastError();
 }
 

@@ -105,12 +105,8 @@ int ng_of(int kind, int d, int r);   // number of kernel grids of a family
 // All return hipSuccess or the first HIP error; they only enqueue work.
 hipError_t twiddles(const double2** out);  // per-device table e^{-2 pi i m/4096} + N-point subsets
 
-// Data bounds: per-block partials (nblk blocks; 8 doubles each) then their
-// reduction into out (min[4], max[4]).
-hipError_t launch_bounds(const double* X, int64_t n, int d, double* partial, int nblk,
-                         double* out, hipStream_t s);
-// The per-block partials only, clearing zero_bytes (a multiple of 16, 16-byte
-// aligned) at zero_ptr on the way.
+// Data bounds: per-block partials (nblk blocks; 8 doubles each, min[4], max[4]),
+// clearing zero_bytes (a multiple of 16, 16-byte aligned) at zero_ptr on the way.
 hipError_t launch_bounds_partial(const double* X, int64_t n, int d, double* partial, int nblk, hipStream_t s,
                                  void* zero_ptr, size_t zero_bytes, int32_t* n_out = nullptr, double* scal = nullptr);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
