@@ -80,7 +80,10 @@ hipError_t twiddles(const double2** out) {
 //  * CountSrc: the R2C input row is read straight from the int64 grid counts,
 //    or gathered from the binning's corner slots (c = count 2^-40 at [0, M)^d
 //    of the circular layout, zero elsewhere), so the zero-padded real array is
-//    never materialised.
+//    never materialised.  The launch covers the rows inside the counts' box:
+//    row r is the counts' row r (leading indices over M), stored at its place in
+//    the padded grid; the padding's zero rows are not written (the next pass
+//    never reads them).
 //  * RowFlip: the C2R pass writes input row l (l_0 in [0, P_0/2] only) to
 //    output row -l, and, as the real output f is even, f(l) = f(-l), that row
 //    reversed to output row l.
@@ -92,47 +95,31 @@ struct CountSrc {
     int slots;              // counts holds the binning's corner slots, gathered here
     int64_t* sum_out;       // the gathered counts, written when slots is set
     int32_t* reach;         // if set, receives M - 1 per axis (block 0)
-    int prune;              // only the rows inside the counts' box: row r of the launch is the counts'
-                            // row r (leading indices over M), stored at its place in the padded grid;
-                            // the padding's zero rows are not written (the next pass never reads them)
 };
 
-// Count of cell i = base + p (base: the cell of the row's first position, p
-// the last-axis index; bit j - 1 of lmask: the row's index along axis d-1-j
-// is >= 1) gathered from the corner slots of the last NSA axes: slot s of the
-// record of cell i - e(s), e(s) = the sum over the set bits j of s of the
-// stride of axis d-1-j, for the slots whose lower cell exists.  Exact
-// (unsigned 64-bit sums).
+// The corner slots' part of the count at position p of a row (base: the cell of
+// its first position; bit j - 1 of lmask: the row's index along axis d-1-j is
+// >= 1).  The count of cell i is the sum over s of slot s of the record of cell
+// i - e(s), e(s) = the sum over the set bits j of s of the stride of axis d-1-j,
+// for the slots whose lower cell exists.  Slots 2t and 2t + 1 of a record are
+// 16 bytes: x collects the even slots, which belong to position p, y the odd
+// ones, which belong to p + 1.  Exact (unsigned 64-bit sums).
 template <int NSA>
-__device__ __forceinline__ uint64_t gather_slots(const int64_t* __restrict__ sl, int64_t i, int p, int lmask,
-                                                 const int* M, int d) {
-    constexpr int NS = 1 << NSA;
+__device__ __forceinline__ ulonglong2 gather_slots(const int64_t* __restrict__ slots, int64_t base, int p, int lmask,
+                                                   const int* M, int d) {
+    constexpr int NP = 1 << (NSA - 1);
+    const ulonglong2* rec = reinterpret_cast<const ulonglong2*>(slots);
     const int64_t st1 = NSA > 1 ? M[d - 1] : 0;
     const int64_t st2 = NSA > 2 ? st1 * M[d - 2] : 0;
-    uint64_t t = 0;
+    ulonglong2 sum = make_ulonglong2(0, 0);
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const bool ok = (!(s & 1) || p >= 1) && (!(s & 2) || (lmask & 1)) && (!(s & 4) || (lmask & 2));
-        const int64_t off = (s & 1 ? 1 : 0) + (s & 2 ? st1 : 0) + (s & 4 ? st2 : 0);
-        if (ok) t += static_cast<uint64_t>(sl[(i - off) * NS + s]);
+    for (int t = 0; t < NP; ++t) {
+        if ((t & 1 && !(lmask & 1)) || (t & 2 && !(lmask & 2))) continue;
+        const ulonglong2 v = rec[(base + p - (t & 1 ? st1 : 0) - (t & 2 ? st2 : 0)) * NP + t];
+        sum.x += v.x;
+        sum.y += v.y;
     }
-    return t;
-}
-
-// Count of cell base + p: read directly, or gathered from the corner slots
-// (then also stored to sum_out).
-__device__ __forceinline__ int64_t load_count(const CountSrc& cs, int64_t base, int p, int lmask) {
-    const int64_t i = base + p;
-    if (!cs.slots) return cs.counts[i];
-    uint64_t t;
-    if (cs.d == 1)
-        t = gather_slots<1>(cs.counts, i, p, lmask, cs.M, cs.d);
-    else if (cs.d == 2)
-        t = gather_slots<2>(cs.counts, i, p, lmask, cs.M, cs.d);
-    else
-        t = gather_slots<3>(cs.counts, i, p, lmask, cs.M, cs.d);
-    cs.sum_out[i] = static_cast<int64_t>(t);
-    return static_cast<int64_t>(t);
+    return sum;
 }
 
 struct RowFlip {
@@ -181,60 +168,91 @@ __global__ __launch_bounds__(NT) void k_r2c_last(const double* __restrict__ in, 
     if (cs.counts) {
         const double quantum = 9.094947017729282379150390625e-13;  // 2^-40
         const int Ml = cs.M[cs.d - 1];
-        // offset of each row's counts (-1: a zero row of the padding), decoded
-        // once per row
+        // offset of each row's counts (-1: past the end), decoded once per row
         __shared__ int64_t rbase[ROWS];
         __shared__ int rmask[ROWS];   // bit 0: the row's index along axis d-2 is >= 1; bit 1: along d-3
         for (int rr = threadIdx.x; rr < ROWS; rr += NT) {
             const int64_t row = r0 + rr;
-            int64_t base = -1;
+            uint32_t rem = (uint32_t)row;
             int mask = 0;
-            if (row < rows) {
-                // the row's leading indices: digits over M (pruned launches
-                // run over the counts' rows) or over P (others)
-                uint32_t rem = (uint32_t)row, cf = 0, mul = 1;
-                bool ok = true;
-                for (int k = cs.d - 2; k >= 0; --k) {
-                    const uint32_t p = (uint32_t)(cs.prune ? cs.M[k] : cs.P[k]), i = rem % p;
-                    rem /= p;
-                    ok = ok && i < (uint32_t)cs.M[k];
-                    if (k == cs.d - 2 && i >= 1) mask |= 1;
-                    if (k == cs.d - 3 && i >= 1) mask |= 2;
-                    cf += i * mul;
-                    mul *= (uint32_t)cs.M[k];
-                }
-                if (ok) base = (int64_t)cf * Ml;
+            for (int k = cs.d - 2; k >= 0 && k >= cs.d - 3; --k) {
+                const uint32_t m = (uint32_t)cs.M[k];
+                if (rem % m >= 1) mask |= k == cs.d - 2 ? 1 : 2;
+                rem /= m;
             }
-            rbase[rr] = base;
+            rbase[rr] = row < rows ? row * Ml : -1;
             rmask[rr] = mask;
         }
         __syncthreads();
-        // a block of zero rows only (the padding): its spectrum is zero
-        bool any = false;
-        for (int rr = 0; rr < ROWS; ++rr) any = any || rbase[rr] >= 0;
-        if (!any) {
-            for (int e = threadIdx.x; e < ROWS * Q; e += NT) {
-                const int64_t row = r0 + e / Q;
-                if (row < rows) out[row * Q + (e % Q)] = make_double2(0.0, 0.0);
-            }
-            return;
-        }
-        // a thread's elements in an unrolled loop, so that their loads are in
-        // flight together (these passes are bound by load latency)
         constexpr int PE = (ROWS * H + NT - 1) / NT;
+        double2 v[PE];
+        if (cs.slots) {
+            // Each 16-byte piece is read once, by one lane; the odd slots reach
+            // their cell through LDS.  Reading the 2^d slots of each cell, 8 bytes
+            // each, was bound by the lines per load instruction: d = 4, M = 32
+            // 42 -> 30 us, d = 3, M = 64 14.7 -> 9.6 us.
+            uint64_t* part = reinterpret_cast<uint64_t*>(buf);   // rows of 2 PS words
+            const int lw = Ml <= H ? ilog2c(H) : ilog2c(N);      // lanes per row: the positions that can hold counts
+            uint64_t odd[2 * PE];
+#pragma unroll
+            for (int u = 0; u < 2 * PE; ++u) {
+                odd[u] = 0;
+                const int e = threadIdx.x + u * NT, rr = e >> lw, p = e - (rr << lw);
+                if (rr < ROWS && p < Ml && rbase[rr] >= 0) {
+                    const int64_t base = rbase[rr];
+                    const int lm = rmask[rr];
+                    const ulonglong2 t = cs.d == 1   ? gather_slots<1>(cs.counts, base, p, lm, cs.M, cs.d)
+                                         : cs.d == 2 ? gather_slots<2>(cs.counts, base, p, lm, cs.M, cs.d)
+                                                     : gather_slots<3>(cs.counts, base, p, lm, cs.M, cs.d);
+                    part[rr * 2 * PS + p] = t.x;
+                    odd[u] = t.y;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 2 * PE; ++u) {
+                const int e = threadIdx.x + u * NT, rr = e >> lw, p = e - (rr << lw);
+                if (rr < ROWS && p + 1 < Ml && rbase[rr] >= 0) part[rr * 2 * PS + p + 1] += odd[u];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < PE; ++u) {
+                const int e = threadIdx.x + u * NT;
+                v[u] = make_double2(0.0, 0.0);
+                if ((ROWS * H) % NT == 0 || e < ROWS * H) {
+                    const int rr = e / H, p = 2 * (e - rr * H);
+                    const int64_t base = rbase[rr];
+                    const uint64_t* c = part + rr * 2 * PS + p;
+                    if (base >= 0 && p < Ml) {
+                        cs.sum_out[base + p] = (int64_t)c[0];
+                        v[u].x = (double)(int64_t)c[0] * quantum;
+                    }
+                    if (base >= 0 && p + 1 < Ml) {
+                        cs.sum_out[base + p + 1] = (int64_t)c[1];
+                        v[u].y = (double)(int64_t)c[1] * quantum;
+                    }
+                }
+            }
+            __syncthreads();
+        } else {
+#pragma unroll
+            for (int u = 0; u < PE; ++u) {
+                const int e = threadIdx.x + u * NT;
+                v[u] = make_double2(0.0, 0.0);
+                if ((ROWS * H) % NT == 0 || e < ROWS * H) {
+                    const int rr = e / H, p = 2 * (e - rr * H);
+                    const int64_t base = rbase[rr];
+                    if (base >= 0 && p < Ml) v[u].x = (double)cs.counts[base + p] * quantum;
+                    if (base >= 0 && p + 1 < Ml) v[u].y = (double)cs.counts[base + p + 1] * quantum;
+                }
+            }
+        }
 #pragma unroll
         for (int u = 0; u < PE; ++u) {
             const int e = threadIdx.x + u * NT;
             if ((ROWS * H) % NT == 0 || e < ROWS * H) {
                 const int rr = e / H, m = e - rr * H;
-                const int64_t base = rbase[rr];
-                double2 v = make_double2(0.0, 0.0);
-                if (base >= 0) {
-                    const int p0 = 2 * m, p1 = 2 * m + 1, lm = rmask[rr];
-                    if (p0 < Ml) v.x = (double)load_count(cs, base, p0, lm) * quantum;
-                    if (p1 < Ml) v.y = (double)load_count(cs, base, p1, lm) * quantum;
-                }
-                buf[rr * PS + m] = v;
+                buf[rr * PS + m] = v[u];
             }
         }
     } else {
@@ -255,7 +273,7 @@ __global__ __launch_bounds__(NT) void k_r2c_last(const double* __restrict__ in, 
     __shared__ int64_t rout[ROWS];   // output row of each row: its place in the padded grid when pruned
     for (int rr = threadIdx.x; rr < ROWS; rr += NT) {
         int64_t row = r0 + rr;
-        if (cs.counts && cs.prune) {
+        if (cs.counts) {
             uint32_t rem = (uint32_t)row, o = 0, mul = 1;
             for (int k = cs.d - 2; k >= 0; --k) {
                 const uint32_t m = (uint32_t)cs.M[k];
@@ -698,7 +716,7 @@ static hipError_t run_c2c(double2* buf, double2* out2, int64_t outer, int64_t in
     }
 
 static hipError_t r2c_last(const double* in, double2* out, int64_t rows, int N, const double2* tw, hipStream_t s,
-                           CountSrc cs = CountSrc{nullptr, 0, {0, 0, 0, 0}, {0, 0, 0, 0}, 0, nullptr, nullptr, 0},
+                           CountSrc cs = CountSrc{nullptr, 0, {0, 0, 0, 0}, {0, 0, 0, 0}, 0, nullptr, nullptr},
                            int fs = FS_AUTO) {
 #define CALL(NN) run_r2c_last<NN>(in, out, rows, tw, s, cs, fs)
     if (N < 4) return hipErrorInvalidValue;
@@ -792,7 +810,7 @@ static hipError_t counts_forward(const int64_t* src, int slots, int64_t* counts,
     const double2* tw;
     hipError_t e = twiddles(&tw);
     if (e != hipSuccess) return e;
-    CountSrc cs{src, g.d, {1, 1, 1, 1}, {1, 1, 1, 1}, slots ? 1 : 0, counts, reach, 1};
+    CountSrc cs{src, g.d, {1, 1, 1, 1}, {1, 1, 1, 1}, slots ? 1 : 0, counts, reach};
     for (int k = 0; k < g.d; ++k) {
         cs.M[k] = g.M[k];
         cs.P[k] = g.P[k];

@@ -42,7 +42,10 @@ def test_band_counts_exact(d, M, n):
 
 
 @pytest.mark.parametrize("d,M,n", [(1, [64], 10000), (2, [143, 143], 61400), (3, [27, 27, 27], 20001),
-                                   (4, [8, 8, 8, 9], 10000)])
+                                   (4, [8, 8, 8, 9], 10000),
+                                   # through the corner slots: short, odd and full rows
+                                   (1, [65], 500), (2, [130, 3], 700), (2, [3, 256], 9000), (3, [5, 33, 64], 900),
+                                   (4, [3, 7, 4, 31], 900), (4, [4, 5, 6, 32], 2000)])
 def test_band_preparation(d, M, n):
     """The preparation on the device's own grid, eager and replayed on new data."""
     import paper_1511_07482_amd as kf
