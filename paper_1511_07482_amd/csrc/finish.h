@@ -73,36 +73,50 @@ __device__ static double chunk_sum(const double* __restrict__ partial, int64_t h
     return wave_sum(s);
 }
 
-// Sums of the first NG grids of the count items from item `first` (partial
-// sums of ng values per item; a grid from ng on gives 0), by one wavefront in
-// the same fixed order as chunk_sum; the grids' loads and trees in flight
-// together.
+// Sums over candidate h's count items (partial sums of ng values per item) of
+// its first NG grids (a grid from ng on gives 0) into T[0, NG), and of the first
+// grid of candidate c (if c >= 0) into T[NG], by one wavefront in the same fixed
+// order as chunk_sum; all loads and trees are in flight together.
 template <int NG>
-__device__ __forceinline__ static void item_sums(const double* __restrict__ partial, int64_t first, int64_t count,
-                                                 int ng, double* T) {
+__device__ __forceinline__ static void item_sums(const double* __restrict__ partial, int64_t h, int64_t c,
+                                                 int64_t count, int ng, double* T) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int g = 0; g < NG; ++g) T[g] = 0.0;
-    for (int64_t c = lane; c < count; c += 64) {
-        const double* row = partial + (first + c) * ng;
+    for (int g = 0; g <= NG; ++g) T[g] = 0.0;
+    const double* own = partial + h * count * ng;
+    const double* other = c >= 0 ? partial + c * count * ng : own;
+    for (int64_t i = lane; i < count; i += 64) {
 #pragma unroll
-        for (int g = 0; g < NG; ++g) T[g] += row[g < ng ? g : 0];
+        for (int g = 0; g < NG; ++g) T[g] += own[i * ng + (g < ng ? g : 0)];
+        T[NG] += other[i * ng];
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1)
 #pragma unroll
-        for (int g = 0; g < NG; ++g) T[g] += __shfl_xor(T[g], off, 64);
+        for (int g = 0; g <= NG; ++g) T[g] += __shfl_xor(T[g], off, 64);
 #pragma unroll
-    for (int g = 0; g < NG; ++g) T[g] = g < ng ? T[g] : 0.0;
+    for (int g = 0; g <= NG; ++g) T[g] = (g == NG ? c >= 0 : g < ng) ? T[g] : 0.0;
 }
 
+// Slots 0..63 of a parameter block, one per lane (loaded with the sums' loads,
+// not after them).
+struct ParamLanes {
+    double v;
+    __device__ __forceinline__ explicit ParamLanes(const double* __restrict__ p) : v(p[threadIdx.x & 63]) {}
+    __device__ __forceinline__ double operator[](int slot) const {   // wavefront-uniform
+        const long long b = __double_as_longlong(v);
+        const int lo = __builtin_amdgcn_readlane((int)b, slot), hi = __builtin_amdgcn_readlane((int)(b >> 32), slot);
+        return __longlong_as_double((long long)((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo));
+    }
+};
+
 // Criterion assembly for a candidate (p: its parameter block, T: its sums over
-// the lags).  kind: FUN_SCV_OBJ or FUN_ETA* (objective only), FUN_SCV_OBJGRAD
+// the lags), by a whole wavefront.  kind: FUN_SCV_OBJ or FUN_ETA* (objective only), FUN_SCV_OBJGRAD
 // (objective + gradient), FUN_SCV_GRAD (adjoint: gradient scaled by gscale).
 // cst is the constant term added to the objective (the SCV phi_{2G} sum, else
 // 0).  Returns the objective; gv: the gradient in vech(L) order, if kind has one.
 template <int D>
-__device__ __forceinline__ static double crit_finish(int kind, const double* T, const double* __restrict__ p,
+__device__ __forceinline__ static double crit_finish(int kind, const double* T, const ParamLanes& p,
                                                      double cst, double gscale, bool want_grad, double* gv) {
     constexpr int d = D;
     const bool sing = p[S_SING] != 0.0;

@@ -45,7 +45,7 @@ __global__ __launch_bounds__(64) void k_min_step(int64_t B, MinStep a, const dou
     double g[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) g[i] = gt[b * Q + i];
-    min_step<Q>(a, b, ft[b], g, a.stt && a.stt[b] != 0);
+    min_step<Q>(a, b, MinState<Q>(a, b), ft[b], g);
 }
 
 __global__ void k_min_final(int64_t B, int q, const double* __restrict__ st, const int32_t* __restrict__ ist,

@@ -6,8 +6,7 @@
 // the state is read into registers at once (one round trip instead of a load
 // per use) and the extents are compile-time, so that nothing is indexed
 // through scratch memory.  d = 2, 4 candidates, us an update: 10.0 by itself
-// with a runtime q; 4.3 now together with the criterion's assembly, which takes
-// 4.5 alone.
+// with a runtime q; 3.9 now together with the criterion's assembly.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -47,39 +46,63 @@ __device__ __forceinline__ double min_amax(const double* a) {
     return m;
 }
 
-// Candidate b: value fb and gradient gb at its trial point; bad: the criterion
-// rejected the point.
+// State of candidate b in registers.
 template <int Q>
-__device__ __forceinline__ void min_step(const MinStep& a, int64_t b, double fb, const double* gb, bool bad) {
+struct MinState {
+    double x[Q], g[Q], p[Q], Hi[Q * Q], xt[Q], f, alpha;
+    int phase, back, acc, outcome, flat;
+    bool bad;   // the criterion rejected the trial point
+    __device__ __forceinline__ MinState(const MinStep& a, int64_t b) {
+        const double* st = a.st + b * min_sw(Q);
+        const int32_t* is = a.ist + MIN_IS * b;
+        phase = is[0];
+        back = is[1];
+        acc = is[2];
+        outcome = is[3];
+        flat = is[4];
+        bad = a.stt && a.stt[b] != 0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            x[i] = st[i];
+            g[i] = st[Q + i];
+            p[i] = st[2 * Q + i];
+            xt[i] = a.xt[b * Q + i];
+        }
+#pragma unroll
+        for (int i = 0; i < Q * Q; ++i) Hi[i] = st[3 * Q + i];
+        f = st[3 * Q + Q * Q];
+        alpha = st[3 * Q + Q * Q + 1];
+    }
+};
+
+// Candidate b: value fb and gradient gb at its trial point.
+template <int Q>
+__device__ __forceinline__ void min_step(const MinStep& a, int64_t b, const MinState<Q>& now, double fb,
+                                         const double* gb) {
     double* st = a.st + b * min_sw(Q);
     int32_t* is = a.ist + MIN_IS * b;
     double* xt_out = a.xt + b * Q;
-    double x[Q], g[Q], p[Q], Hi[Q * Q], xt[Q];
-    const int phase = is[0], back = is[1], acc = is[2], outcome = is[3], flat = is[4];
+    const auto &x = now.x, &g = now.g, &xt = now.xt;
+    const double f = now.f;
+    const int back = now.back, acc = now.acc, flat = now.flat;
+    double p[Q], Hi[Q * Q], alpha = now.alpha;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        x[i] = st[i];
-        g[i] = st[Q + i];
-        p[i] = st[2 * Q + i];
-        xt[i] = xt_out[i];
-    }
+    for (int i = 0; i < Q; ++i) p[i] = now.p[i];
 #pragma unroll
-    for (int i = 0; i < Q * Q; ++i) Hi[i] = st[3 * Q + i];
-    const double f = st[3 * Q + Q * Q];
-    double alpha = st[3 * Q + Q * Q + 1];
+    for (int i = 0; i < Q * Q; ++i) Hi[i] = now.Hi[i];
     const auto trial_at_x = [&](const double* at) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) xt_out[i] = at[i];
     };
-    if (outcome != KDEFFT_MIN_RUNNING) {
+    if (now.outcome != KDEFFT_MIN_RUNNING) {
         trial_at_x(x);
         return;
     }
-    bool ok = !bad && isfinite(fb);
+    bool ok = !now.bad && isfinite(fb);
 #pragma unroll
     for (int i = 0; i < Q; ++i) ok = ok && isfinite(gb[i]);
     const double gp = min_dot<Q>(g, p);
-    const bool start = phase == PH_START;
+    const bool start = now.phase == PH_START;
     if (!start && !(ok && fb <= f + C_ARMIJO * alpha * gp)) {
         // rejected: shorten the step to the minimiser of the quadratic through
         // f, the slope gp and the trial value, kept within [0.1, 0.5] of the step

@@ -289,9 +289,9 @@ hipError_t launch_ds_header(const HeaderArgs& h, hipStream_t s) {
 // Criterion assembly, one wavefront per candidate (see crit_finish); the
 // npseudo constant-term candidates after the real ones store their term in
 // their dataset's scalar block.  Work items of candidate c: c * nchunks + [0, nchunks).
-// STEP: the value and the gradient go straight to the minimiser's
-// update of the candidate (d = 2, 4 candidates, us per evaluation: assembly and
-// update as two launches 14.5, together 4.3).
+// STEP: the value and the gradient go straight to the minimiser's update of the
+// candidate (d = 2, 4 candidates, us per evaluation: assembly and update as two
+// launches 14.5, together 4.3, with every load issued before the sums 3.9).
 template <int D, bool STEP>
 __global__ __launch_bounds__(64) void k_scv_final(int kind, const double* __restrict__ partial, int64_t nchunks, int ng,
                                                   const double* __restrict__ prm, int64_t ncand, int npseudo,
@@ -302,28 +302,29 @@ __global__ __launch_bounds__(64) void k_scv_final(int kind, const double* __rest
     if (h >= ncand + npseudo) return;
     const double* p = prm + h * PRM;
     if (h >= ncand) {
-        double v[1];
-        item_sums<1>(partial, h * nchunks, nchunks, ng, v);
+        double v[2];
+        item_sums<1>(partial, h, -1, nchunks, ng, v);
         if (threadIdx.x == 0) static_cast<double*>(slot_ptr(p[S_FIN_SCAL]))[0] = v[0] * p[S_SCALE];
         return;
     }
-    double T[1 + Q], C[1] = {0.0};
-    double cscale = 0.0;
-    if (p[S_PSEUDO] >= 0.0) {
-        const int64_t c = (int64_t)p[S_PSEUDO];
-        item_sums<1>(partial, c * nchunks, nchunks, ng, C);
-        cscale = prm[c * PRM + S_SCALE];
-    }
-    item_sums<1 + Q>(partial, h * nchunks, nchunks, ng, T);
-    if (threadIdx.x != 0) return;
+    // with one dataset the constant term's place is known without reading the
+    // candidate's record
+    const int64_t c = npseudo == 0 ? -1 : npseudo == 1 ? ncand : (int64_t)p[S_PSEUDO];
+    const ParamLanes pl(p);
+    const double cscale = c >= 0 ? prm[c * PRM + S_SCALE] : 0.0;
     const bool grads = kind == FUN_SCV_OBJGRAD || kind == FUN_SCV_GRAD;
-    double gv[Q];
-    const double f = crit_finish<D>(kind, T, p, C[0] * cscale, kind == FUN_SCV_GRAD ? grad_out[h] : 1.0,
-                                    STEP || (grads && grad != nullptr), gv);
+    double T[2 + Q], gv[Q];
     if constexpr (STEP) {
-        min_step<Q>(step, h, f, gv, step.stt && step.stt[h] != 0);
+        const MinState<Q> now(step, h);
+        item_sums<1 + Q>(partial, h, c, nchunks, ng, T);
+        const double f = crit_finish<D>(kind, T, pl, T[1 + Q] * cscale, 1.0, true, gv);
+        if (threadIdx.x == 0) min_step<Q>(step, h, now, f, gv);
         return;
     }
+    item_sums<1 + Q>(partial, h, c, nchunks, ng, T);
+    const double f = crit_finish<D>(kind, T, pl, T[1 + Q] * cscale, kind == FUN_SCV_GRAD ? grad_out[h] : 1.0,
+                                    grads && grad != nullptr, gv);
+    if (threadIdx.x != 0) return;
     if (kind != FUN_SCV_GRAD) obj[h] = f;
     if (grads && grad != nullptr)
 #pragma unroll
