@@ -511,14 +511,13 @@ hipStream_t S(void* stream) { return static_cast<hipStream_t>(stream); }
 
 // Step 1 of the plain path: bin X, and the spectrum of the counts.
 int bin_and_transform(const double* X, int64_t n, const kdefft_grid& g, const PlainScratch& p, hipStream_t s) {
-    HIPCHK(launch_zero(p.n_out, sizeof(int32_t), s), "zero n_out");
     const bool bands = linbin_in_bands(n, g);
-    if (bands) {
-        HIPCHK(launch_zero(p.counts, sizes_of(g).prodM * sizeof(int64_t), s), "zero counts");
-        HIPCHK(launch_linbin_bands(X, n, g, p.counts, p.n_out, s), "linbin");
-    } else {
-        HIPCHK(launch_linbin_slots(X, n, g, p.slots, p.n_out, s, nullptr, false), "linbin");
-    }
+    const size_t cells = (size_t)sizes_of(g).prodM;
+    HIPCHK(launch_clear(bands ? p.counts : p.slots, (bands ? 1 : corner_slots(g.d)) * cells * sizeof(int64_t), p.n_out,
+                        s),
+           "clear");
+    HIPCHK(bands ? launch_linbin_bands(X, n, g, p.counts, p.n_out, s) : launch_linbin_slots(X, n, g, p.slots, p.n_out, s),
+           "linbin");
     HIPCHK(fft_counts_nd(bands ? p.counts : p.slots, bands ? 0 : 1, p.counts, p.C, g, s), "R2C counts");
     return KDEFFT_OK;
 }
@@ -564,19 +563,20 @@ int prepare_into(const double* X, int64_t n, const kdefft_grid& g, const double*
     h.nblk = nblk;
     h.g = g;
     for (int k = 0; k < g.d; ++k) h.pad[k] = pad ? pad[k] : 0.0;
-    h.n_out = L.n_out;
     h.scal = L.scal;
     const bool bands = linbin_in_bands(n, g);   // counts directly, without the corner slots
     // with partials: the grid and the header inside the binning launch (the
     // bounds launch cleared the counter, the scalar block and the target)
-    if (!partial) HIPCHK(launch_ds_header(h, s), "dataset header");
-    if (bands) {
-        if (!partial) HIPCHK(launch_zero(L.counts, sizes_of(g).prodM * sizeof(int64_t), s), "zero counts");
-        HIPCHK(launch_linbin_bands(X, n, g, L.counts, L.n_out, s, partial ? &h : nullptr), "linbin");
-    } else {
-        HIPCHK(launch_linbin_slots(X, n, g, slots, L.n_out, s, nullptr, partial != nullptr, partial ? &h : nullptr),
-               "linbin");
+    const HeaderArgs* hp = partial ? &h : nullptr;
+    if (!partial) {
+        const size_t cells = (size_t)sizes_of(g).prodM;
+        HIPCHK(launch_clear(bands ? L.counts : slots, (bands ? 1 : corner_slots(g.d)) * cells * sizeof(int64_t),
+                            L.n_out, s, &h),
+               "dataset header");
     }
+    HIPCHK(bands ? launch_linbin_bands(X, n, g, L.counts, L.n_out, s, hp)
+                 : launch_linbin_slots(X, n, g, slots, L.n_out, s, hp),
+           "linbin");
     const int fs = fft_sched_for(g);
     HIPCHK(fft_prepare_nd(bands ? L.counts : slots, bands ? 0 : 1, L.counts, L.spec, L.wmix, g, s, fs),
            "count transform");
@@ -870,8 +870,7 @@ int kdefft_linbin(const double* X, int64_t n, const kdefft_grid* g, int64_t* cou
     if (rc) return rc;
     if (!X || !counts) return fail(KDEFFT_E_ARG, "NULL X or counts");
     hipStream_t s = S(stream);
-    HIPCHK(launch_zero(counts, sizes_of(*g).prodM * sizeof(int64_t), s), "zero counts");
-    if (n_out_dev) HIPCHK(launch_zero(n_out_dev, sizeof(int32_t), s), "zero n_out");
+    HIPCHK(launch_clear(counts, sizes_of(*g).prodM * sizeof(int64_t), n_out_dev, s), "clear");
     if (linbin_in_bands(n, *g))
         HIPCHK(launch_linbin_bands(X, n, *g, counts, n_out_dev, s), "linbin");
     else

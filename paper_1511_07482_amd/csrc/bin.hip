@@ -84,21 +84,31 @@ hipError_t launch_bounds_partial(const double* X, int64_t n, int d, double* part
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ zero fill
-// Zero `bytes` bytes (a multiple of 4) with 32-bit vector stores.
-__global__ void k_zero(uint32_t* __restrict__ p, int64_t words) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < words;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0u;
+// ------------------------------------------------------------------ clearing
+// Everything that a binning adds to, in one launch: words 64-bit words at p,
+// the out-of-grid counter, and for a dataset on a given grid (hdr.rec set) its
+// record, counter and scalar block.  A launch of its own for the counter or the
+// record costs 2 us.
+__global__ __launch_bounds__(256) void k_clear(uint64_t* __restrict__ p, int64_t words, int32_t* __restrict__ n_out,
+                                               HeaderArgs hdr) {
+    for (int64_t i = blockIdx.x * 256LL + threadIdx.x; i < words; i += gridDim.x * 256LL) p[i] = 0u;
+    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    if (n_out) *n_out = 0;
+    if (hdr.rec) {
+        *hdr.rec = hdr.val;
+        for (int k = 0; k < 4; ++k) hdr.scal[k] = 0.0;
+    }
 }
 
-hipError_t launch_zero(void* p, size_t bytes, hipStream_t s) {
-    if (bytes % 4) return hipErrorInvalidValue;
-    const int64_t words = (int64_t)(bytes / 4);
-    if (words == 0) return hipSuccess;
+hipError_t launch_clear(void* p, size_t bytes, int32_t* n_out, hipStream_t s, const HeaderArgs* hdr) {
+    if (bytes % 8) return hipErrorInvalidValue;
+    const int64_t words = (int64_t)(bytes / 8);
     int64_t blocks = (words + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)blocks), dim3(256), 0, s, static_cast<uint32_t*>(p), words);
+    if (blocks < 1) blocks = 1;
+    HeaderArgs h{};
+    if (hdr) h = *hdr;
+    hipLaunchKernelGGL(k_clear, dim3((unsigned)blocks), dim3(256), 0, s, static_cast<uint64_t*>(p), words, n_out, h);
     return hipGetLastError();
 }
 
@@ -229,20 +239,12 @@ __device__ __forceinline__ bool point_increments(const double* x, const kdefft_g
 // partials (grid_from_bounds), and block 0 writes the dataset record.
 template <int D>
 __global__ __launch_bounds__(256) void k_linbin(const double* __restrict__ X, int64_t n, kdefft_grid g,
-                                                const double* __restrict__ gdev,
                                                 unsigned long long* __restrict__ counts,
                                                 int32_t* __restrict__ n_out, int slots, HeaderArgs hdr) {
 #pragma clang fp contract(off)
     constexpr int NC = 1 << D;
     __shared__ long long qs[256 * NC];   // increments, per wavefront in issue order
     __shared__ int64_t fbs[256];         // flat index of each point's lowest corner
-    if (gdev) {   // origin and spacing computed on the device
-#pragma unroll
-        for (int k = 0; k < D; ++k) {
-            g.lo[k] = gdev[k];
-            g.delta[k] = gdev[4 + k];
-        }
-    }
     if (hdr.partial) dataset_header<D>(hdr, g);   // block-uniform
     int64_t stride[D];
     stride[D - 1] = 1;
@@ -413,41 +415,34 @@ hipError_t launch_linbin_bands(const double* X, int64_t n, const kdefft_grid& g,
 }
 
 hipError_t launch_linbin_slots(const double* X, int64_t n, const kdefft_grid& g, int64_t* slots, int32_t* n_out,
-                               hipStream_t s, const double* gdev, bool slots_zeroed, const HeaderArgs* hdr) {
-    int64_t prodM = 1;
-    for (int k = 0; k < g.d; ++k) prodM *= g.M[k];
-    hipError_t e = hipSuccess;
-    if (!slots_zeroed) {
-        e = launch_zero(slots, (size_t)(corner_slots(g.d) * prodM) * sizeof(int64_t), s);
-        if (e != hipSuccess) return e;
-    }
+                               hipStream_t s, const HeaderArgs* hdr) {
     int64_t blocks = (n + 255) / 256;
     if (blocks > 16384) blocks = 16384;
     auto* c = reinterpret_cast<unsigned long long*>(slots);
     HeaderArgs h{};
     if (hdr) h = *hdr;
     switch (g.d) {
-        case 1: hipLaunchKernelGGL(k_linbin<1>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, gdev, c, n_out, 1, h); break;
-        case 2: hipLaunchKernelGGL(k_linbin<2>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, gdev, c, n_out, 1, h); break;
-        case 3: hipLaunchKernelGGL(k_linbin<3>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, gdev, c, n_out, 1, h); break;
-        case 4: hipLaunchKernelGGL(k_linbin<4>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, gdev, c, n_out, 1, h); break;
+        case 1: hipLaunchKernelGGL(k_linbin<1>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, c, n_out, 1, h); break;
+        case 2: hipLaunchKernelGGL(k_linbin<2>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, c, n_out, 1, h); break;
+        case 3: hipLaunchKernelGGL(k_linbin<3>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, c, n_out, 1, h); break;
+        case 4: hipLaunchKernelGGL(k_linbin<4>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, c, n_out, 1, h); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
 hipError_t launch_linbin(const double* X, int64_t n, const kdefft_grid& g, int64_t* counts, int32_t* n_out,
-                         hipStream_t s, const double* gdev) {
+                         hipStream_t s) {
     int64_t blocks = (n + 255) / 256;
     if (blocks > 16384) blocks = 16384;
     if (blocks < 1) blocks = 1;
     auto* c = reinterpret_cast<unsigned long long*>(counts);
     const HeaderArgs h{};
     switch (g.d) {
-        case 1: hipLaunchKernelGGL(k_linbin<1>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, gdev, c, n_out, 0, h); break;
-        case 2: hipLaunchKernelGGL(k_linbin<2>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, gdev, c, n_out, 0, h); break;
-        case 3: hipLaunchKernelGGL(k_linbin<3>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, gdev, c, n_out, 0, h); break;
-        case 4: hipLaunchKernelGGL(k_linbin<4>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, gdev, c, n_out, 0, h); break;
+        case 1: hipLaunchKernelGGL(k_linbin<1>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, c, n_out, 0, h); break;
+        case 2: hipLaunchKernelGGL(k_linbin<2>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, c, n_out, 0, h); break;
+        case 3: hipLaunchKernelGGL(k_linbin<3>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, c, n_out, 0, h); break;
+        case 4: hipLaunchKernelGGL(k_linbin<4>, dim3((unsigned)blocks), dim3(256), 0, s, X, n, g, c, n_out, 0, h); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

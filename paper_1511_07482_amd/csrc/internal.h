@@ -109,13 +109,12 @@ hipError_t twiddles(const double2** out);  // per-device table e^{-2 pi i m/4096
 // clearing zero_bytes (a multiple of 16, 16-byte aligned) at zero_ptr on the way.
 hipError_t launch_bounds_partial(const double* X, int64_t n, int d, double* partial, int nblk, hipStream_t s,
                                  void* zero_ptr, size_t zero_bytes, int32_t* n_out = nullptr, double* scal = nullptr);
-hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
-// gdev: if not NULL, 8 device doubles (lo[4], delta[4]) that replace g's
+// Binning into the count grid (zero on entry).
 hipError_t launch_linbin(const double* X, int64_t n, const kdefft_grid& g, int64_t* counts,
-                         int32_t* n_out, hipStream_t s, const double* gdev = nullptr);
+                         int32_t* n_out, hipStream_t s);
 // Binning into corner slots over the last min(d, 3) axes: a record of
 // S = 2^min(d, 3) int64 per cell of the count grid (slots: S * prod M int64,
-// cleared here unless slots_zeroed).  A point adds its 2^d corner weights to
+// zero on entry).  A point adds its 2^d corner weights to
 // 2^(d-3) records for d = 4 (one per node of axis 0: the cell of the lowest
 // corner moved along axis 0 for the upper one), to one record otherwise,
 // slot s of a record taking the corner's nodes along the slotted axes (bit j
@@ -130,18 +129,17 @@ struct HeaderArgs;
 // hdr (may be NULL): with hdr->partial set, the binning launch also computes
 // the grid from the bound partials and writes the dataset header (block 0).
 hipError_t launch_linbin_slots(const double* X, int64_t n, const kdefft_grid& g, int64_t* slots, int32_t* n_out,
-                               hipStream_t s, const double* gdev, bool slots_zeroed, const HeaderArgs* hdr = nullptr);
+                               hipStream_t s, const HeaderArgs* hdr = nullptr);
 // Binning straight into the count grid (zero on entry) by bands of nodes in
 // LDS: for the samples and grids that linbin_in_bands accepts.
 bool linbin_in_bands(int64_t n, const kdefft_grid& g);
 hipError_t launch_linbin_bands(const double* X, int64_t n, const kdefft_grid& g, int64_t* counts, int32_t* n_out,
                                hipStream_t s, const HeaderArgs* hdr = nullptr);
 
-// One small launch at the start of a dataset's preparation: the record (with
-// the grid origin and spacing from the data bounds when `partial` is set --
-// lo = min - pad, hi = max + pad, hi = lo + 1 for a degenerate axis,
-// delta = (hi - lo)/(M - 1), the same IEEE steps as the host planner), the
-// out-of-grid counter and scalar block cleared.
+// A dataset's record and what to write with it.  partial set: the grid origin
+// and spacing come from the data bounds, in the binning launch -- lo = min - pad,
+// hi = max + pad, hi = lo + 1 for a degenerate axis, delta = (hi - lo)/(M - 1),
+// the same IEEE steps as the host planner.
 struct HeaderArgs {
     DsDev* rec;
     DsDev val;
@@ -149,11 +147,12 @@ struct HeaderArgs {
     int nblk;
     kdefft_grid g;
     double pad[4];
-    int32_t* n_out;
     double* scal;
 };
-hipError_t launch_ds_header(const HeaderArgs& h, hipStream_t s);
-
+// Clears what a binning adds to: bytes (a multiple of 8) at p, the counter
+// n_out (may be NULL); hdr (may be NULL): a dataset's record is written and its
+// scalar block cleared too.
+hipError_t launch_clear(void* p, size_t bytes, int32_t* n_out, hipStream_t s, const HeaderArgs* hdr = nullptr);
 
 // Transforms along all axes but the first of arrays of slices (fft.hip).
 hipError_t fft_slices_forward(const double* in, double2* out, const kdefft_grid& g, int64_t slices, hipStream_t s);

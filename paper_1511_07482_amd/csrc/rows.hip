@@ -243,49 +243,6 @@ hipError_t launch_psi_setup(const PsiBatchArgs& a, double* prm, hipStream_t s) {
     return hipGetLastError();
 }
 
-// The preparation header (one block: the reduction of the bound partials uses
-// all its threads, the rest one thread): grid origin and spacing from the data
-// bounds (same IEEE steps and order as the host planner; non-finite data give
-// a NaN spacing, so every point counts as out of the grid), the record, the
-// cleared counter and scalar block, and the constant-term parameter block.
-template <int D>
-__global__ __launch_bounds__(256) void k_ds_header(HeaderArgs h) {
-#pragma clang fp contract(off)
-    __shared__ double scratch[32], red[8];
-    if (h.partial) reduce_bounds(h.partial, h.nblk, D, scratch, red);   // uniform branch
-    if (threadIdx.x != 0) return;
-    DsDev v = h.val;
-    if (h.partial) {
-        const double nan = __longlong_as_double(0x7ff8000000000000LL);
-        for (int k = 0; k < D; ++k) {
-            const double lo = red[k] - h.pad[k];
-            double hi = red[4 + k] + h.pad[k];
-            if (!isfinite(lo) || !isfinite(hi)) {
-                v.lo[k] = nan;
-                v.delta[k] = nan;
-                continue;
-            }
-            if (!(hi > lo)) hi = lo + 1.0;
-            v.lo[k] = lo;
-            v.delta[k] = (hi - lo) / (double)(h.g.M[k] - 1);
-        }
-    }
-    *h.rec = v;
-    if (h.n_out) *h.n_out = 0;
-    for (int k = 0; k < 4; ++k) h.scal[k] = 0.0;
-}
-
-hipError_t launch_ds_header(const HeaderArgs& h, hipStream_t s) {
-    switch (h.g.d) {
-        case 1: hipLaunchKernelGGL(k_ds_header<1>, dim3(1), dim3(256), 0, s, h); break;
-        case 2: hipLaunchKernelGGL(k_ds_header<2>, dim3(1), dim3(256), 0, s, h); break;
-        case 3: hipLaunchKernelGGL(k_ds_header<3>, dim3(1), dim3(256), 0, s, h); break;
-        case 4: hipLaunchKernelGGL(k_ds_header<4>, dim3(1), dim3(256), 0, s, h); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
 // Criterion assembly, one wavefront per candidate (see crit_finish); the
 // npseudo constant-term candidates after the real ones store their term in
 // their dataset's scalar block.  Work items of candidate c: c * nchunks + [0, nchunks).
