@@ -499,8 +499,9 @@ def fftl_section(kf, torch, dev, X, Gpsi, g):
 
 
 def fft_stage_bytes(P, M, d):
-    """Algorithmic HBM bytes of one dataset's count transform as the passes are
-    built (d >= 2, f = M/P the live fraction of a leading axis): the last-axis
+    """Algorithmic HBM bytes of one dataset's count transform with every column
+    and row of the mixed spectrum visited, the reference work of the transform
+    (d >= 2, f = M/P the live fraction of a leading axis): the last-axis
     R2C reads the int64 counts (prod M) and writes the rows of the half
     spectrum that can be nonzero (a fraction f^(d-1) of its 16 L Q bytes, L =
     prod of the leading P, Q = P/2 + 1); the forward pass along axis a
@@ -512,6 +513,16 @@ def fft_stage_bytes(P, M, d):
     f = M / P
     fwd = f ** (d - 1) + sum(f ** (a + 1) + f ** a for a in range(1, d - 1)) + f + 2
     return int(round(8 * M ** d + 8 * P ** d + half * (fwd + 2 * (d - 2) + 1)))
+
+
+def fft_stage_moved_bytes(P, M, d):
+    """Bytes that the passes move as they are built: fft_stage_bytes less what
+    the symmetry of the mixed spectrum saves (h = (P/2 + 1)/P): the axis-0 pass
+    writes the part h of it (d >= 3), axes 1..d-3 read and write h, axis d-2
+    reads h and writes all, the C2R pass reads h."""
+    half = 16 * P ** (d - 1) * (P // 2 + 1)
+    left = half - 16 * P ** (d - 2) * (P // 2 + 1) ** 2
+    return fft_stage_bytes(P, M, d) - left * (1 if d == 2 else 3 + 2 * (d - 3))
 
 
 def fft_stage_section(kf, torch, dev, stream, tune=True):
@@ -539,7 +550,7 @@ def fft_stage_section(kf, torch, dev, stream, tune=True):
     e1.record(stream)
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / (reps * len(dss))
-    nbytes = fft_stage_bytes(P, M, d)
+    nbytes = fft_stage_moved_bytes(P, M, d)
     half = 16 * P ** (d - 1) * (P // 2 + 1)
     touched = 8 * M ** d + 2 * half + 8 * P ** d
     return {"workload": f"count transform of {len(dss)} case-5-shaped datasets back to back (d={d}, M={M}, "

@@ -405,16 +405,17 @@ int kdefft_scv_plain(const kdefft_dataset* ds_host, const double* H_host, double
  * instead: sum_l k(l) A(l) against the prepared count autocorrelation
  * (identical sums, no per-candidate transform); for the SCV families, runs of
  * lags that start below 1e-290 and rise are evaluated lag by lag (3) or
- * walked with values scaled by e^600 (4); the psi and eta families treat 3 and
- * 4 alike and have no spectral variants for eta.  Variants 5 and 6 (one
- * kernel for both) walk the lag array in columns along axis d-2, 16
- * neighbouring lags of the last axis together, with every Gaussian whitened by
- * its Cholesky factor: only the lags whose widest Gaussian reaches 1e-30 of its
- * peak are walked (found in closed form per column; the dropped terms are far
- * below float64 rounding of the result), and the launch builds the candidates'
- * parameters itself.  Variant 5 with one block per work item is the untuned
- * default of the SCV families; the psi and eta families treat 5 and 6 as 3.
- * The untuned default of the other families is variant 3, grid 0.
+ * walked with values scaled by e^600 (4).  Variants 5 and 6 (one kernel for
+ * both) walk the lag array in columns along axis d-2, 16 neighbouring lags of
+ * the last axis together, with every Gaussian whitened by its Cholesky factor:
+ * only the lags whose widest Gaussian reaches 1e-30 of its peak are walked
+ * (found in closed form per column; the dropped terms are far below float64
+ * rounding of the result), and the launch builds the candidates' parameters
+ * itself.  Variant 5 with one block per work item is the untuned default of the
+ * SCV families.  The psi family, and the eta families up to r = 2 (d = 4: r =
+ * 1), walk columns for every variant from 3 on; the eta families of higher
+ * order treat 3 to 6 alike (every lag of every row) and no eta family has
+ * spectral variants.  The untuned default of those families is variant 3, grid 0.
  * variant = -1 drops the pinned (or tuned) choice of that key, so the untuned
  * default applies again.  Used by kdefft_autotune and by tests that cover
  * every variant.  Host only. */
@@ -432,8 +433,7 @@ int kdefft_get_row_launch(int kind, int d, int r, int N, int* variant, int* grid
  * families), *runs_per_seg = consecutive runs one thread walks carrying the
  * recurrence (moment families; 1 otherwise), *rows_per_pass = rows one
  * 256-thread block covers per pass.  moments = 1 for the SCV / LSCV families
- * (moment form), 0 for the psi_r and eta_r families with at most 12 outputs
- * per lag.  Lets a caller's work model use the constants the kernels were
+ * (moment form), 0 for the eta_r families that are summed row by row.  Lets a caller's work model use the constants the kernels were
  * compiled with.  Host only; KDEFFT_E_ARG for other N or NULL outputs. */
 int kdefft_lag_layout(int N, int moments, int* run_len, int* runs_per_seg, int* rows_per_pass);
 

@@ -17,7 +17,9 @@
 // one Horner scheme and its two nested ones give sum w, sum s w and
 // sum s(s+1)/2 w (s = t + 1) in four operations per lag and Gaussian.  The next
 // run starts at e r^8 g_8 and r exp(-8 u^2); a column is walked in segments of
-// SEG rows, each started with exponentials.  The constants that carry a walk
+// SEG rows, each started with exponentials.  The walked component of each run is
+// formed from its lag, not added up: the roundings of the far end would stay in
+// it (d = 3 and 4 gradients 6.5e-15 and 1.2e-14 off, so 3.6e-15 and 5.1e-15).  The constants that carry a walk
 // on are common to all columns, so their rounding would not average out (with
 // plain doubles 1.5e-14 of the d = 3, 4 results): they are kept as two doubles.
 //
@@ -26,9 +28,9 @@
 // load touches four lines; a row-wise walk (one lane per row run) touches 64
 // and folds 25 flops per Hessian entry into every run.  Whole SCV
 // objective-and-gradient call, replayed: d = 2, M = 256, 256 candidates 53.1 ->
-// 42.9 us, 4 candidates 23.6 -> 16.8 us; d = 3, M = 64, 64 candidates 150 ->
-// 65 us; d = 4, M = 32, four datasets of 64 candidates 3618 -> 979 us (row walk
-// -> column walk).
+// 36.9 us, 4 candidates 23.6 -> 16.2 us; d = 3, M = 64, 64 candidates 150 ->
+// 57 us; d = 4, M = 32, four datasets of 64 candidates 3618 -> 884 us (row walk
+// -> column walk; 979 before the walk was cut to the lags that the data reach).
 //
 // Live set: a lag is walked when its first Gaussian is at or above the cut of
 // its peak (LOG_REL_CUT).  The first Gaussian is the widest of its family
@@ -183,27 +185,57 @@ __device__ __forceinline__ double col_exp(double x, double xl, const double2* ta
     const double2 v = col_exp2(x, xl, tab, &k);
     return ldexp(v.x + v.y, k);
 }
-// exp(-k u^2) as a high and a low part (to about 2^-59): the constants that
-// carry a walk from run to run are the same for every column, so their
-// rounding would not average out.
+// exp(-k u^2) as a high and a low part (to about 2^-67): the constants that
+// carry a walk from run to run are the same for every column, so their errors
+// do not average out, and they grow with the square of the runs walked.
 __device__ __forceinline__ double2 col_exp_ku2(double k, double u, const double2* tab) {
 #pragma clang fp contract(off)
     const double uh = u * u, ul = fma(u, u, -uh), a = k * uh;
-    int n;
-    const double2 v = col_exp2(-a, -(fma(k, uh, -a) + k * ul), tab, &n);
-    const double s = v.x + v.y;
-    return make_double2(ldexp(s, n), ldexp(v.y - (s - v.x), n));
+    const double x = -a, xl = -(fma(k, uh, -a) + k * ul);
+    const double n = rint(x * 46.16624130844683);
+    const double r = fma(-n, 0.02166084939249829, x);   // exact
+    const double rl = fma(-n, 7.247021293269686e-19, xl);
+    const int ni = (int)n;
+    double p = fma(r, 1.0 / 5040.0, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    const double c = fma(p * r, r, fma(r, rl, rl));     // exp(r + rl) = 1 + r + c
+    const double2 t = tab[ni & 31];
+    const double b = t.x * r, rest = fma(t.x, r, -b) + fma(t.x, c, fma(t.y, r, t.y));
+    const double s = t.x + b, lo = (b - (s - t.x)) + rest, h = s + lo;
+    return make_double2(ldexp(h, ni >> 5), ldexp(lo - (h - s), ni >> 5));
 }
 
-// e = exp(-(q + y^2) / 2) and r = exp(-u y), the roundings of the arguments (up
-// to 69) taken along.
-__device__ __forceinline__ void col_start(double q, double u, double y, const double2* tab, double* e, double* r) {
+// *l += the rounding of the returned a + b.
+__device__ __forceinline__ double two_sum(double a, double b, double* l) {
 #pragma clang fp contract(off)
-    const double yy = y * y, s = q + yy, bb = s - q;
-    const double sl = (q - (s - bb)) + (yy - bb) + fma(y, y, -yy);
-    *e = col_exp(-0.5 * s, -0.5 * sl, tab);
+    const double s = a + b, bb = s - a;
+    *l += (a - (s - bb)) + (b - bb);
+    return s;
+}
+// exp(-(q + ql + (y + yl)^2) / 2), ql and yl small corrections, the rounding of
+// the argument (up to 69) taken along.
+__device__ __forceinline__ double col_weight(double q, double ql, double y, double yl, const double2* tab) {
+#pragma clang fp contract(off)
+    const double yy = y * y;
+    double sl = ql + fma(y, y, -yy);
+    const double s = two_sum(q, yy, &sl);
+    return col_exp(-0.5 * s, fma(-y, yl, -0.5 * sl), tab);
+}
+// e = exp(-(q + y^2) / 2) and r = exp(-u y) at y = y0 + u l (ql, yl: low parts of
+// q and y0), with the rounding of y: at a column's far end it would shift the
+// column's weights against its components.
+__device__ __forceinline__ void col_start(double q, double ql, double u, double y0, double yl, double l,
+                                          const double2* tab, double* e, double* r) {
+#pragma clang fp contract(off)
+    const double ul = u * l;
+    yl += fma(u, l, -ul);
+    const double y = two_sum(ul, y0, &yl);
+    *e = col_weight(q, ql, y, yl, tab);
     const double ru = u * y;
-    *r = col_exp(-ru, -fma(u, y, -ru), tab);
+    *r = col_exp(-ru, -(fma(u, y, -ru) + u * yl), tab);
 }
 
 // Lags with |y|^2 above this are dropped: exp(-|y|^2 / 2) below 1e-30, and for
@@ -395,7 +427,10 @@ __device__ __forceinline__ void col_psi_setup(const PsiBatchArgs& a, int64_t h, 
 #pragma unroll
         for (int i = 0; i < D; ++i)
 #pragma unroll
-            for (int m = 0; m < D; ++m) p[S_P1 + i * D + m] = m <= i ? li[tri(i, m)] : 0.0;
+            for (int m = 0; m < D; ++m)   // L^{-1} per lag, as the walk used it
+                p[S_P1 + i * D + m] = m <= i ? li[tri(i, m)] * delta[col_axis(D, m)] : 0.0;
+#pragma unroll
+        for (int i = 0; i < D; ++i) p[S_DELTA + i] = delta[i];
     }
 }
 
@@ -476,6 +511,7 @@ __device__ __forceinline__ void col_item(const ColGeom& geo, int64_t item, int64
 template <int D, int MODE>
 struct ColScvAcc {
     static constexpr int NGS = 2;
+    static constexpr bool EXACT = false;
     static constexpr int NQ = D * (D + 1) / 2;
     static constexpr int NA = MODE == 0 ? 1 : 1 + NQ;
     double v[2][NA];
@@ -548,6 +584,7 @@ struct ColScvAcc {
 template <int D, int K, int N_GS>
 struct ColHermAcc {
     static constexpr int NGS = N_GS;
+    static constexpr bool EXACT = D >= 3;
     using T = HermTab<D, K>;
     static constexpr int NA = T::NU;
     double v[NGS][NA];
@@ -707,15 +744,53 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
                     y[p] = v;
                 }
             };
-            double yE[NGS], q[NGS];   // yE: the walked component at lag 0
+            // the same, rounded once, and its low part
+            auto whiten_exact = [&](int k, double* y, double* l) {
+#pragma unroll
+                for (int p = 0; p < D; ++p) {
+                    double v = 0.0, w = 0.0;
+#pragma unroll
+                    for (int j = 0; j <= (p < D - 1 ? p : D - 2); ++j) {
+                        const double c = it.g[k].ld[tri(p, j)], x = (double)lag[j], cx = c * x;
+                        w += fma(c, x, -cx);
+                        v = two_sum(v, cx, &w);
+                    }
+                    y[p] = v + w;
+                    l[p] = w - (y[p] - v);
+                }
+            };
+            // Few columns carry a narrow kernel's sums, and sums of high order cancel,
+            // so that a component's or the exponent's rounding would not average out:
+            // there both are kept with their low parts.  (psi_4, d = 4, M = 32, mean
+            // error of the largest entry over ten samples against extended precision
+            // 9.7e-15; a row walk with S^{-1} 9.9e-15.)
+            double yE[NGS], yl[NGS], q[NGS], ql[NGS];   // yE: the walked component at lag 0
+            auto exact = [&](int k) {
+                double y[D], l[D];
+                whiten_exact(k, y, l);
+                q[k] = ql[k] = 0.0;
+#pragma unroll
+                for (int p = 0; p < D - 1; ++p) {
+                    const double yy = y[p] * y[p];
+                    ql[k] += fma(2.0 * y[p], l[p], fma(y[p], y[p], -yy));
+                    q[k] = two_sum(q[k], yy, &ql[k]);
+                }
+                yE[k] = y[D - 1];
+                yl[k] = l[D - 1];
+            };
 #pragma unroll
             for (int k = 0; k < NGS; ++k) {
-                double y[D];
-                whiten(k, y);
-                q[k] = 0.0;
+                if constexpr (Acc::EXACT) {
+                    exact(k);
+                } else {
+                    double y[D];
+                    whiten(k, y);
+                    q[k] = 0.0;
 #pragma unroll
-                for (int p = 0; p < D - 1; ++p) q[k] = fma(y[p], y[p], q[k]);
-                yE[k] = y[D - 1];
+                    for (int p = 0; p < D - 1; ++p) q[k] = fma(y[p], y[p], q[k]);
+                    yE[k] = y[D - 1];
+                    ql[k] = yl[k] = 0.0;
+                }
             }
             // live rows of this column, as runs of the segment
             int ca = 127, cb = -1;
@@ -749,22 +824,19 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
             };
             acc.begin();
             if (near1) {
-                double e[NGS], r[NGS];   // yE: from here the component at the row before the run
+                double e[NGS], r[NGS];
                 const double ls = (double)(s0 + COL_RUN * (cb >= 0 ? ca : 0));
 #pragma unroll
-                for (int k = 0; k < NGS; ++k) {
-                    const double ys = fma(uw[k], ls, yE[k]);
-                    col_start(q[k], uw[k], ys, s_exp, &e[k], &r[k]);
-                    yE[k] = ys - uw[k];
-                }
+                for (int k = 0; k < NGS; ++k) col_start(q[k], ql[k], uw[k], yE[k], yl[k], ls, s_exp, &e[k], &r[k]);
                 auto run = [&](int c, const double* av) {
                     if (c < ca) return;   // the lane's column starts in a later run
+                    const double before = (double)(s0 + COL_RUN * c - 1);
 #pragma unroll
                     for (int k = 0; k < NGS; ++k) {
-                        acc.run(k, av, g[k], e[k], r[k], yE[k], uw[k]);
-                        yE[k] = fma(uw[k], (double)COL_RUN, yE[k]);
+                        acc.run(k, av, g[k], e[k], r[k], fma(uw[k], before, yE[k]), uw[k]);
                         const double r2 = r[k] * r[k], r4 = r2 * r2, r8 = r4 * r4;
-                        e[k] *= fma(r8, g8[k][0], r8 * g8[k][1]);   // (exact products with the high parts)
+                        // (exact products with the high parts)
+                        e[k] *= fma(r8, g8[k][0], r8 * g8[k][1]);
                         r[k] = fma(r[k], hh[k][0], r[k] * hh[k][1]);
                     }
                 };
@@ -779,6 +851,10 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
                 }
             } else if (cb >= 0) {
                 // narrow kernels: lag by lag
+                if constexpr (!Acc::EXACT) {
+#pragma unroll
+                    for (int k = 0; k < NGS; ++k) exact(k);
+                }
 #pragma unroll 1
                 for (int l = s0 + COL_RUN * ga; l < s0 + COL_RUN * (gb + 1); ++l) {
                     double a = 0.0;
@@ -786,8 +862,10 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
                     if (D == 2 && l == 0) a *= 0.5;
 #pragma unroll
                     for (int k = 0; k < NGS; ++k) {
-                        const double yw = fma(uw[k], (double)l, yE[k]);
-                        acc.lag(k, exp(-0.5 * fma(yw, yw, q[k])) * a, yw);
+                        const double ul = uw[k] * (double)l;
+                        double low = yl[k] + fma(uw[k], (double)l, -ul);
+                        const double yw = two_sum(ul, yE[k], &low);
+                        acc.lag(k, col_weight(q[k], ql[k], yw, low, s_exp) * a, yw);
                     }
                 }
             }
@@ -797,8 +875,11 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
             for (int p = 0; p < D - 1; ++p) asm volatile("" : "+v"(lag[p]));
 #pragma unroll
             for (int k = 0; k < NGS; ++k) {
-                double y[D];
-                whiten(k, y);
+                double y[D], l[D];
+                if (near1 && !Acc::EXACT)
+                    whiten(k, y);
+                else
+                    whiten_exact(k, y, l);
                 acc.column(k, rw, y);
             }
         }
@@ -981,10 +1062,11 @@ template <int D, int R>
 __global__ __launch_bounds__(COL_NT) void k_cols_psi_final(const double* __restrict__ partial, int64_t nchunks,
                                                            const double* __restrict__ prm, double* __restrict__ psi) {
     constexpr int NU = HermTab<D, R>::NU, NF = ipow(D, R), NR = COL_NT / NU;
-    __shared__ double s_part[NR * NU], s_t[2][NF], s_li[D * D];
+    __shared__ double s_part[NR * NU], s_t[2][NF], s_li[D * D], s_dl[D];
     const int tid = threadIdx.x;
     const int64_t h = blockIdx.x;
     if (tid < D * D) s_li[tid] = prm[h * PRM + S_P1 + tid];
+    if (tid < D) s_dl[tid] = prm[h * PRM + S_DELTA + tid];
     const double scale = prm[h * PRM + S_C];
     if (tid < NR * NU) {
         const double* p = partial + h * nchunks * NU;
@@ -1024,7 +1106,13 @@ __global__ __launch_bounds__(COL_NT) void k_cols_psi_final(const double* __restr
         __syncthreads();
         cur ^= 1;
     }
-    for (int e = tid; e < NU; e += COL_NT) psi[h * NU + e] = scale * s_t[cur][R > 0 ? COL_UNIQUE<D, R>.e[e] : 0];
+    for (int e = tid; e < NU; e += COL_NT) {
+        int x = R > 0 ? COL_UNIQUE<D, R>.e[e] : 0;
+        double v = scale * s_t[cur][x];
+#pragma unroll
+        for (int m = 0; m < R; ++m, x /= D) v /= s_dl[x % D];   // from lags to the axes' units
+        psi[h * NU + e] = v;
+    }
 }
 
 // Scalar eta_r families (Q_r with one Gaussian, LSCV_r with two), r <= 2:
