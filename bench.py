@@ -639,7 +639,7 @@ def main_case5(a):
            "prepare_all_ms": t_prep, "psi4_batch_ms": t_psi, "scv_objgrad_batch_ms": t_scv,
            "scv_evals_per_s": B / (t_scv * 1e-3), "psi4_evals_per_s": len(dss) / (t_psi * 1e-3),
            "largest_n": ns[big], "linbin_largest_ms": t_bin, "prepare_largest_ms": t_prep1,
-           "fft_stage_bytes_per_dataset": fft_stage_bytes(P, M, d), "scv_roofline": roofline, "tuned": tuned}
+           "fft_stage_bytes_per_dataset": fft_stage_moved_bytes(P, M, d), "scv_roofline": roofline, "tuned": tuned}
     print(json.dumps(out))
 
 
