@@ -206,7 +206,8 @@ __device__ __forceinline__ bool point_increments(const double* x, const kdefft_g
     for (int k = 0; k < D; ++k) {
         const double t = (x[k] - g.lo[k]) / g.delta[k];
         ok = ok && (t >= 0.0) && (t <= (double)(g.M[k] - 1));
-        const double jf = fmin(floor(t), (double)(g.M[k] - 2));   // M - 1 -> M - 2
+        // M - 1 -> M - 2 (and outside the grid a value that an int holds)
+        const double jf = fmax(fmin(floor(t), (double)(g.M[k] - 2)), 0.0);
         const double f = t - jf;
         w0[k] = 1.0 - f;
         w1[k] = f;
