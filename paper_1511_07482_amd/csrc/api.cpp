@@ -438,11 +438,15 @@ PlainScratch carve_plain(Arena& a, const kdefft_grid& g, int batch, bool with_co
 struct BatchScratch {
     double* prm;
     double* partial;
+    int64_t room;        // doubles of partial
     int32_t* wc;         // live run counts per candidate (kdefft_scv_walk_runs)
 };
 
 // Partial sums of the row kernels: sized for every family that may run in
-// this workspace (the SCV families differ in grids per item and chunking).
+// this workspace (the SCV families differ in grids per item and chunking), at
+// the largest number of candidates a launch may have.  Fewer of them may ask for
+// more items in all (a candidate's share is rounded): their launches are cut to
+// the room there is (crit_walk), which holds at least one item of each.
 BatchScratch carve_batch(Arena& a, const kdefft_grid& g, int kind, int r, int64_t ncand) {
     BatchScratch b;
     // the criteria add one constant-term candidate per dataset (SCV)
@@ -455,7 +459,8 @@ BatchScratch carve_batch(Arena& a, const kdefft_grid& g, int kind, int r, int64_
         for (int k = FUN_SCV_OBJ; k <= FUN_ETA2; ++k)
             need = std::max<int64_t>(need, max_nchunks(g, k, 2, ncand) * ng_of(k, g.d, 2));
     }
-    b.partial = a.take<double>(ncand * need);
+    b.room = ncand * need;
+    b.partial = a.take<double>(b.room);
     b.wc = a.take<int32_t>(ncand);
     return b;
 }
@@ -716,6 +721,28 @@ int scv_batch_ws_need(const kdefft_dataset* ds, int n_ds, const int64_t* off, si
     carve_batch(a, g, FUN_SCV_OBJGRAD, 2, B);
     *need = a.off + 256;
     return KDEFFT_OK;
+}
+
+static bool moment_family(int kind) {
+    return kind == FUN_SCV_OBJ || kind == FUN_SCV_OBJGRAD || kind == FUN_SCV_GRAD;
+}
+
+CritWalk crit_walk(const kdefft_grid& g, int kind, int r, int variant, int64_t nc, int64_t room) {
+    CritWalk w{};
+    const int ng = ng_of(kind, g.d, 2);
+    const int64_t most = room / (nc * ng);
+    w.cols = moment_family(kind) ? variant >= 5 : (variant == 3 || variant == 4) && cols_eta_ok(g.d, r);
+    if (w.cols)
+        w.col = cols_geom(g, nc, ng, true, most);
+    else
+        w.row = make_geom(g, kind, moment_family(kind) ? 2 : r, nc, variant, most);
+    w.nchunks = w.cols ? w.col.nchunks : w.row.nchunks;
+    return w;
+}
+
+int64_t crit_room(const kdefft_grid& g, int64_t B) {
+    Arena a(nullptr, 0, true);
+    return carve_batch(a, g, FUN_SCV_OBJGRAD, 2, B).room;
 }
 
 }  // namespace kdefft
@@ -1266,13 +1293,15 @@ static int crit_common(const kdefft_dataset* ds, int n_ds, const int64_t* off, c
     // the criteria complete in their own kernel: fused into the walk the
     // assembly lengthens the dominant launch by about what the separate
     // launch costs in a replayed graph
-    int64_t nchunks = 0;
-    const bool mom = kind == FUN_SCV_OBJ || kind == FUN_SCV_OBJGRAD || kind == FUN_SCV_GRAD;
-    if (mom ? rl.variant >= 5 : (rl.variant == 3 || rl.variant == 4) && cols_eta_ok(g.d, r)) {
+    const CritWalk walk = crit_walk(g, kind, r, rl.variant, nc, b.room);
+    const int64_t nchunks = walk.nchunks;
+    if (nc * nchunks * ng_of(kind, g.d, 2) > b.room)
+        return fail(KDEFFT_E_WORKSPACE, "partial sums of %lld candidates do not fit the workspace", (long long)nc);
+    const bool mom = moment_family(kind);
+    if (walk.cols) {
         // the column walk computes its parameters in its own launch
         const ScvSetup setup{npseudo, B, vechL, status, b.prm, a};
-        const ColGeom geo = cols_geom(g, nc, ng_of(kind, g.d, 2), true);
-        nchunks = geo.nchunks;
+        const ColGeom& geo = walk.col;
         HIPCHK(timed_launch(kind, kr, s,
                             [&] {
                                 return mom ? launch_cols_scv(kind, g.d, geo, setup, nc * nchunks, b.partial,
@@ -1282,8 +1311,7 @@ static int crit_common(const kdefft_dataset* ds, int n_ds, const int64_t* off, c
                             }),
                "criterion columns");
     } else {
-        const RowGeom geo = make_geom(g, kind, kr, nc, rl.variant);
-        nchunks = geo.nchunks;
+        const RowGeom& geo = walk.row;
         HIPCHK(launch_scv_setup(vechL, a, B, npseudo, b.prm, status, geo, nullptr, s), "criterion setup");
         HIPCHK(timed_launch(kind, kr, s,
                             [&] { return launch_rows(kind, g.d, kr, geo, b.prm, nc, b.partial, rl, s); }),

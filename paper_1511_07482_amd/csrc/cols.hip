@@ -1,6 +1,8 @@
 // Column walk (cols.h): geometry, and the launchers of the SCV families.
 #include "cols.h"
 
+#include <algorithm>
+
 namespace kdefft {
 
 // Resident blocks on the current device: the kernels' launch bounds ask for
@@ -36,7 +38,7 @@ static int64_t cols_steps(const kdefft_grid& g) {
 // of axis-0 lags (a power of two from 8 on, so that a group's planes stay within
 // about 2 MB), split further when the candidates are few; psi, whose parts one
 // block adds up, takes at most 256 of them.
-ColGeom cols_geom(const kdefft_grid& g, int64_t ncand, int ng, bool scv) {
+ColGeom cols_geom(const kdefft_grid& g, int64_t ncand, int ng, bool scv, int64_t max_chunks) {
     ColGeom geo{};
     for (int k = 0; k < 4; ++k) {
         geo.M[k] = k < g.d ? g.M[k] : 1;
@@ -55,15 +57,16 @@ ColGeom cols_geom(const kdefft_grid& g, int64_t ncand, int ng, bool scv) {
         const int64_t slice = 8LL * g.P[d - 1] * g.P[d - 2] * (d == 4 ? g.P[1] : 1);
         int n0 = 1;
         while (2 * n0 <= g.M[0] && (n0 < 8 || g.M[0] * slice > n0 * (2LL << 20))) n0 *= 2;
-        while (n0 > 1 && n0 * ng > room) n0 /= 2;
+        while (n0 > 1 && (n0 * ng > room || n0 > max_chunks)) n0 /= 2;
         int64_t nsub = (per + n0 - 1) / n0;
         if (nsub > 1 && n0 * nsub * ng > room) nsub = 1;
+        if (n0 * nsub > max_chunks) nsub = std::max<int64_t>(max_chunks / n0, 1);
         geo.n0 = n0;
         geo.nchunks = n0 * nsub;
         return geo;
     }
     while (per > 1 && per * ng > room) per /= 2;
-    geo.nchunks = per;
+    geo.nchunks = std::min(per, std::max<int64_t>(max_chunks, 1));
     return geo;
 }
 

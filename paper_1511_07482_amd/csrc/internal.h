@@ -250,7 +250,8 @@ struct ColGeom {
 };
 // ng: outputs per item; scv: the batch may have to fit the fixed scratch of the
 // call without a workspace.
-ColGeom cols_geom(const kdefft_grid& g, int64_t ncand, int ng, bool scv);
+// max_chunks: work items per candidate that the partial sums have room for.
+ColGeom cols_geom(const kdefft_grid& g, int64_t ncand, int ng, bool scv, int64_t max_chunks = INT64_MAX);
 bool cols_eta_ok(int d, int r);
 hipError_t launch_cols_scv(int kind, int d, const ColGeom& geo, const ScvSetup& setup, int64_t nitems,
                            double* partial, int grid_blocks, hipStream_t s);
@@ -260,7 +261,20 @@ hipError_t launch_cols_eta(int kind, int d, int r, const ColGeom& geo, const Scv
 hipError_t launch_cols_psi(const ColGeom& geo, const PsiBatchArgs& a, int grid_blocks, double* prm, double* partial,
                            double* psi, hipStream_t s);
 
-RowGeom make_geom(const kdefft_grid& g, int kind, int r, int64_t ncand, int variant);
+RowGeom make_geom(const kdefft_grid& g, int kind, int r, int64_t ncand, int variant, int64_t max_chunks = INT64_MAX);
+
+// The work items of a criterion launch over nc candidates (real and
+// constant-term ones): the column walk's or the row kernels' geometry.
+struct CritWalk {
+    bool cols;
+    ColGeom col;
+    RowGeom row;
+    int64_t nchunks;
+};
+// room: doubles of partial sums.  kind, r: kernel family and criterion order.
+CritWalk crit_walk(const kdefft_grid& g, int kind, int r, int variant, int64_t nc, int64_t room);
+// Doubles of partial sums in the workspace of a batch of B candidates.
+int64_t crit_room(const kdefft_grid& g, int64_t B);
 
 // Host helpers of the C-ABI layer shared with other units: record an error
 // (returned code, message for kdefft_last_error_detail), and the workspace

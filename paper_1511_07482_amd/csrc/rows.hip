@@ -105,7 +105,7 @@ int rows_per_iter(int kind, int d, int r, int N, int variant) {
     }
 }
 
-RowGeom make_geom(const kdefft_grid& g, int kind, int r, int64_t ncand, int variant) {
+RowGeom make_geom(const kdefft_grid& g, int kind, int r, int64_t ncand, int variant, int64_t max_chunks) {
     RowGeom geo{};
     geo.d = g.d;
     for (int k = 0; k < 4; ++k) {
@@ -126,6 +126,10 @@ RowGeom make_geom(const kdefft_grid& g, int kind, int r, int64_t ncand, int vari
     int64_t iters = (nrows * ncand + (int64_t)ri * target - 1) / ((int64_t)ri * target);
     if (iters < 1) iters = 1;
     int64_t chunk = iters * ri;
+    if (max_chunks < 1) max_chunks = 1;
+    // (items of at least nrows / max_chunks rows; not from nrows + max_chunks - 1, which may overflow)
+    const int64_t least = nrows / max_chunks + (nrows % max_chunks ? 1 : 0);
+    if (chunk < least) chunk = (least + ri - 1) / ri * ri;
     if (chunk > nrows) chunk = ((nrows + ri - 1) / ri) * ri;
     geo.chunk = chunk;
     geo.nchunks = (nrows + chunk - 1) / chunk;
