@@ -460,10 +460,6 @@ __device__ __forceinline__ int min16(int v) {
 }
 __device__ __forceinline__ int max16(int v) { return -min16(-v); }
 
-// Quotient of u / d for u < 2^21 by a reciprocal in float (exact: the float
-// error of (u + 1/2) / d stays below 1 / (2 d)).
-__device__ __forceinline__ int fdiv_small(int u, float rd) { return (int)(((float)u + 0.5f) * rd); }
-
 // Units of one candidate: (plane, segment of the walked axis, block of 16
 // lags of the last axis), numbered with the block fastest.
 template <int D>
@@ -472,7 +468,7 @@ struct ColUnits {
     int nseg, nsn;     // segments, of them on the negative side
     int n1;            // planes along axis 1 (D = 4)
     int total;
-    float rnb, rnseg, rn1;
+    ColRecip<D> rnb, rnseg, rn1;
     // n0lags: lags of axis 0 the item takes (D >= 3)
     __device__ __forceinline__ ColUnits(const int* lm, int N, bool small, int n0lags) {
         const int lx = lm[D - 2], lw = lm[D - 1];
@@ -482,9 +478,9 @@ struct ColUnits {
         nseg = small ? 1 : col_segs(D, lw);
         n1 = D == 4 ? 2 * lm[1] + 1 : 1;
         total = nb * nseg * n1 * n0lags;
-        rnb = 1.0f / (float)nb;
-        rnseg = 1.0f / (float)nseg;
-        rn1 = 1.0f / (float)n1;
+        rnb = 1 / (ColRecip<D>)nb;
+        rnseg = 1 / (ColRecip<D>)nseg;
+        rn1 = 1 / (ColRecip<D>)n1;
     }
 };
 
@@ -709,9 +705,9 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
         const uint32_t strideP = (uint32_t)Pw * (uint32_t)N;   // elements of a plane
         for (int u = sub * 16 + (tid >> 4); u < un.total; u += nsub * 16) {
             // decode: block fastest, then segment, then plane
-            const int rs = fdiv_small(u, un.rnb);
+            const int rs = col_quot(u, un.rnb);
             const int b = u - rs * un.nb;
-            const int pl = fdiv_small(rs, un.rnseg);
+            const int pl = col_quot(rs, un.rnseg);
             const int seg = rs - pl * un.nseg;
             int lag[D];
             double rw = 2.0;
@@ -721,7 +717,7 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
                 col += (uint32_t)lag[0] * strideP;
             }
             if constexpr (D == 4) {
-                const int i0 = fdiv_small(pl, un.rn1);
+                const int i0 = col_quot(pl, un.rn1);
                 const int l1 = pl - i0 * un.n1 - lm[1];
                 lag[0] = lag0(i0);
                 lag[1] = l1;

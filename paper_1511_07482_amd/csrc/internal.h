@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/kdefft.h"
 
 namespace kdefft {
@@ -253,6 +255,15 @@ struct ColGeom {
 // max_chunks: work items per candidate that the partial sums have room for.
 ColGeom cols_geom(const kdefft_grid& g, int64_t ncand, int ng, bool scv, int64_t max_chunks = INT64_MAX);
 bool cols_eta_ok(int d, int r);
+// floor(u / d) for u >= 0 and rd = 1 / d: exact while the roundings of (u + 1/2) rd
+// stay below 1 / (2 d), in float for u < 2^22, in double for all int.  d <= 3: the
+// units of a candidate stay below 2^21 (prod P <= 2^30, P <= 4096).  d = 4: a part has up
+// to 2^23, where the last two axes are short, the others long and the
+// candidates so many that the axis-0 groups are few.
+template <int D>
+using ColRecip = std::conditional_t<D == 4, double, float>;
+template <class R>
+__host__ __device__ inline int col_quot(int u, R rd) { return (int)(((R)u + (R)0.5) * rd); }
 hipError_t launch_cols_scv(int kind, int d, const ColGeom& geo, const ScvSetup& setup, int64_t nitems,
                            double* partial, int grid_blocks, hipStream_t s);
 hipError_t launch_cols_eta(int kind, int d, int r, const ColGeom& geo, const ScvSetup& setup, int64_t nitems,

@@ -1,6 +1,8 @@
 // Launch extents of the batched criteria against the workspace they are given,
 // over thin and long grids, every kernel family and variant, and batches whose
-// candidates share the device unevenly.  Host only: nothing is launched.
+// candidates share the device unevenly; and the column walk's unit numbers, taken
+// apart as the kernel does, up to the largest a part can have.  Host only:
+// nothing is launched.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -50,7 +52,49 @@ static void check(const kdefft_grid& g, int64_t B) {
     }
 }
 
+// Every u around a multiple of d of a candidate of `total` units.
+template <int D>
+static void check_quotients(int d, int total) {
+    const ColRecip<D> rd = 1 / (ColRecip<D>)d;
+    for (int64_t m = 0; m < total; m += d)
+        for (int64_t u = m > 0 ? m - 1 : 0; u <= m + 1 && u < total; ++u) {
+            ++checked;
+            if (col_quot((int)u, rd) != u / d && fails++ < 5)
+                std::printf("d=%d unit %lld of %d: quotient by %d\n", D, (long long)u, total, d);
+        }
+}
+
+// The largest number of units a launch of dimension d can ask for (prod P <=
+// 2^30, one axis-0 group), as cols.h counts them.
+static int64_t most_units(int d) {
+    int64_t most = 0;
+    for (int n = 2; n <= 2048; n *= 2)             // nodes of the last axis; P = 2 n
+        for (int w = 2; w <= 2048; w *= 2)         // of the walked one
+            for (int a = d > 2 ? 2 : 1; a <= (d > 2 ? 2048 : 1); a *= 2)
+                for (int b = d > 3 ? 2 : 1; b <= (d > 3 ? 2048 : 1); b *= 2)
+                    for (int e = 0; e < 2; ++e) {   // just past half a padded axis, and filling it
+                        const int64_t P = 4LL * n * w * (d > 2 ? 2 * a : 1) * (d > 3 ? 2 * b : 1);
+                        if (P > (1LL << 30)) continue;
+                        const int lx = (e ? n : n / 2 + 1) - 1, lw = (e ? w : w / 2 + 1) - 1;
+                        int64_t u = 2 * n <= 16 ? 1 : lx / 16 + 1 + (lx + 15) / 16;
+                        const int side = d == 2 || lw < 32 ? 0 : (lw - 32) / 64 + 1;
+                        u *= 2 * w < 16 ? 1 : d == 2 ? lw / 64 + 1 : 2 * side + 1;
+                        u *= (d > 2 ? a : 1) * (d > 3 ? 2LL * b - 1 : 1);
+                        if (u > most) most = u;
+                    }
+    return most;
+}
+
 int main() {
+    for (int d : {1, 2, 3, 5, 7, 31, 32, 33, 63, 129, 257, 1000, 4095}) {
+        check_quotients<2>(d, (int)most_units(2));
+        check_quotients<3>(d, (int)most_units(3));
+        check_quotients<4>(d, (int)most_units(4));
+    }
+    if (most_units(3) >= 1 << 21 || most_units(4) < 1 << 22) {
+        ++fails;
+        std::printf("units: %lld at d = 3, %lld at d = 4\n", (long long)most_units(3), (long long)most_units(4));
+    }
     // thin first axes beside long ones, batches around a whole number per resident block
     for (int m0 = 2; m0 <= 8; ++m0)
         for (int m1 : {2, 17, 155, 372, 511}) {
@@ -72,7 +116,7 @@ int main() {
         for (int k = 0; k < d; ++k) M[k] = 2 + (int)(rng() % (rng() % 2 ? 7 : most[d] - 1));
         check(shape(d, M), 1 + (int64_t)(rng() % (rng() % 2 ? 1200 : 40000)));
     }
-    std::printf("%lld launches, %lld beyond the workspace\n", checked, fails);
+    std::printf("%lld checks, %lld failures\n", checked, fails);
     if (fails == 0) std::printf("ok\n");
     return fails != 0;
 }
