@@ -224,6 +224,13 @@ __device__ __forceinline__ double col_weight(double q, double ql, double y, doub
     const double s = two_sum(q, yy, &sl);
     return col_exp(-0.5 * s, fma(-y, yl, -0.5 * sl), tab);
 }
+// Kernels far narrower than a grid step: a component beyond this has a weight of
+// exactly 0 (exp(-2048)), but as an argument it could overflow the reduction of
+// col_exp and the polynomials (0 times infinity).  Below COL_FAR / 4 per lag the
+// components of a segment stay in col_exp's range: those kernels have a loop
+// without the comparison (which took 10% of a d = 4 psi_4 call).
+constexpr double COL_FAR = 64.0;
+
 // e = exp(-(q + y^2) / 2) and r = exp(-u y) at y = y0 + u l (ql, yl: low parts of
 // q and y0), with the rounding of y: at a column's far end it would shift the
 // column's weights against its components.
@@ -651,11 +658,12 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
     constexpr int NGS = Acc::NGS;
     const int tid = threadIdx.x, l16 = tid & 15;
     double uw[NGS];
-    bool near1 = true;
+    bool near1 = true, far = false;   // far: components beyond COL_FAR are possible
 #pragma unroll
     for (int k = 0; k < NGS; ++k) {
         uw[k] = wave_uniform(it.g[k].ld[tri(D - 1, D - 1)]);
         near1 = near1 && uw[k] * uw[k] < 0.69314718055994531;
+        far = far || uw[k] > COL_FAR / 4;
     }
     // (a pointer taken from memory: named global so that its loads are not flat ones)
     using gptr = const __attribute__((address_space(1))) char*;
@@ -674,7 +682,7 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
 #pragma unroll
             for (int k = 0; k < NGS; ++k) {
                 const double y = uw[k] * (double)l;
-                acc.lag(k, exp(-0.5 * y * y) * a, y);
+                if (fabs(y) < COL_FAR) acc.lag(k, exp(-0.5 * y * y) * a, y);
             }
         }
 #pragma unroll
@@ -851,19 +859,26 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
 #pragma unroll
                     for (int k = 0; k < NGS; ++k) exact(k);
                 }
+                auto lags = [&](auto guarded) {
 #pragma unroll 1
-                for (int l = s0 + COL_RUN * ga; l < s0 + COL_RUN * (gb + 1); ++l) {
-                    double a = 0.0;
-                    if (!SMALL || l <= wl) a = at(l, 0);
-                    if (D == 2 && l == 0) a *= 0.5;
+                    for (int l = s0 + COL_RUN * ga; l < s0 + COL_RUN * (gb + 1); ++l) {
+                        double a = 0.0;
+                        if (!SMALL || l <= wl) a = at(l, 0);
+                        if (D == 2 && l == 0) a *= 0.5;
 #pragma unroll
-                    for (int k = 0; k < NGS; ++k) {
-                        const double ul = uw[k] * (double)l;
-                        double low = yl[k] + fma(uw[k], (double)l, -ul);
-                        const double yw = two_sum(ul, yE[k], &low);
-                        acc.lag(k, col_weight(q[k], ql[k], yw, low, s_exp) * a, yw);
+                        for (int k = 0; k < NGS; ++k) {
+                            const double ul = uw[k] * (double)l;
+                            double low = yl[k] + fma(uw[k], (double)l, -ul);
+                            const double yw = two_sum(ul, yE[k], &low);
+                            if (guarded && fabs(yw) >= COL_FAR) continue;
+                            acc.lag(k, col_weight(q[k], ql[k], yw, low, s_exp) * a, yw);
+                        }
                     }
-                }
+                };
+                if (far)
+                    lags(std::true_type{});
+                else
+                    lags(std::false_type{});
             }
             // the column's sums: products with the fixed components (formed
             // again: kept over the walk they would cost registers)
