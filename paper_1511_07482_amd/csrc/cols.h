@@ -361,12 +361,19 @@ __device__ __forceinline__ void col_crit_setup(const ScvSetup& s, int64_t h, boo
     bool ok;
     const double c0 = col_gauss<D, NGS>(S, delta, sing, cut2, ds, tab, it, &ok, li);
     sing = __ballot(ok) != ~0ull;
+    if constexpr (R > 0 || NGS == 1) {   // the eta families
+        // no grid (data that are not finite): no lag is live, and the result is NaN
+        double none = 0.0;
+#pragma unroll
+        for (int c = 0; c < D; ++c) none += 0.0 * delta[c];
+        if (t == 0) it->g[k].c = c0 + none;
+    }
     const double n = ds.n;
     if (t == 0) {
         const bool exact = a.crit == KDEFFT_CRIT_LSCV_EXACT;
         const double sgn = !scv && !qr && (R & 1) ? -1.0 : 1.0;
         if (k == 1 && pseudo) it->g[k].c = 0.0;
-        if (k == 1 && exact) it->g[k].c = c0 * (n / (n - 1.0));
+        if (k == 1 && exact) it->g[k].c *= n / (n - 1.0);
         if (k == 0) it->sign = sgn;
         if (first && k == NGS - 1) {
             // what the final kernel reads
@@ -430,7 +437,10 @@ __device__ __forceinline__ void col_psi_setup(const PsiBatchArgs& a, int64_t h, 
     const double c0 = col_gauss<D, 1>(S, delta, false, cut2, ds, tab, it, &ok, li);
     if (first && threadIdx.x == 0) {
         double* p = prm + h * PRM;
-        p[S_C] = c0 * (1.0 / (ds.n * ds.n * a.prodP));
+        double none = 0.0;   // NaN without a grid (data that are not finite): no lag is live then
+#pragma unroll
+        for (int i = 0; i < D; ++i) none += 0.0 * delta[i];
+        p[S_C] = (c0 + none) * (1.0 / (ds.n * ds.n * a.prodP));
 #pragma unroll
         for (int i = 0; i < D; ++i)
 #pragma unroll
