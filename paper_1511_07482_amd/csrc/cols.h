@@ -16,12 +16,20 @@
 // so a run of RUN = 8 rows is a polynomial in r with the coefficients a_t g_t:
 // one Horner scheme and its two nested ones give sum w, sum s w and
 // sum s(s+1)/2 w (s = t + 1) in four operations per lag and Gaussian.  The next
-// run starts at e r^8 g_8 and r exp(-8 u^2); a column is walked in segments of
+// run starts at e s and r exp(-8 u^2), its s is s exp(-64 u^2) (s = r^8 g_8, from the
+// start on its own: as a power of each run's r it would take eight times that
+// run's roundings); a column is walked in segments of
 // SEG rows, each started with exponentials.  The walked component of each run is
 // formed from its lag, not added up: the roundings of the far end would stay in
 // it (d = 3 and 4 gradients 6.5e-15 and 1.2e-14 off, so 3.6e-15 and 5.1e-15).  The constants that carry a walk
 // on are common to all columns, so their rounding would not average out (with
 // plain doubles 1.5e-14 of the d = 3, 4 results): they are kept as two doubles.
+// Errors of whole results against extended precision, 2-norm relative, mean of 12
+// samples, s as a power of r -> s by itself (a row walk of the same sums): d = 3,
+// M = 64 SCV objective 2.9e-15 -> 1.1e-15 (1.3e-15), gradient 1.7e-15 -> 1.1e-15
+// (0.9e-15), psi_4 3.1e-14 -> 1.4e-14 (0.7e-14; one with the components' low
+// parts too), psi_2 2.7e-15 -> 1.0e-15 (5.2e-15); d = 2, M = 203 gradient 2.1e-15 ->
+// 1.7e-15 (3.5e-15).
 //
 // Bound: FP64 issue (d = 4), the latency of an item's set-up and reductions
 // (few candidates).  16 lanes x 8 bytes are one cache line, so a wavefront's
@@ -90,7 +98,8 @@ struct ColGauss {
     double li[D * D];         // (square, zero above the diagonal)
     double c;
     double gt[COL_RUN];   // exp(-u^2 t^2 / 2), t < RUN
-    double h[2], g8[2];   // exp(-RUN u^2) and exp(-RUN^2 u^2 / 2), as high and low parts
+    // exp(-RUN u^2), exp(-RUN^2 u^2 / 2) and exp(-RUN^2 u^2), as high and low parts
+    double h[2], g8[2], h8[2];
 };
 
 // An item's parameters, in LDS.
@@ -231,18 +240,33 @@ __device__ __forceinline__ double col_weight(double q, double ql, double y, doub
 // without the comparison (which took 10% of a d = 4 psi_4 call).
 constexpr double COL_FAR = 64.0;
 
-// e = exp(-(q + y^2) / 2) and r = exp(-u y) at y = y0 + u l (ql, yl: low parts of
-// q and y0), with the rounding of y: at a column's far end it would shift the
-// column's weights against its components.
+// e = exp(-(q + y^2) / 2), r = exp(-u y) and the step to the next run's e, s =
+// exp(-8 u y - 32 u^2) = r^8 g8, at y = y0 + u l (ql, yl: low parts of q and y0), with
+// the rounding of y: at a column's far end it would shift the column's weights
+// against its components.  LOW: s from r with its low part, since its error is
+// multiplied by the runs walked (not for d = 4, whose columns are short: it took
+// 1% of the call and changed no error).
+template <bool LOW>
 __device__ __forceinline__ void col_start(double q, double ql, double u, double y0, double yl, double l,
-                                          const double2* tab, double* e, double* r) {
+                                          const double* g8, const double2* tab, double* e, double* r, double* s) {
 #pragma clang fp contract(off)
     const double ul = u * l;
     yl += fma(u, l, -ul);
     const double y = two_sum(ul, y0, &yl);
     *e = col_weight(q, ql, y, yl, tab);
     const double ru = u * y;
-    *r = col_exp(-ru, -(fma(u, y, -ru) + u * yl), tab);
+    int k;
+    const double2 v = col_exp2(-ru, -(fma(u, y, -ru) + u * yl), tab, &k);
+    const double rh = v.x + v.y;
+    *r = ldexp(rh, k);
+    double p = rh, pl = LOW ? v.y - (rh - v.x) : 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const double p2 = p * p;
+        if (LOW) pl = fma(2.0 * p, pl, fma(p, p, -p2));
+        p = p2;
+    }
+    *s = ldexp(fma(p, g8[0], fma(pl, g8[0], p * g8[1])), 8 * k);
 }
 
 // Lags with |y|^2 above this are dropped: exp(-|y|^2 / 2) below 1e-30, and for
@@ -276,10 +300,11 @@ __device__ __forceinline__ double col_gauss(double (&S)[D][D], const double* del
     ColGauss<D>* g = &it->g[k];
     // (the narrowest kernels are evaluated lag by lag and read no tables)
     const double u = fmin(li[tri(D - 1, D - 1)] * delta[col_axis(D, D - 1)], 1.0);
-    const double2 v = col_exp_ku2(t < COL_RUN ? 0.5 * (double)(t * t) : (t == COL_RUN ? 8.0 : 32.0), u, tab);
+    const double2 v =
+        col_exp_ku2(t < COL_RUN ? 0.5 * (double)(t * t) : t == COL_RUN ? 8.0 : t == COL_RUN + 1 ? 32.0 : 64.0, u, tab);
     if (t < COL_RUN) g->gt[t] = v.x;
-    if (t == COL_RUN || t == COL_RUN + 1) {
-        double* d = t == COL_RUN ? g->h : g->g8;
+    if (t >= COL_RUN && t < COL_RUN + 3) {
+        double* d = t == COL_RUN ? g->h : t == COL_RUN + 1 ? g->g8 : g->h8;
         d[0] = v.x;
         d[1] = v.y;
     }
@@ -540,7 +565,7 @@ struct ColScvAcc {
         for (int k = 0; k < 2; ++k) m[k][0] = m[k][1] = m[k][2] = 0.0;
     }
     // a run of COL_RUN rows: values a, start e and ratio r, y = yE + u (t + 1)
-    __device__ __forceinline__ void run(int k, const double* a, const double* g, double e, double r, double yE,
+    __device__ __forceinline__ void run(int k, const double* a, const double* g, double e, double r, double yE, double,
                                         double u) {
         double S0 = 0.0, S1 = 0.0, S2 = 0.0;
 #pragma unroll
@@ -562,8 +587,8 @@ struct ColScvAcc {
             m[k][2] = fma(u * us, fma(2.0, S2, -S1), m[k][2]);
         }
     }
-    // one lag: weight w, walked component y
-    __device__ __forceinline__ void lag(int k, double w, double y) {
+    // one lag: weight w, walked component y (its low part not used)
+    __device__ __forceinline__ void lag(int k, double w, double y, double) {
         m[k][0] += w;
         if constexpr (MODE != 0) {
             m[k][1] = fma(w, y, m[k][1]);
@@ -597,7 +622,11 @@ struct ColScvAcc {
 template <int D, int K, int N_GS>
 struct ColHermAcc {
     static constexpr int NGS = N_GS;
-    static constexpr bool EXACT = D >= 3;
+    // LOW: the walked components with their low parts, the polynomials to first
+    // order in them (He_i' = i He_{i-1}): sums of order 4 and more cancel to 1/100 and
+    // less of their terms (psi_4, M = 64, six samples: 7.7e-15 -> 6.6e-15; replayed
+    // call 16.6 -> 18.2 us).
+    static constexpr bool EXACT = D >= 3, LOW = D == 3 && K >= 4;
     using T = HermTab<D, K>;
     static constexpr int NA = T::NU;
     double v[NGS][NA];
@@ -620,19 +649,25 @@ struct ColHermAcc {
 #pragma unroll
         for (int i = 2; i <= K; ++i) he[i] = i == 2 ? fma(y, y, -1.0) : fma(y, he[i - 1], -(double)(i - 1) * he[i - 2]);
     }
-    __device__ __forceinline__ void lag(int k, double w, double y) {
+    __device__ __forceinline__ void lag(int k, double w, double y, double yl) {
         double he[K + 1];
         hermite(y, he);
         m[k][0] += w;
 #pragma unroll
         for (int i = 1; i <= K; ++i) m[k][i] = fma(w, he[i], m[k][i]);
+        if constexpr (LOW) {
+            const double d = w * yl;
+#pragma unroll
+            for (int i = 1; i <= K; ++i) m[k][i] = fma(d * i, he[i - 1], m[k][i]);
+        }
     }
-    __device__ __forceinline__ void run(int k, const double* a, const double* g, double e, double r, double yE,
+    __device__ __forceinline__ void run(int k, const double* a, const double* g, double e, double r, double yE, double yl,
                                         double u) {
 #pragma unroll
         for (int t = 0; t < COL_RUN; ++t) {
             const double w = e * (t == 0 ? a[0] : a[t] * g[t]);
-            lag(k, w, fma(u, (double)(t + 1), yE));
+            const double y = fma(u, (double)(t + 1), yE);
+            lag(k, w, y, LOW ? fma(u, (double)(t + 1), yE - y) + yl : 0.0);
             e *= r;
         }
     }
@@ -692,7 +727,7 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
 #pragma unroll
             for (int k = 0; k < NGS; ++k) {
                 const double y = uw[k] * (double)l;
-                if (fabs(y) < COL_FAR) acc.lag(k, exp(-0.5 * y * y) * a, y);
+                if (fabs(y) < COL_FAR) acc.lag(k, exp(-0.5 * y * y) * a, y, 0.0);
             }
         }
 #pragma unroll
@@ -709,7 +744,7 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
         const int j0 = lm[0] / n0;
         const ColUnits<D> un(lm, N, SMALL, D >= 3 ? j0 + (lag0(j0) <= lm[0] ? 1 : 0) : 1);
         const double iu = 1.0 / uw[0];
-        double g[NGS][COL_RUN], hh[NGS][2], g8[NGS][2];
+        double g[NGS][COL_RUN], hh[NGS][2], h8[NGS][2];
 #pragma unroll
         for (int k = 0; k < NGS; ++k) {
 #pragma unroll
@@ -717,7 +752,7 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 hh[k][i] = wave_uniform(it.g[k].h[i]);
-                g8[k][i] = wave_uniform(it.g[k].g8[i]);
+                h8[k][i] = wave_uniform(it.g[k].h8[i]);
             }
         }
         const uint32_t strideP = (uint32_t)Pw * (uint32_t)N;   // elements of a plane
@@ -838,19 +873,21 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
             };
             acc.begin();
             if (near1) {
-                double e[NGS], r[NGS];
+                double e[NGS], r[NGS], st[NGS];
                 const double ls = (double)(s0 + COL_RUN * (cb >= 0 ? ca : 0));
 #pragma unroll
-                for (int k = 0; k < NGS; ++k) col_start(q[k], ql[k], uw[k], yE[k], yl[k], ls, s_exp, &e[k], &r[k]);
+                for (int k = 0; k < NGS; ++k)
+                    col_start<(D < 4)>(q[k], ql[k], uw[k], yE[k], yl[k], ls, it.g[k].g8, s_exp, &e[k], &r[k], &st[k]);
                 auto run = [&](int c, const double* av) {
                     if (c < ca) return;   // the lane's column starts in a later run
                     const double before = (double)(s0 + COL_RUN * c - 1);
 #pragma unroll
                     for (int k = 0; k < NGS; ++k) {
-                        acc.run(k, av, g[k], e[k], r[k], fma(uw[k], before, yE[k]), uw[k]);
-                        const double r2 = r[k] * r[k], r4 = r2 * r2, r8 = r4 * r4;
+                        const double yb = fma(uw[k], before, yE[k]);
+                        acc.run(k, av, g[k], e[k], r[k], yb, fma(uw[k], before, yE[k] - yb) + yl[k], uw[k]);
+                        e[k] *= st[k];
                         // (exact products with the high parts)
-                        e[k] *= fma(r8, g8[k][0], r8 * g8[k][1]);
+                        st[k] = fma(st[k], h8[k][0], st[k] * h8[k][1]);
                         r[k] = fma(r[k], hh[k][0], r[k] * hh[k][1]);
                     }
                 };
@@ -881,7 +918,7 @@ __device__ __forceinline__ void col_walk(const ColGeom& geo, int ch, const ColIt
                             double low = yl[k] + fma(uw[k], (double)l, -ul);
                             const double yw = two_sum(ul, yE[k], &low);
                             if (guarded && fabs(yw) >= COL_FAR) continue;
-                            acc.lag(k, col_weight(q[k], ql[k], yw, low, s_exp) * a, yw);
+                            acc.lag(k, col_weight(q[k], ql[k], yw, low, s_exp) * a, yw, low);
                         }
                     }
                 };
