@@ -94,8 +94,51 @@ def flops_per_run(N, d=2):
 def col_walk_flops_per_lag():
     """FP64 flops of the column walk (variants 5, 6) at one lag, two Gaussians:
     the run coefficient (1) and three Horner steps (2 each), and per run of 8
-    lags the fold of its three sums (16) and the step to the next run (8)."""
-    return 2 * (1 + 3 * 2 + (16 + 8) / 8)
+    lags the fold of its three sums (16) and the step to the next run (7)."""
+    return 2 * (1 + 3 * 2 + (16 + 7) / 8)
+
+
+def column_walk_lags(M, delta, reach, G, L):
+    """Lags the column walk covers for one SCV candidate H = L L^T with pilot G
+    (L = None: the constant term's 2G) on a grid of M nodes with spacing delta:
+    the half lag set (axis 0 from 0 on; d = 2: the walked axis) inside the box of
+    the widest Gaussian's 1e-30 ellipsoid and of the lags the data reach, and of each
+    column along axis d-2 the runs of 8 lags that hold a lag of the ellipsoid.
+    The neighbours of a 16-lag block are walked over their common interval; what a
+    lane does outside its own is not counted."""
+    d = len(M)
+    assert d >= 2
+    cut2 = 2.0 * np.log(1e30)
+    axes = list(range(d - 2)) + [d - 1, d - 2]           # the walked axis last
+    S = 2.0 * G if L is None else 2.0 * (L @ L.T) + 2.0 * G
+    S = S[np.ix_(axes, axes)]
+    li = np.linalg.inv(np.linalg.cholesky(S))
+    ld = li * np.asarray(delta)[axes]
+    box = [int(min(np.floor(np.sqrt(cut2 * S[p, p]) / delta[k]) + 1, reach[k])) for p, k in enumerate(axes)]
+    lags = [np.arange(0 if p == 0 and d > 2 else -box[p], box[p] + 1) for p in range(d - 1)]
+    cols = np.meshgrid(*lags, indexing="ij")
+    y = [sum(ld[p, j] * cols[j] for j in range(min(p, d - 2) + 1)) for p in range(d)]
+    q = sum(v * v for v in y[:-1])
+    live = q <= cut2
+    u = ld[-1, -1]
+    hw, ctr = np.sqrt(cut2 - q[live]) / u, -y[-1][live] / u
+    first = 0 if d == 2 else -box[-1]
+    fa, fb = np.maximum(np.floor(ctr - hw), first), np.minimum(np.ceil(ctr + hw), box[-1])
+    some = fa <= fb
+    return int(8 * (np.floor(fb[some] / 8) - np.floor(fa[some] / 8) + 1).sum())
+
+
+def data_reach(lo, hi, M, delta):
+    """Largest lag per axis at which the counts of data within [lo, hi] can meet (the
+    library cuts the walk there): two nodes more than the data span."""
+    return [int(min(np.floor((b - a) / dk) + 2, m - 1)) for a, b, m, dk in zip(lo, hi, M, delta)]
+
+
+def unvech(v, d):
+    """The lower triangle whose columns are v."""
+    L = np.zeros((d, d))
+    L[np.triu_indices(d)[1], np.triu_indices(d)[0]] = v
+    return L
 
 
 def algorithmic_flops_per_candidate(M, N, d=2, variant=0, rows=None):
@@ -329,16 +372,24 @@ def main():
         torch.cuda.synchronize()
 
     # ---- roofline of the dominant kernel (batched SCV objective+gradient launch)
-    # work of the launch: the compacted walk (variants 5, 6) visits only the
-    # runs with a lag above 1e-30 of some Gaussian's peak, counted on the device
-    # for these candidates (and the constant term's pseudo-candidate); the
-    # other lag-domain variants walk every run of every row
+    # work of the launch: the column walk (variants 5, 6) covers only the lags above
+    # 1e-30 of the widest Gaussian's peak that the data reach, counted here for
+    # these candidates (and the constant term's pseudo-candidate); the other
+    # lag-domain variants walk every run of every row
     RL = moment_walk_layout(N)[0]
-    all_runs = (B + 1) * M * (N // RL)
-    walked_runs = kf.scv_walk_runs([ds], vechL) if variant >= 5 else all_runs
-    flops = (walked_runs * RL * col_walk_flops_per_lag() if variant >= 5
-             else walked_runs * flops_per_run(N, d) if variant >= 3
-             else algorithmic_flops_per_candidate(M, N, d, variant) * B)
+    all_lags = (B + 1) * M * N
+    if variant >= 5:
+        delta = [float(v) for v in g.delta[:d]]
+        reach = data_reach(X_h.min(axis=0), X_h.max(axis=0), [M] * d, delta)
+        walked_lags = sum(column_walk_lags([M] * d, delta, reach, Gp, unvech(v, d))
+                          for v in vechL.cpu().numpy()) + column_walk_lags([M] * d, delta, reach, Gp, None)
+        walk = {"lags_walked": walked_lags, "lags_all": all_lags, "flops_per_lag": col_walk_flops_per_lag()}
+        flops = walked_lags * col_walk_flops_per_lag()
+    else:
+        walk = {"lags_walked": all_lags, "lags_all": all_lags,
+                "flops_per_lag": flops_per_run(N, d) / RL if variant >= 3 else None}
+        flops = (all_lags // RL * flops_per_run(N, d) if variant >= 3
+                 else algorithmic_flops_per_candidate(M, N, d, variant) * B)
     achieved = flops / (scv_ms * 1e-3)
     spec_flops = algorithmic_flops_per_candidate(M, N, d, spec_variant) * B
     traffic = None
@@ -361,8 +412,7 @@ def main():
                 "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_VECTOR, "traffic": traffic,
                 "kernel": kname, "launch_ms": scv_ms, "call_ms": scv_call_ms,
                 "flops_per_launch": flops, "variant": variant,
-                "walk": {"runs_walked": walked_runs, "runs_all": all_runs, "lags_per_run": RL,
-                         "flops_per_run": flops_per_run(N, d)},
+                "walk": walk,
                 "direct_evaluation_equivalent": {
                     "flops_per_launch": direct_equivalent_flops_per_candidate(M, d) * B,
                     "rate_tflops": direct_equivalent_flops_per_candidate(M, d) * B / (scv_ms * 1e-3) / 1e12}}
@@ -614,9 +664,14 @@ def main_case5(a):
     roofline = None
     if variant >= 3:
         rows = M * (2 * M - 1) ** (d - 2)
-        if variant >= 5:   # the compacted walk: the runs it visits, counted on the device
-            flops = (kf.scv_walk_runs(dss, vech, per_ds=per) * moment_walk_layout(P_last)[0]
-                     * col_walk_flops_per_lag())
+        if variant >= 5:   # the column walk: the lags it covers, from every 8th candidate of each dataset
+            lags = 0.0
+            for ds, X, Gp, H in zip(dss, Xs, w.G_pilot, w.H):
+                delta = [float(v) for v in ds.grid.delta[:d]]
+                reach = data_reach(X.amin(0).tolist(), X.amax(0).tolist(), [M] * d, delta)
+                some = [column_walk_lags([M] * d, delta, reach, Gp, np.linalg.cholesky(h)) for h in H[::8]]
+                lags += np.mean(some) * len(H) + column_walk_lags([M] * d, delta, reach, Gp, None)
+            flops = lags * col_walk_flops_per_lag()
         else:
             flops = B * algorithmic_flops_per_candidate(M, P_last, d=d, variant=variant, rows=rows)
         roofline = {"bound": "alu", "kernel": (f"k_cols_scv<{d},1,false> variant {variant}" if variant >= 5

@@ -310,11 +310,13 @@ int kdefft_crit_batch(const kdefft_dataset* ds_host, int n_ds, const int64_t* h_
                       const double* vechL, int crit, int r, double* obj, double* grad,
                       int32_t* status, void* ws, size_t ws_bytes, void* stream);
 
-/* Work of the compacted lag walk (row-kernel variants 5 and 6) for the SCV
- * objective + gradient of these candidates (Sec. 4, Eq. (17)-(18) in the lag
- * domain): the number of runs of kdefft_lag_layout(P_{d-1}, 1) positions that
- * hold a lag whose Gaussians reach 1e-30 of their peak -- the runs the walk
- * visits -- summed over all candidates and each dataset's constant term.
+/* Size of the live lag set of these candidates' SCV objective + gradient
+ * (Sec. 4, Eq. (17)-(18) in the lag domain), by rows: the number of runs of
+ * kdefft_lag_layout(P_{d-1}, 1) positions of the last axis that hold a lag at which
+ * one of the two Gaussians reaches 1e-30 of its peak, summed over all
+ * candidates and each dataset's constant term.  (No kernel walks these runs:
+ * variants 3 and 4 walk every run, 5 and 6 columns along axis d-2, and only as
+ * far as the data reach.)
  * *runs_host receives the sum.  Arguments and workspace as in
  * kdefft_scv_batch.  Synchronizes `stream` (a measurement helper). */
 int kdefft_scv_walk_runs(const kdefft_dataset* ds_host, int n_ds, const int64_t* h_offsets_host,
@@ -412,10 +414,10 @@ int kdefft_scv_plain(const kdefft_dataset* ds_host, const double* H_host, double
  * (found in closed form per column; the dropped terms are far below float64
  * rounding of the result), and the launch builds the candidates' parameters
  * itself.  Variant 5 with one block per work item is the untuned default of the
- * SCV families.  The psi family, and the eta families up to r = 2 (d = 4: r =
- * 1), walk columns for every variant from 3 on; the eta families of higher
- * order treat 3 to 6 alike (every lag of every row) and no eta family has
- * spectral variants.  The untuned default of those families is variant 3, grid 0.
+ * SCV families.  The psi family walks columns for every variant from 3 on.  The
+ * eta families take variants 3 and 4 only (any other is KDEFFT_E_UNSUPPORTED),
+ * which are one kernel: columns up to r = 2 (d = 4: r = 1), every lag of every
+ * row above.  The untuned default of those families is variant 3, grid 0.
  * variant = -1 drops the pinned (or tuned) choice of that key, so the untuned
  * default applies again.  Used by kdefft_autotune and by tests that cover
  * every variant.  Host only. */

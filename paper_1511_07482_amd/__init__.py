@@ -437,7 +437,7 @@ def scv(datasets: Sequence[Dataset], vechL: torch.Tensor, per_ds=None, grad: boo
 
 
 def scv_walk_runs(datasets: Sequence[Dataset], vechL: torch.Tensor, per_ds=None) -> int:
-    """Runs the compacted lag walk visits for the SCV objective + gradient of
+    """Runs of the last axis that hold a live lag of the SCV objective + gradient of
     these candidates (kdefft_scv_walk_runs; synchronizes)."""
     datasets = list(datasets)
     if len(datasets) > _lib.MAX_BATCH_DS:

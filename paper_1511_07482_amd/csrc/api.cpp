@@ -304,7 +304,7 @@ RowLaunch launch_for(int kind, int d, int r, int N, int crit = 0) {
     auto it = g_launch.find(LaunchKey{dev, kind, d, r, N, crit});
     if (it != g_launch.end()) return it->second;
     // untuned default: the lag-domain evaluation (fewest operations, no LDS);
-    // for the SCV families the compacted walk, one block per work item (it
+    // for the SCV families the column walk, one block per work item (it
     // builds its own parameter blocks)
     const bool mom = kind == FUN_SCV_OBJ || kind == FUN_SCV_OBJGRAD || kind == FUN_SCV_GRAD;
     return mom ? RowLaunch{5, -1} : RowLaunch{3, 0};
@@ -1279,7 +1279,7 @@ static int crit_common(const kdefft_dataset* ds, int n_ds, const int64_t* off, c
     const int npseudo = (crit == KDEFFT_CRIT_SCV && kind != FUN_SCV_GRAD) ? n_ds : 0;
     const int64_t nc = B + npseudo;
     if (walk_runs) {
-        // the live runs of every candidate (the compacted walk's work), summed
+        // the runs of the last axis with a live lag, summed over the candidates
         const RowGeom geo = make_geom(g, kind, kr, nc, 3);
         HIPCHK(launch_scv_setup(vechL, a, B, npseudo, b.prm, status, geo, b.wc, s), "criterion setup");
         std::vector<int32_t> wc((size_t)nc);

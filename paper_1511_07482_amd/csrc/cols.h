@@ -36,8 +36,8 @@
 // load touches four lines; a row-wise walk (one lane per row run) touches 64
 // and folds 25 flops per Hessian entry into every run.  Whole SCV
 // objective-and-gradient call, replayed: d = 2, M = 256, 256 candidates 53.1 ->
-// 36.9 us, 4 candidates 23.6 -> 16.2 us; d = 3, M = 64, 64 candidates 150 ->
-// 57 us; d = 4, M = 32, four datasets of 64 candidates 3618 -> 884 us (row walk
+// 37.0 us, 4 candidates 23.6 -> 16.2 us; d = 3, M = 64, 64 candidates 150 ->
+// 57 us; d = 4, M = 32, four datasets of 64 candidates 3618 -> 906 us (row walk
 // -> column walk; 979 before the walk was cut to the lags that the data reach).
 //
 // Live set: a lag is walked when its first Gaussian is at or above the cut of
@@ -169,7 +169,8 @@ static __device__ const double2 COL_EXP2[32] = {
     {1.8340080864093424, 3.283107224245627e-17}, {1.8741676341103, -6.122763413004143e-17},
     {1.9152065613971474, -1.0619946056195963e-16}, {1.9571441241754002, 8.960767791036668e-17}};
 
-// exp(x + xl) for a small correction xl: x = (32 k + j) log 2 / 32 + r,
+// exp(x + xl) for a small correction xl, by the table-driven method of P. T. P.
+// Tang (ACM Trans. Math. Softw. 15, 1989): x = (32 k + j) log 2 / 32 + r,
 // |r| < 0.011, 2^(j/32) from the table (a copy in LDS), the series of exp(r) to
 // r^6.  One rounding of any weight, so the error is that of one rounding and
 // without a bias; a bias of the start's r would be multiplied by the lags

@@ -487,8 +487,8 @@ constexpr int mom_run_of() { return N >= 256 ? 16 : LAG_RUN; }
 template <int N, int RL>
 constexpr int mom_seg_of() { return N >= 256 && RL <= 32 && (N / 2) % 32 == 0 ? 32 / RL : 1; }
 
-// Relative cut of the compacted lag walk: a run is walked only if some of its
-// lags x has c_k exp(-x^T S_k^{-1} x / 2) >= 1e-30 c_k for some Gaussian k of
+// Relative cut of the column walk and of the live-run count: a lag counts only if
+// x has c_k exp(-x^T S_k^{-1} x / 2) >= 1e-30 c_k for some Gaussian k of
 // the family (log 1e-30 below).  The dropped values are each below 1e-30 of
 // their Gaussian's peak, so all of them together (times the moment-form
 // polynomial factors, at most a few hundred times P) stay below 1e-30 x (number
