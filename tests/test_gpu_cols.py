@@ -1,6 +1,6 @@
 """The column walk (SCV families: launch variants 5 and 6; psi_r; eta_r of low
-order) at the edges of its units -- 16-lag blocks of the last axis, runs of 8 rows, segments of 32
-(d = 2) or 64 rows, walked axes shorter than a run -- against the oracle's
+order) at the edges of its units -- 16-lag blocks of the last axis, runs of 8 rows, segments of 64
+rows, walked axes shorter than a run -- against the oracle's
 binned criterion on the same counts, for narrow kernels (a fraction of a grid
 step: evaluated lag by lag), ordinary and wide ones.
 
